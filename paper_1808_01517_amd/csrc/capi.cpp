@@ -149,7 +149,7 @@ struct dlm_lsc_plan {
   double alpha = 0, lambda = 0;
   std::vector<double> g, points, Bnb, Pm;
   std::vector<double> Q, pm1;  // Q[t][k][j] = (P_m B_t)[k][j]; pm1 = P_m 1
-  DevMat dBnb, dBnbT, dPm, dPmT, dQ, dpm1;
+  DevMat dBnb, dBnbT, dPm, dPmT, dQ, dQT, dpm1;  // dQT: [T][K_in][K_out]
 };
 
 namespace {
@@ -754,6 +754,13 @@ dlm_status dlm_lsc_plan_create(const double *sampled_gradients, int64_t m, int s
   std::vector<float> sf;
   std::vector<uint16_t> shh;
   bool good = upload(p->dQ, p->Q, T, Ko * Ki, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
+  {
+    std::vector<double> qt(p->Q.size());
+    for (int t = 0; t < T; ++t)
+      for (int k = 0; k < Ko; ++k)
+        for (int j = 0; j < Ki; ++j) qt[(size_t(t) * Ki + j) * Ko + k] = p->Q[(size_t(t) * Ko + k) * Ki + j];
+    good = good && upload(p->dQT, qt, T, Ko * Ki, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
+  }
   good = good && upload(p->dpm1, p->pm1, 1, Ko, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
   good = good && upload(p->dBnb, p->Bnb, int(P), p->K_in, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
   good = good && upload(p->dBnbT, transpose(p->Bnb, int(P), p->K_in), p->K_in, int(P), nullptr, sf, shh) &&
@@ -793,6 +800,7 @@ void dlm_lsc_plan_destroy(dlm_lsc_plan *p) {
   release(p->dPm);
   release(p->dPmT);
   release(p->dQ);
+  release(p->dQT);
   release(p->dpm1);
   delete p;
 }
@@ -862,6 +870,7 @@ struct FoldWs {
 };
 
 constexpr int kFoldSplitMax = 128;
+constexpr int kUnfoldSplits = 2;  // partial weight gradients the unfold adds up itself, at most
 
 // The folded matrices (float32 and bfloat16 copies) keep rows padded with
 // zeros to a multiple of 32 entries: the streaming core copies whole
@@ -919,29 +928,32 @@ dlm_status dlm_lsc_workspace_bytes(const dlm_lsc_plan *p, int C, int O, int64_t 
 
 namespace {
 
-// The folded matrix for one use: T (forward, `transposed` false) or T^T
-// (input gradient), in the precision's storage only (float32 or bfloat16),
-// with its row padding zeroed.
+// The folded matrix for one use: T and the folded bias (forward, `transposed`
+// false) or T^T (input gradient), in the precision's storage only (float32 or
+// bfloat16), with its row padding zeroed.
 dlm_status fold_weights(const dlm_lsc_plan *p, int C, int O, const float *W, const float *bias, const FoldWs &w,
                         bool transposed, dlm_precision prec, void *stream) {
   const double KK = double(p->K_out) * p->K_in, M = double(O) * p->K_out, CK = double(C) * p->K_in;
-  const bool bf = prec == DLM_BF16;
-  {
-    TimedScope ts("lsc_fold", stream, (double(O) * C * p->T + p->T * KK) * 4.0 + M * CK * (bf ? 2.0 : 4.0),
-                  2.0 * O * C * KK * p->T);
-    const size_t M_ = size_t(O) * p->K_out, CK_ = size_t(C) * p->K_in;
-    const size_t esz = bf ? 2 : 4;
-    void *table = transposed ? (bf ? (void *)w.TwTh : (void *)w.TwT) : (bf ? (void *)w.Twh : (void *)w.Tw);
-    const size_t rows = transposed ? CK_ : M_, cols = transposed ? M_ : CK_;
-    if (launch_zero_cols(table, int64_t(rows), int64_t(cols * esz), int64_t(pad32(cols) * esz), stream) != 0)
-      return launched(-1);
-    float *Tw = !transposed && !bf ? w.Tw : nullptr, *TwT = transposed && !bf ? w.TwT : nullptr;
-    uint16_t *Twh = !transposed && bf ? w.Twh : nullptr, *TwTh = transposed && bf ? w.TwTh : nullptr;
-    if (launch_lsc_fold(W, p->dQ.f32, C, O, p->T, p->K_in, p->K_out, Tw, TwT, Twh, TwTh, int64_t(pad32(CK_)),
-                        int64_t(pad32(M_)), stream) != 0)
-      return launched(-1);
+  FoldOut f;
+  f.W = W;
+  f.Q = transposed ? p->dQT.f32 : p->dQ.f32;
+  f.C = C;
+  f.O = O;
+  f.T = p->T;
+  f.Ki = p->K_in;
+  f.Ko = p->K_out;
+  f.transposed = transposed;
+  f.bf16 = prec == DLM_BF16;
+  f.out = transposed ? (f.bf16 ? (void *)w.TwTh : (void *)w.TwT) : (f.bf16 ? (void *)w.Twh : (void *)w.Tw);
+  f.ld = int64_t(pad32(transposed ? size_t(O) * p->K_out : size_t(C) * p->K_in));
+  if (!transposed) {
+    f.bias = bias;
+    f.pm1 = p->dpm1.f32;
+    f.bvec = w.bvec;
   }
-  return launched(launch_lsc_bias_vec(bias, p->dpm1.f32, O, p->K_out, w.bvec, stream));
+  TimedScope ts("lsc_fold", stream, (double(O) * C * p->T + p->T * KK) * 4.0 + M * CK * (f.bf16 ? 2.0 : 4.0),
+                2.0 * O * C * KK * p->T);
+  return launched(launch_lsc_fold(f, stream));
 }
 
 dlm_status lsc_fwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const float *W, const float *bias, int O,
@@ -1042,13 +1054,19 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
       }
       if (s != DLM_OK) return s;
     }
-    {
+    // Few partial matrices are added up as the unfold reads them; many (the
+    // narrow layers' 100 MB of them) go through a pass of their own that
+    // spreads over the chip, which O C blocks would not.
+    const float *dT = w.part;
+    if (splits > kUnfoldSplits || splits == 0) {
       TimedScope ts("lsc_fold_reduce", stream, double(M) * N1 * 4.0, double(splits) * M * N1);
       if ((s = launched(launch_sum_partials(w.part, splits, int64_t(M) * N1, w.dTw, stream))) != DLM_OK) return s;
+      dT = w.dTw;
+      splits = 1;
     }
     TimedScope ts("lsc_unfold", stream, (double(M) * N1 + p->T * double(p->K_out) * p->K_in + double(O) * C * p->T) * 4.0,
                   2.0 * O * C * p->T * double(p->K_out) * p->K_in);
-    if ((s = launched(launch_lsc_unfold(w.dTw, p->dQ.f32, p->dpm1.f32, C, O, p->T, p->K_in, p->K_out, dW, dbias,
+    if ((s = launched(launch_lsc_unfold(dT, splits, p->dQ.f32, p->dpm1.f32, C, O, p->T, p->K_in, p->K_out, dW, dbias,
                                         stream))) != DLM_OK)
       return s;
   }

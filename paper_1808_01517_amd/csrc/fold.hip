@@ -1,0 +1,278 @@
+// Kernel-tensor side of the folded LSC layer (Sec. 2.3: resampling, cyclic
+// kernel dot and refit composed into one matrix per layer).
+//
+//   fold:    T[(o,k)][(c,j)] = sum_t W[o][c][t] Q[t][k][j]      (or T^T)
+//   unfold:  dW[o][c][t]     = sum_{k,j} dT[(o,k)][(c,j)] Q[t][k][j]
+//            db[o]           = sum_k dT[(o,k)][C K_in] (P_m 1)[k]
+//
+// Both are thin (17 taps) contractions against the small table Q (138 KB at
+// order 8, L2-resident); what they cannot do without is one pass over the
+// O K_out x C K_in matrix, so they are laid out for that pass.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "gemm_common.h"
+#include "internal.h"
+
+namespace dlm {
+namespace fold {
+
+constexpr int kPairs = 8;  // (o, c) pairs per block of the fold
+constexpr int kTaps = 32;  // taps held in registers at a time
+
+// Store one entry of the folded matrix.
+template <bool BF16>
+__device__ __forceinline__ void put(void *out, int64_t at, float v) {
+  if constexpr (BF16) static_cast<uint16_t *>(out)[at] = to_bf16_bits(v);
+  else static_cast<float *>(out)[at] = v;
+}
+
+// A thread owns one (k, j) entry of Q for all taps, in registers, and runs
+// through kPairs (o, c) pairs, whose taps the block keeps in LDS (one address
+// per wave: broadcasts); consecutive threads write consecutive columns.  TR
+// writes T^T from the transposed table (Q is then [t][j][k]), so its columns
+// are consecutive too.  Row padding (columns ncol .. ld - 1, zeros) and the folded
+// bias are written by the blocks of the last grid column of the same launch.
+// Inside a group of 16 the taps are added in the order 0 4 8 12, 1 5 9 13, ..
+// (that of four 16x16x4 matrix instructions whose lane group g holds taps 4 g
+// .. 4 g + 3), so the rounding of the table is the same whichever kernel
+// makes it.  It is bound by the stores' address and issue work.  64 -> 64
+// channels in BF16 45.8 -> 19.5 us, 32 -> 64 in FP32 25.9 -> 12.7 us, 3 -> 32
+// 9.6 -> 5 us against a matrix-core GEMM with a 17-deep reduction and
+// element-wise scattered stores, which also needed a launch each for the
+// padding and the bias (2-5 us).
+template <bool TR, bool BF16>
+__global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *Q, int C, int O, int T, int Ki, int Ko,
+                                                   void *out, int64_t ld, const float *bias, const float *pm1,
+                                                   float *bvec, int nbE) {
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x == nbE) {
+    const int64_t id = (int64_t)blockIdx.y * 256 + tid, nth = (int64_t)gridDim.y * 256;
+    const int64_t rows = TR ? (int64_t)C * Ki : (int64_t)O * Ko, ncol = TR ? (int64_t)O * Ko : (int64_t)C * Ki;
+    const int64_t pad = ld - ncol;
+    for (int64_t i = id; i < rows * pad; i += nth) {
+      const int64_t r = i / pad;
+      put<BF16>(out, r * ld + ncol + (i - r * pad), 0.0f);
+    }
+    if (bvec)
+      for (int64_t i = id; i < (int64_t)O * Ko; i += nth) {
+        const int o = (int)(i / Ko), k = (int)i - o * Ko;
+        bvec[i] = bias ? bias[o] * pm1[k] : 0.0f;
+      }
+    return;
+  }
+  __shared__ float taps[kPairs][kTaps];
+  static_assert(kPairs * kTaps == 256, "one tap per thread");
+  const int KK = Ko * Ki, e = blockIdx.x * 256 + tid;
+  const int nq = TR ? Ko : Ki, np = TR ? Ki : Ko;  // columns, rows of one pair's block
+  const int p = e / nq, q = e - p * nq;
+  const int Y = TR ? O : C, pairs = C * O;
+  const int p0 = blockIdx.y * kPairs;
+  float acc[kPairs];
+#pragma unroll
+  for (int i = 0; i < kPairs; ++i) acc[i] = 0.0f;
+  for (int t0 = 0; t0 < T; t0 += kTaps) {
+    // the pairs' taps t0 .. t0 + kTaps - 1, zeros beyond T
+    __syncthreads();
+    {
+      const int i = tid / kTaps, t = tid - i * kTaps;
+      const int x = (p0 + i) / Y, y = (p0 + i) - x * Y;
+      taps[i][t] = p0 + i < pairs && t0 + t < T ? W[((int64_t)(TR ? y : x) * C + (TR ? x : y)) * T + t0 + t] : 0.0f;
+    }
+    float qv[kTaps];
+#pragma unroll
+    for (int t = 0; t < kTaps; ++t) qv[t] = e < KK && t0 + t < T ? Q[(int64_t)(t0 + t) * KK + e] : 0.0f;
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < kTaps; h += 16)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (t0 + h + j >= T) break;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int i = 0; i < kPairs; ++i) acc[i] = fmaf(taps[i][h + 4 * g + j], qv[h + 4 * g + j], acc[i]);
+      }
+  }
+  if (e >= KK) return;
+  int x = p0 / Y, y = p0 - x * Y;
+#pragma unroll
+  for (int i = 0; i < kPairs; ++i) {
+    if (p0 + i >= pairs) break;
+    put<BF16>(out, ((int64_t)x * np + p) * ld + (int64_t)y * nq + q, acc[i]);
+    if (++y == Y) {
+      y = 0;
+      ++x;
+    }
+  }
+}
+
+// dW of PC channels c of one output channel per block: the block reads their
+// K_out x K_in gradients once (adding up the SP partial matrices as it reads),
+// keeps them in registers and runs through its taps of Q, TB at a time, which
+// the PC pairs share.  Few pairs (PC = 1) also split the taps over blocks.
+// It is bound by the latency of its loads and of the wave sums.  64 -> 64
+// channels 135 + 15 + 7 us (a wave per (o, c, t), the partial sums and the
+// bias gradient in kernels of their own) -> 41.6 us in one launch, 32 -> 64
+// with two partials 72.6 + 11 + 15 -> 28.4 us, 3 -> 32 15.5 + 15.2 -> 5.4 us.
+constexpr int kChunk = 2048;  // gradient entries held by a block at a time
+constexpr int kTapBlock = 4;  // taps per step
+
+template <int PC, int SP>
+__global__ __launch_bounds__(256) void unfold_kernel(const float *part, int64_t mstride, const float *Q,
+                                                     const float *pm1, int C, int O, int T, int Ki, int Ko, int N1,
+                                                     float *dW, float *db, int nb) {
+  constexpr int PER = kChunk / 256, TB = kTapBlock;
+  __shared__ float red[4][PC * TB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if ((int)blockIdx.x >= nb) {  // the bias gradient, one wave per output channel
+    const int o = ((int)blockIdx.x - nb) * 4 + wave;
+    if (o >= O || blockIdx.y != 0) return;
+    float s = 0.0f;
+    for (int k = lane; k < Ko; k += 64) {
+      const float *g = part + ((int64_t)o * Ko + k) * N1 + (N1 - 1);
+      float v = 0.0f;
+#pragma unroll
+      for (int p = 0; p < SP; ++p) v += g[p * mstride];
+      s += v * pm1[k];
+    }
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) db[o] = s;
+    return;
+  }
+  const int cb = (C + PC - 1) / PC, KK = Ko * Ki;
+  const int o = blockIdx.x / cb, c0 = (blockIdx.x - o * cb) * PC;
+  float g[PC][PER];
+  auto load = [&](int base) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = base + i * 256 + tid;
+      const int kk = e / Ki, j = e - kk * Ki;
+      const float *src = part + ((int64_t)o * Ko + kk) * N1 + (int64_t)c0 * Ki + j;
+#pragma unroll
+      for (int c = 0; c < PC; ++c) {
+        g[c][i] = 0.0f;
+        if (e < KK && c0 + c < C) {
+#pragma unroll
+          for (int p = 0; p < SP; ++p) g[c][i] += src[p * mstride + c * Ki];
+        }
+      }
+    }
+  };
+  const bool one = KK <= kChunk;
+  if (one) load(0);
+  for (int t0 = blockIdx.y * TB; t0 < T; t0 += gridDim.y * TB) {
+    float s[PC][TB];
+#pragma unroll
+    for (int c = 0; c < PC; ++c)
+#pragma unroll
+      for (int u = 0; u < TB; ++u) s[c][u] = 0.0f;
+    for (int base = 0; base < KK; base += kChunk) {
+      if (!one) load(base);
+      float q[TB][PER];
+#pragma unroll
+      for (int u = 0; u < TB; ++u)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          const int e = base + i * 256 + tid;
+          q[u][i] = e < KK && t0 + u < T ? Q[(int64_t)(t0 + u) * KK + e] : 0.0f;
+        }
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int c = 0; c < PC; ++c)
+#pragma unroll
+          for (int u = 0; u < TB; ++u) s[c][u] = fmaf(g[c][i], q[u][i], s[c][u]);
+    }
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int c = 0; c < PC; ++c)
+#pragma unroll
+        for (int u = 0; u < TB; ++u) s[c][u] += __shfl_xor(s[c][u], off, 64);
+    if (lane == 0)
+#pragma unroll
+      for (int c = 0; c < PC; ++c)
+#pragma unroll
+        for (int u = 0; u < TB; ++u) red[wave][c * TB + u] = s[c][u];
+    __syncthreads();
+    if (tid < PC * TB) {
+      const int c = tid / TB, u = tid - c * TB;
+      if (c0 + c < C && t0 + u < T)
+        dW[((int64_t)o * C + c0 + c) * T + t0 + u] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+    }
+    __syncthreads();
+  }
+}
+
+// out[i] = sum_p part[p * n + i], in the order of p; eight loads in flight
+// per thread (one at a time took 55 us for 128 partials of 135 x 1441).
+__global__ __launch_bounds__(256) void sum_partials_kernel(const float *part, int splits, int64_t n, float *out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  float s = 0.0f;
+  int p = 0;
+  for (; p + 8 <= splits; p += 8) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(p + u) * n + i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  for (; p < splits; ++p) s += part[(int64_t)p * n + i];
+  out[i] = s;
+}
+
+}  // namespace fold
+
+int launch_lsc_fold(const FoldOut &f, void *stream) {
+  const int KK = f.Ko * f.Ki, pairs = f.C * f.O;
+  const int nbE = (KK + 255) / 256;
+  const dim3 grid(nbE + 1, (pairs + fold::kPairs - 1) / fold::kPairs);
+  hipStream_t st = (hipStream_t)stream;
+#define DLM_FOLD(TR, BF)                                                                                          \
+  hipLaunchKernelGGL((fold::fold_kernel<TR, BF>), grid, dim3(256), 0, st, f.W, f.Q, f.C, f.O, f.T, f.Ki, f.Ko, f.out, \
+                     f.ld, f.bias, f.pm1, f.bvec, nbE)
+  if (f.transposed) {
+    if (f.bf16) DLM_FOLD(true, true);
+    else DLM_FOLD(true, false);
+  } else {
+    if (f.bf16) DLM_FOLD(false, true);
+    else DLM_FOLD(false, false);
+  }
+#undef DLM_FOLD
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_sum_partials(const float *part, int splits, int64_t n, float *out, void *stream) {
+  hipLaunchKernelGGL(fold::sum_partials_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+                     part, splits, n, out);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <int SP>
+static void unfold(const float *part, const float *Q, const float *pm1, int C, int O, int T, int Ki, int Ko, float *dW,
+                   float *db, hipStream_t st) {
+  const int N1 = C * Ki + 1;
+  const int64_t ms = (int64_t)O * Ko * N1;
+  const int extra = db ? (O + 3) / 4 : 0, nb4 = O * ((C + 3) / 4);
+  // four channels per block once that still gives every compute unit a block
+  if (nb4 >= 256)
+    hipLaunchKernelGGL((fold::unfold_kernel<4, SP>), dim3(nb4 + extra), dim3(256), 0, st, part, ms, Q, pm1, C, O, T, Ki,
+                       Ko, N1, dW, db, nb4);
+  else
+    hipLaunchKernelGGL((fold::unfold_kernel<1, SP>),
+                       dim3(O * C + extra, (T + fold::kTapBlock - 1) / fold::kTapBlock), dim3(256), 0, st, part, ms, Q,
+                       pm1, C, O, T, Ki, Ko, N1, dW, db, O * C);
+}
+
+int launch_lsc_unfold(const float *part, int splits, const float *Q, const float *pm1, int C, int O, int T, int Ki,
+                      int Ko, float *dW, float *db, void *stream) {
+  hipStream_t st = (hipStream_t)stream;
+  if (splits == 1) unfold<1>(part, Q, pm1, C, O, T, Ki, Ko, dW, db, st);
+  else if (splits == 2) unfold<2>(part, Q, pm1, C, O, T, Ki, Ko, dW, db, st);
+  else return -3;
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+}  // namespace dlm

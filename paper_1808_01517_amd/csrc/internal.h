@@ -167,11 +167,6 @@ int launch_sh2s_mse(const Sh2sMse &t, dlm_precision prec, void *stream);
 constexpr int kSumBlocks = 256;
 int launch_sum_scaled(const float *partials, int64_t n, float *out, float scale, float *scratch, void *stream);
 
-// fill `bytes` (a multiple of 4) at p with zeros
-int launch_zero(void *p, size_t bytes, void *stream);
-// zero bytes [c0_bytes, ld_bytes) of each of `rows` rows ld_bytes apart (even sizes)
-int launch_zero_cols(void *p, int64_t rows, int64_t c0_bytes, int64_t ld_bytes, void *stream);
-
 // y[v][o][i] = bias[o] + sum_{c,t} W[o][c][t] X[v][c][i*T+t]
 int launch_lsc_contract_fwd(const float *X, const float *W, const uint16_t *Wh, const float *bias, float *y,
                             int64_t V, int C, int O, int m, int T, dlm_precision prec, void *stream);
@@ -204,14 +199,22 @@ int launch_adam(float *w, const float *g, float *m, float *v, int64_t n, float l
                 float c1, float c2, void *stream);
 
 // ----------------------------------------------------- folded LSC form
-// Tw[(o*Ko+k)][(c*Ki+j)] = sum_t W[o][c][t] Q[t][k][j]  (and the transpose
-// TwT[(c*Ki+j)][(o*Ko+k)]), float32 always, bfloat16 copies when non-null;
-// rows of Tw / Twh have stride ld, rows of TwT / TwTh stride ldt.
-int launch_lsc_fold(const float *W, const float *Q, int C, int O, int T, int Ki, int Ko, float *Tw, float *TwT,
-                    uint16_t *Twh, uint16_t *TwTh, int64_t ld, int64_t ldt, void *stream);
+// The folded matrix of a layer: out[(o*Ko+k)][(c*Ki+j)] = sum_t W[o][c][t]
+// Q[t][k][j], or its transpose out[(c*Ki+j)][(o*Ko+k)], in float32 or
+// bfloat16; rows of stride ld, zeros in their padding.  With bvec, also
+// bvec[o*Ko+k] = bias[o] * pm1[k] (zeros when bias is null).  Q is [t][k][j],
+// for the transpose [t][j][k].
+struct FoldOut {
+  const float *W = nullptr, *Q = nullptr;
+  int C = 0, O = 0, T = 0, Ki = 0, Ko = 0;
+  bool transposed = false, bf16 = false;
+  void *out = nullptr;
+  int64_t ld = 0;
+  const float *bias = nullptr, *pm1 = nullptr;
+  float *bvec = nullptr;
+};
+int launch_lsc_fold(const FoldOut &f, void *stream);
 int fold_grad_split_len(int64_t V, int splits);
-// bvec[o*Ko+k] = bias[o] * pm1[k]  (zero when bias is null)
-int launch_lsc_bias_vec(const float *bias, const float *pm1, int O, int Ko, float *bvec, void *stream);
 // partial[s][m][n] over voxel slice s: m = (o,k) of g = da_out (masked by
 // a_out > 0 when mask != null), n = (c,j) of a_in plus one ones-column.
 int launch_lsc_fold_grad(const float *da_out, const float *mask, const float *a_in, int64_t V, int M, int CK,
@@ -219,9 +222,10 @@ int launch_lsc_fold_grad(const float *da_out, const float *mask, const float *a_
 int fold_grad_splits(int64_t V, int M, int N1);
 // out[i] = sum_s part[s*n + i]
 int launch_sum_partials(const float *part, int splits, int64_t n, float *out, void *stream);
-// dW[(o*C+c)][t] = sum_{k,j} dTw[(o*Ko+k)][c*Ki+j] Q[t][k][j];  db[o] = sum_k dTw[(o*Ko+k)][C*Ki] pm1[k]
-int launch_lsc_unfold(const float *dTw, const float *Q, const float *pm1, int C, int O, int T, int Ki, int Ko,
-                      float *dW, float *db, void *stream);
+// dT = sum over the splits of part[s][(o*Ko+k)][C*Ki + 1];
+// dW[(o*C+c)][t] = sum_{k,j} dT[(o*Ko+k)][c*Ki+j] Q[t][k][j];  db[o] = sum_k dT[(o*Ko+k)][C*Ki] pm1[k]
+int launch_lsc_unfold(const float *part, int splits, const float *Q, const float *pm1, int C, int O, int T, int Ki,
+                      int Ko, float *dW, float *db, void *stream);
 
 // ----------------------------------------------------------- status text
 // Set the thread's dlm_last_error() text and return s (for library sources

@@ -774,89 +774,6 @@ int lsc_weight_splits(int64_t V, int m, int target) {
 }
 
 // ------------------------------------------------------- folded LSC form
-// B(n = (k,j), t) = Q[t][k][j]: consecutive n are consecutive in memory.
-struct BQt {
-  static constexpr bool kContig = false;
-  static constexpr bool kMask = false;
-  using type = float;
-  const float *Q;
-  int KK;
-  __device__ float operator()(int n, int t, int) const { return Q[(int64_t)t * KK + n]; }
-  __device__ floatx4 load4(int n, int t, int) const { return ld4(Q + (int64_t)t * KK + n); }
-};
-
-struct CFold {
-  float *Tw, *TwT;
-  uint16_t *Twh, *TwTh;
-  int C, Ki, Ko, O;
-  int64_t ld, ldt;
-  __device__ void operator()(int64_t r, int n, int, float v) const {
-    const int o = (int)r / C, c = (int)r - o * C;
-    const int k = n / Ki, j = n - k * Ki;
-    const int64_t row = (int64_t)o * Ko + k, col = (int64_t)c * Ki + j;
-    const int64_t a = row * ld + col, b = col * ldt + row;
-    if (Tw) Tw[a] = v;
-    if (TwT) TwT[b] = v;
-    if (Twh) Twh[a] = to_bf16_bits(v);
-    if (TwTh) TwTh[b] = to_bf16_bits(v);
-  }
-  __device__ void store4(int64_t r, int n, int g, floatx4 v) const {
-    for (int q = 0; q < 4; ++q) (*this)(r, n + q, g, v[q]);
-  }
-};
-
-int launch_lsc_fold(const float *W, const float *Q, int C, int O, int T, int Ki, int Ko, float *Tw, float *TwT,
-                    uint16_t *Twh, uint16_t *TwTh, int64_t ld, int64_t ldt, void *stream) {
-  const int KK = Ko * Ki;
-  return run_gemm<kOpFoldMake>(ARowMajor{W, nullptr, T, 0}, BQt{Q, KK},
-                               CFold{Tw, TwT, Twh, TwTh, C, Ki, Ko, O, ld, ldt}, (int64_t)O * C, KK, T, 1, 0,
-                               DLM_FP32, (hipStream_t)stream, pick_shape(KK));
-}
-
-__global__ void zero_kernel(uint32_t *p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
-
-int launch_zero(void *p, size_t bytes, void *stream) {
-  const int64_t n = (int64_t)(bytes / 4);
-  if (n == 0) return 0;
-  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
-                     static_cast<uint32_t *>(p), n);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-// zero bytes [c0, ld) of each of `rows` rows of ld bytes (c0, ld even)
-__global__ void zero_cols_kernel(uint16_t *p, int64_t rows, int64_t c0, int64_t ld) {
-  const int64_t w = (ld - c0) / 2;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * w) return;
-  const int64_t r = i / w;
-  p[(r * ld + c0) / 2 + (i - r * w)] = 0;
-}
-
-int launch_zero_cols(void *p, int64_t rows, int64_t c0_bytes, int64_t ld_bytes, void *stream) {
-  if (rows <= 0 || ld_bytes <= c0_bytes) return 0;
-  if ((c0_bytes | ld_bytes) & 1) return -3;
-  const int64_t n = rows * ((ld_bytes - c0_bytes) / 2);
-  hipLaunchKernelGGL(zero_cols_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
-                     static_cast<uint16_t *>(p), rows, c0_bytes, ld_bytes);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-__global__ void bias_vec_kernel(const float *bias, const float *pm1, int O, int Ko, float *bvec) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= O * Ko) return;
-  const int o = i / Ko, k = i - o * Ko;
-  bvec[i] = bias ? bias[o] * pm1[k] : 0.0f;
-}
-
-int launch_lsc_bias_vec(const float *bias, const float *pm1, int O, int Ko, float *bvec, void *stream) {
-  hipLaunchKernelGGL(bias_vec_kernel, dim3((O * Ko + 255) / 256), dim3(256), 0, (hipStream_t)stream, bias, pm1, O,
-                     Ko, bvec);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
 // Weight-gradient reduction dT[m][n] = sum_v g[v][m] * act[v][n] over voxel
 // slices (split K).  g = da_out masked by a_out > 0 (m = (o,k)); act = a_in
 // plus a ones column (n = (c,j) or n = CK, giving the bias term).  Both
@@ -958,62 +875,6 @@ int launch_lsc_fold_grad(const float *da_out, const float *mask, const float *a_
                                  (int)V, splits, ks, prec, st, sh);
   return run_gemm<kOpFoldGrad>(AActT{a_in, CK}, BGradT<false>{da_out, nullptr, M}, CPartial2<true>{partial, M, N1}, N1,
                                M, (int)V, splits, ks, prec, st, sh);
-}
-
-__global__ void sum_partials_kernel(const float *part, int splits, int64_t n, float *out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.0f;
-  for (int p = 0; p < splits; ++p) s += part[(int64_t)p * n + i];
-  out[i] = s;
-}
-
-int launch_sum_partials(const float *part, int splits, int64_t n, float *out, void *stream) {
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, part,
-                     splits, n, out);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-// dW[(o*C+c)][t] = sum_{kk,j} dTw[(o*Ko+kk)][c*Ki+j] Q[t][kk][j]: one wave
-// per output (O*C*T of them), lanes striding the Ko*Ki-long reduction in a
-// fixed order, then a butterfly sum.  (A GEMM here has a 96 x 17 output and
-// a 2025-deep reduction: two blocks, all latency.)
-__global__ __launch_bounds__(256) void unfold_kernel(const float *dTw, const float *Q, int C, int T, int Ki, int Ko,
-                                                     int N1, int nout, float *dW) {
-  const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (w >= nout) return;  // whole waves only
-  const int t = w % T, oc = w / T, o = oc / C, c = oc - o * C;
-  const int KK = Ko * Ki;
-  const float *q = Q + (int64_t)t * KK;
-  const float *g = dTw + (int64_t)o * Ko * N1 + (int64_t)c * Ki;
-  float s = 0.0f;
-  for (int e = lane; e < KK; e += 64) {
-    const int kk = e / Ki, j = e - kk * Ki;
-    s += g[(int64_t)kk * N1 + j] * q[e];
-  }
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) dW[(int64_t)oc * T + t] = s;
-}
-
-__global__ void bias_grad_kernel(const float *dTw, const float *pm1, int O, int Ko, int N1, int CK, float *db) {
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= O) return;
-  float s = 0.0f;
-  for (int k = 0; k < Ko; ++k) s += dTw[((int64_t)o * Ko + k) * N1 + CK] * pm1[k];
-  db[o] = s;
-}
-
-int launch_lsc_unfold(const float *dTw, const float *Q, const float *pm1, int C, int O, int T, int Ki, int Ko,
-                      float *dW, float *db, void *stream) {
-  hipStream_t st = (hipStream_t)stream;
-  const int N1 = C * Ki + 1;
-  const int nout = O * C * T;
-  hipLaunchKernelGGL(unfold_kernel, dim3((unsigned)((nout + 3) / 4)), dim3(256), 0, st, dTw, Q, C, T, Ki, Ko, N1, nout,
-                     dW);
-  if (hipGetLastError() != hipSuccess) return -1;
-  if (!db) return 0;
-  hipLaunchKernelGGL(bias_grad_kernel, dim3((O + 63) / 64), dim3(64), 0, st, dTw, pm1, O, Ko, N1, C * Ki, db);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // --------------------------------------------------------- small kernels
