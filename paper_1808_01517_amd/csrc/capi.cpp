@@ -867,6 +867,7 @@ int64_t lsc_chunk(const dlm_lsc_plan *p, int C, int O, int64_t V, size_t ws_byte
 struct FoldWs {
   float *Tw = nullptr, *TwT = nullptr, *bvec = nullptr, *part = nullptr, *dTw = nullptr;
   uint16_t *Twh = nullptr, *TwTh = nullptr;
+  uint16_t *parts = nullptr;
 };
 
 constexpr int kFoldSplitMax = 128;
@@ -888,6 +889,7 @@ FoldWs fold_ws_carve(const dlm_lsc_plan *p, int C, int O, void *ws) {
   const size_t M = size_t(O) * p->K_out, CK = size_t(C) * p->K_in, N1 = CK + 1;
   char *b = static_cast<char *>(ws);
   FoldWs w;
+  w.parts = reinterpret_cast<uint16_t *>(b);
   w.Tw = reinterpret_cast<float *>(b);
   b += align256(M * pad32(CK) * 4);
   w.TwT = reinterpret_cast<float *>(b);
@@ -929,10 +931,11 @@ dlm_status dlm_lsc_workspace_bytes(const dlm_lsc_plan *p, int C, int O, int64_t 
 namespace {
 
 // The folded matrix for one use: T and the folded bias (forward, `transposed`
-// false) or T^T (input gradient), in the precision's storage only (float32 or
-// bfloat16), with its row padding zeroed.
+// false) or T^T (input gradient), in the storage its GEMM reads: bfloat16,
+// three parts (FP32), or float32 for the masked GEMMs of the register-staged
+// core (`masked`), with its row padding zeroed.
 dlm_status fold_weights(const dlm_lsc_plan *p, int C, int O, const float *W, const float *bias, const FoldWs &w,
-                        bool transposed, dlm_precision prec, void *stream) {
+                        bool transposed, bool masked, dlm_precision prec, void *stream) {
   const double KK = double(p->K_out) * p->K_in, M = double(O) * p->K_out, CK = double(C) * p->K_in;
   FoldOut f;
   f.W = W;
@@ -943,15 +946,17 @@ dlm_status fold_weights(const dlm_lsc_plan *p, int C, int O, const float *W, con
   f.Ki = p->K_in;
   f.Ko = p->K_out;
   f.transposed = transposed;
-  f.bf16 = prec == DLM_BF16;
-  f.out = transposed ? (f.bf16 ? (void *)w.TwTh : (void *)w.TwT) : (f.bf16 ? (void *)w.Twh : (void *)w.Tw);
+  f.kind = prec == DLM_BF16 ? kFoldBf16 : masked ? kFoldF32 : kFoldParts;
+  f.out = f.kind == kFoldParts  ? (void *)w.parts
+          : f.kind == kFoldBf16 ? (void *)(transposed ? w.TwTh : w.Twh)
+                                : (void *)(transposed ? w.TwT : w.Tw);
   f.ld = int64_t(pad32(transposed ? size_t(O) * p->K_out : size_t(C) * p->K_in));
   if (!transposed) {
     f.bias = bias;
     f.pm1 = p->dpm1.f32;
     f.bvec = w.bvec;
   }
-  TimedScope ts("lsc_fold", stream, (double(O) * C * p->T + p->T * KK) * 4.0 + M * CK * (f.bf16 ? 2.0 : 4.0),
+  TimedScope ts("lsc_fold", stream, (double(O) * C * p->T + p->T * KK) * 4.0 + M * CK * (f.kind == kFoldBf16 ? 2.0 : f.kind == kFoldParts ? 6.0 : 4.0),
                 2.0 * O * C * KK * p->T);
   return launched(launch_lsc_fold(f, stream));
 }
@@ -962,16 +967,16 @@ dlm_status lsc_fwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
   if (ws_bytes < fold_ws_need(p, C, O))
     return fail(DLM_EWORKSPACE, "workspace of %zu bytes is below the %zu-byte minimum", ws_bytes, fold_ws_need(p, C, O));
   FoldWs w = fold_ws_carve(p, C, O, ws);
-  dlm_status s = fold_weights(p, C, O, W, bias, w, false, prec, stream);
+  dlm_status s = fold_weights(p, C, O, W, bias, w, false, false, prec, stream);
   if (s != DLM_OK) return s;
   const int M = O * p->K_out, CK = C * p->K_in;
   TableGemm t;  // a_out[v][(o,k)] = sum_{(c,j)} Tw[(o,k)][(c,j)] a_in[v][(c,j)] + bias[o] (P_m 1)[k]
   if (io & DLM_IO_IN_BF16) t.Ah = static_cast<const uint16_t *>(a_in);
   else t.A = static_cast<const float *>(a_in);
   t.lda = CK;
-  t.Bf = w.Tw;
   t.Bh = w.Twh;
-  t.ldb_f = t.ldb_h = int64_t(pad32(size_t(CK)));
+  t.B3 = w.parts;
+  t.ldb_h = int64_t(pad32(size_t(CK)));
   if (io & DLM_IO_OUT_BF16) t.Ch = static_cast<uint16_t *>(a_out);
   else t.C = static_cast<float *>(a_out);
   t.ldc = M;
@@ -1002,7 +1007,7 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
   // DLM_RELU_OUT with a bfloat16 a_out is rejected by the caller
   const float *mask = (relu_flags & DLM_RELU_OUT) ? static_cast<const float *>(a_out) : nullptr;
   if (da_in && V > 0) {
-    if ((s = fold_weights(p, C, O, W, nullptr, w, true, prec, stream)) != DLM_OK) return s;
+    if ((s = fold_weights(p, C, O, W, nullptr, w, true, mask != nullptr, prec, stream)) != DLM_OK) return s;
     TableGemm t;  // da_in[v][(c,j)] = sum_{(o,k)} Tw[(o,k)][(c,j)] (da_out * [a_out > 0])[v][(o,k)]
     if (out_h) t.Ah = static_cast<const uint16_t *>(da_out);
     else t.A = static_cast<const float *>(da_out);
@@ -1010,6 +1015,7 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
     t.lda = M;
     t.Bf = w.TwT;
     t.Bh = w.TwTh;
+    t.B3 = w.parts;
     t.ldb_f = t.ldb_h = int64_t(pad32(size_t(M)));
     const bool bits = (relu_flags & DLM_RELU_IN) && relu_bits;  // mask from the forward's ReLU bits
     if (in_h) {
@@ -1041,17 +1047,18 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
       TimedScope ts("lsc_folded_grad", stream,
                     double(V) * (double(M) * (mask ? 2.0 : 1.0) * (out_h ? 2.0 : 4.0) + CK * (in_h ? 2.0 : 4.0)),
                     2.0 * double(V) * M * N1);
-      if (in_h || out_h) {
-        const int ks = fold_grad_split_len(V, splits);
-        s = launched(launch_stream_grad(out_h ? nullptr : static_cast<const float *>(da_out),
-                                        out_h ? static_cast<const uint16_t *>(da_out) : nullptr,
-                                        in_h ? nullptr : static_cast<const float *>(a_in),
-                                        in_h ? static_cast<const uint16_t *>(a_in) : nullptr, V, M, CK, splits, ks,
-                                        w.part, prec, stream));
-      } else {
-        s = launched(launch_lsc_fold_grad(static_cast<const float *>(da_out), mask, static_cast<const float *>(a_in), V,
-                                          M, CK, splits, w.part, prec, stream));
-      }
+      GradGemm x;
+      if (out_h) x.gh = static_cast<const uint16_t *>(da_out);
+      else x.g = static_cast<const float *>(da_out);
+      if (in_h) x.ah = static_cast<const uint16_t *>(a_in);
+      else x.a = static_cast<const float *>(a_in);
+      x.mask = mask;
+      x.V = V;
+      x.M = M;
+      x.CK = CK;
+      x.splits = splits;
+      x.partial = w.part;
+      s = launched(launch_lsc_fold_grad(x, prec, stream));
       if (s != DLM_OK) return s;
     }
     // Few partial matrices are added up as the unfold reads them; many (the

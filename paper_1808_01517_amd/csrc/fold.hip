@@ -21,11 +21,22 @@ namespace fold {
 constexpr int kPairs = 8;  // (o, c) pairs per block of the fold
 constexpr int kTaps = 32;  // taps held in registers at a time
 
-// Store one entry of the folded matrix.
-template <bool BF16>
-__device__ __forceinline__ void put(void *out, int64_t at, float v) {
-  if constexpr (BF16) static_cast<uint16_t *>(out)[at] = to_bf16_bits(v);
-  else static_cast<float *>(out)[at] = v;
+// Store entry (row, col) of the folded matrix.
+template <int KIND>
+__device__ __forceinline__ void put(void *out, int64_t ld, int64_t row, int64_t col, float v) {
+  if constexpr (KIND == kFoldParts) {
+    uint16_t *o = static_cast<uint16_t *>(out) + row * 3 * ld + col;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const __bf16 h = (__bf16)v;  // the part: what is left so far, rounded (RNE)
+      o[i * ld] = __builtin_bit_cast(uint16_t, h);
+      v -= (float)h;
+    }
+  } else if constexpr (KIND == kFoldBf16) {
+    static_cast<uint16_t *>(out)[row * ld + col] = to_bf16_bits(v);
+  } else {
+    static_cast<float *>(out)[row * ld + col] = v;
+  }
 }
 
 // A thread owns one (k, j) entry of Q for all taps, in registers, and runs
@@ -42,7 +53,7 @@ __device__ __forceinline__ void put(void *out, int64_t at, float v) {
 // 9.6 -> 5 us against a matrix-core GEMM with a 17-deep reduction and
 // element-wise scattered stores, which also needed a launch each for the
 // padding and the bias (2-5 us).
-template <bool TR, bool BF16>
+template <bool TR, int KIND>
 __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *Q, int C, int O, int T, int Ki, int Ko,
                                                    void *out, int64_t ld, const float *bias, const float *pm1,
                                                    float *bvec, int nbE) {
@@ -53,7 +64,7 @@ __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *
     const int64_t pad = ld - ncol;
     for (int64_t i = id; i < rows * pad; i += nth) {
       const int64_t r = i / pad;
-      put<BF16>(out, r * ld + ncol + (i - r * pad), 0.0f);
+      put<KIND>(out, ld, r, ncol + (i - r * pad), 0.0f);
     }
     if (bvec)
       for (int64_t i = id; i < (int64_t)O * Ko; i += nth) {
@@ -100,7 +111,7 @@ __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *
 #pragma unroll
   for (int i = 0; i < kPairs; ++i) {
     if (p0 + i >= pairs) break;
-    put<BF16>(out, ((int64_t)x * np + p) * ld + (int64_t)y * nq + q, acc[i]);
+    put<KIND>(out, ld, (int64_t)x * np + p, (int64_t)y * nq + q, acc[i]);
     if (++y == Y) {
       y = 0;
       ++x;
@@ -234,11 +245,13 @@ int launch_lsc_fold(const FoldOut &f, void *stream) {
   hipLaunchKernelGGL((fold::fold_kernel<TR, BF>), grid, dim3(256), 0, st, f.W, f.Q, f.C, f.O, f.T, f.Ki, f.Ko, f.out, \
                      f.ld, f.bias, f.pm1, f.bvec, nbE)
   if (f.transposed) {
-    if (f.bf16) DLM_FOLD(true, true);
-    else DLM_FOLD(true, false);
+    if (f.kind == kFoldBf16) DLM_FOLD(true, kFoldBf16);
+    else if (f.kind == kFoldParts) DLM_FOLD(true, kFoldParts);
+    else DLM_FOLD(true, kFoldF32);
   } else {
-    if (f.bf16) DLM_FOLD(false, true);
-    else DLM_FOLD(false, false);
+    if (f.kind == kFoldBf16) DLM_FOLD(false, kFoldBf16);
+    else if (f.kind == kFoldParts) DLM_FOLD(false, kFoldParts);
+    else DLM_FOLD(false, kFoldF32);
   }
 #undef DLM_FOLD
   return hipGetLastError() == hipSuccess ? 0 : -1;

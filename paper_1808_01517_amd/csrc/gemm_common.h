@@ -96,26 +96,4 @@ struct CRowMajor {
   }
 };
 
-
-template <bool TRANS>
-struct CPartial2 {
-  static constexpr bool kSide = false;
-  float *part;
-  int M, N1;
-  __device__ void operator()(int64_t r, int c, int s, float v) const {
-    if constexpr (TRANS)
-      part[((int64_t)s * M + c) * N1 + r] = v;
-    else
-      part[((int64_t)s * M + r) * N1 + c] = v;
-  }
-  __device__ void store4(int64_t r, int c, int s, floatx4 v) const {
-    if constexpr (TRANS) {
-      for (int q = 0; q < 4; ++q) part[((int64_t)s * M + c + q) * N1 + r] = v[q];
-    } else {
-      __builtin_memcpy(part + ((int64_t)s * M + r) * N1 + c, &v, 16);
-    }
-  }
-};
-
-
 }  // namespace dlm

@@ -67,9 +67,10 @@ struct TableGemm {
   int64_t lda = 0, a_gs = 0;
   const float *Bf = nullptr;
   const uint16_t *Bh = nullptr;
+  const uint16_t *B3 = nullptr;  // three-part float32 table (streaming core in FP32), rows of 3 ldb_h
   int64_t b_gs = 0;
   int64_t ldb_f = 0;  // row stride of the float32 table (0: K)
-  int64_t ldb_h = 0;  // row stride of the bfloat16 table (0: K)
+  int64_t ldb_h = 0;  // row stride of the bfloat16 table or of one part of B3 (0: K)
   float *C = nullptr;
   const float *bias_n = nullptr;
   const float *out_mask = nullptr;  // C zeroed where out_mask (indexed as C) <= 0
@@ -92,18 +93,24 @@ struct TableGemm {
 int launch_table_gemm(const TableGemm &g, dlm_precision prec, void *stream);
 
 // Streaming core (operands DMA'd into an LDS ring).  Table form: one group,
-// no operand mask, the precision's table (float32 Bf / bfloat16 Bh) with row
-// stride ldb_f / ldb_h a multiple of 32 and zeros in columns K .. stride-1.
+// no operand mask, the precision's table (three-part B3 / bfloat16 Bh) with
+// row stride ldb_h a multiple of 32 and zeros in columns K .. stride-1.
 bool stream_table_ok(const TableGemm &g, dlm_precision prec);
 int launch_stream_table(const TableGemm &g, dlm_precision prec, void *stream);
-// Weight-gradient form of launch_lsc_fold_grad (no mask), ksplit a multiple of 32.
-// whether launch_stream_grad takes these sizes (ksplit: voxels per split)
-bool stream_grad_ok(int M, int CK, int ksplit);
-// g / a as float32, or (BF16 only) as bfloat16 gh / ah (M, CK multiples of 8,
-// 16-byte aligned); the other pointer of each pair is null.
-bool stream_grad_bf16_ok(const uint16_t *gh, const uint16_t *ah, int M, int CK);
-int launch_stream_grad(const float *g, const uint16_t *gh, const float *a, const uint16_t *ah, int64_t V, int M,
-                       int CK, int splits, int ksplit, float *partial, dlm_precision prec, void *stream);
+// Weight gradient of the folded form over voxel slices of ksplit voxels:
+// partial[s][m][n] = sum_v g[v][m] a[v][n], with a ones column at n = CK (the
+// bias).  g / a as float32, or (BF16 only) as bfloat16 gh / ah (M, CK
+// multiples of 8, 16-byte aligned); the other pointer of each pair is null.
+// mask (float32 g only, as g): g is replaced by g * (mask > 0).
+struct GradGemm {
+  const float *g = nullptr, *mask = nullptr, *a = nullptr;
+  const uint16_t *gh = nullptr, *ah = nullptr;
+  int64_t V = 0;
+  int M = 0, CK = 0, splits = 1;
+  float *partial = nullptr;
+};
+int launch_lsc_fold_grad(const GradGemm &x, dlm_precision prec, void *stream);
+int fold_grad_splits(int64_t V, int M, int N1);
 // Per-shell SH contraction, one wave per 16 voxels x one shell (groups
 // shells of equal size in one launch):
 //   C[v][g*c_gs + n] = sum_k A[v][g*a_gs + k] * Bt_g[n][k],  n < ncol, k < nred
@@ -200,26 +207,23 @@ int launch_adam(float *w, const float *g, float *m, float *v, int64_t n, float l
 
 // ----------------------------------------------------- folded LSC form
 // The folded matrix of a layer: out[(o*Ko+k)][(c*Ki+j)] = sum_t W[o][c][t]
-// Q[t][k][j], or its transpose out[(c*Ki+j)][(o*Ko+k)], in float32 or
-// bfloat16; rows of stride ld, zeros in their padding.  With bvec, also
+// Q[t][k][j], or its transpose out[(c*Ki+j)][(o*Ko+k)], in float32, bfloat16
+// or as the three bfloat16 parts of its float32 values (part i of a row i * ld
+// entries on, rows 3 ld apart); rows of stride ld, zeros in their padding.  With bvec, also
 // bvec[o*Ko+k] = bias[o] * pm1[k] (zeros when bias is null).  Q is [t][k][j],
 // for the transpose [t][j][k].
+enum FoldKind : int { kFoldF32 = 0, kFoldBf16, kFoldParts };
 struct FoldOut {
   const float *W = nullptr, *Q = nullptr;
   int C = 0, O = 0, T = 0, Ki = 0, Ko = 0;
-  bool transposed = false, bf16 = false;
+  bool transposed = false;
+  FoldKind kind = kFoldF32;
   void *out = nullptr;
   int64_t ld = 0;
   const float *bias = nullptr, *pm1 = nullptr;
   float *bvec = nullptr;
 };
 int launch_lsc_fold(const FoldOut &f, void *stream);
-int fold_grad_split_len(int64_t V, int splits);
-// partial[s][m][n] over voxel slice s: m = (o,k) of g = da_out (masked by
-// a_out > 0 when mask != null), n = (c,j) of a_in plus one ones-column.
-int launch_lsc_fold_grad(const float *da_out, const float *mask, const float *a_in, int64_t V, int M, int CK,
-                         int splits, float *partial, dlm_precision prec, void *stream);
-int fold_grad_splits(int64_t V, int M, int N1);
 // out[i] = sum_s part[s*n + i]
 int launch_sum_partials(const float *part, int splits, int64_t n, float *out, void *stream);
 // dT = sum over the splits of part[s][(o*Ko+k)][C*Ki + 1];

@@ -773,110 +773,6 @@ int lsc_weight_splits(int64_t V, int m, int target) {
   return s < 1 ? 1 : s;
 }
 
-// ------------------------------------------------------- folded LSC form
-// Weight-gradient reduction dT[m][n] = sum_v g[v][m] * act[v][n] over voxel
-// slices (split K).  g = da_out masked by a_out > 0 (m = (o,k)); act = a_in
-// plus a ones column (n = (c,j) or n = CK, giving the bias term).  Both
-// operands are contiguous along their row index, so the voxel index is the
-// strided one.  The larger of M and N1 is put on the GEMM's row side.
-template <bool MASK>
-struct AGradT {
-  static constexpr bool kContig = false;
-  static constexpr bool kMask = MASK;
-  const float *g, *mask;
-  int M;
-  __device__ float operator()(int64_t m, int v, int) const { return g[(int64_t)v * M + m]; }
-  __device__ floatx4 load4(int64_t m, int v, int) const { return ld4(g + (int64_t)v * M + m); }
-  __device__ float maskv(int64_t m, int v, int) const { return mask[(int64_t)v * M + m]; }
-  __device__ floatx4 mask4(int64_t m, int v, int) const { return ld4(mask + (int64_t)v * M + m); }
-};
-
-struct BActT {
-  static constexpr bool kContig = false;
-  static constexpr bool kMask = false;
-  using type = float;
-  const float *a;
-  int CK;
-  __device__ float operator()(int n, int v, int) const { return n < CK ? a[(int64_t)v * CK + n] : 1.0f; }
-  __device__ floatx4 load4(int n, int v, int g) const {
-    if (n + 3 < CK) return ld4(a + (int64_t)v * CK + n);
-    return floatx4{(*this)(n, v, g), (*this)(n + 1, v, g), (*this)(n + 2, v, g), (*this)(n + 3, v, g)};
-  }
-};
-
-// transposed orientation: activations on the row side, gradient on the column side
-struct AActT {
-  static constexpr bool kContig = false;
-  static constexpr bool kMask = false;
-  const float *a;
-  int CK;
-  __device__ float operator()(int64_t n, int v, int) const { return n < CK ? a[(int64_t)v * CK + n] : 1.0f; }
-  __device__ floatx4 load4(int64_t n, int v, int g) const {
-    if (n + 3 < CK) return ld4(a + (int64_t)v * CK + n);
-    return floatx4{(*this)(n, v, g), (*this)(n + 1, v, g), (*this)(n + 2, v, g), (*this)(n + 3, v, g)};
-  }
-};
-
-template <bool MASK>
-struct BGradT {
-  static constexpr bool kContig = false;
-  static constexpr bool kMask = MASK;
-  using type = float;
-  const float *g, *mask;
-  int M;
-  __device__ float operator()(int m, int v, int) const { return g[(int64_t)v * M + m]; }
-  __device__ floatx4 load4(int m, int v, int) const { return ld4(g + (int64_t)v * M + m); }
-  __device__ float maskv(int m, int v, int) const { return mask[(int64_t)v * M + m]; }
-  __device__ floatx4 mask4(int m, int v, int) const { return ld4(mask + (int64_t)v * M + m); }
-};
-
-
-static int split_len(int64_t K, int splits) {
-  const int bk = 32;
-  int ks = (int)((K + splits - 1) / splits);
-  return (ks + bk - 1) / bk * bk;
-}
-
-int fold_grad_split_len(int64_t V, int splits) { return split_len(V, splits); }
-
-static Shape grad_shape(int M, int N1) {
-  // the smaller side (135/136 for the three-shell layers) fits one 144-wide
-  // tile, so the larger operand is read once; otherwise 64 x 64
-  return std::min(M, N1) <= 144 ? Shape::S144 : Shape::S64;
-}
-
-int fold_grad_splits(int64_t V, int M, int N1) {
-  const int big = std::max(M, N1), small = std::min(M, N1);
-  const int64_t tiles = grad_shape(M, N1) == Shape::S144 ? (big + 127) / 128 : ((big + 63) / 64) * ((small + 63) / 64);
-  int s = (int)std::min<int64_t>(128, std::max<int64_t>(1, (2048 + tiles - 1) / tiles));
-  s = (int)std::min<int64_t>(s, std::max<int64_t>(1, V / 512));
-  while (s > 1 && (V + split_len(V, s) - 1) / split_len(V, s) != s) --s;
-  return s;
-}
-
-int launch_lsc_fold_grad(const float *da_out, const float *mask, const float *a_in, int64_t V, int M, int CK,
-                         int splits, float *partial, dlm_precision prec, void *stream) {
-  const int N1 = CK + 1;
-  const int ks = split_len(V, splits);
-  if ((V + ks - 1) / ks != splits) return -2;
-  if (!mask && stream_grad_ok(M, CK, ks))
-    return launch_stream_grad(da_out, nullptr, a_in, nullptr, V, M, CK, splits, ks, partial, prec, stream);
-  hipStream_t st = (hipStream_t)stream;
-  const Shape sh = grad_shape(M, N1);
-  if (M >= N1) {
-    if (mask)
-      return run_gemm<kOpFoldGrad>(AGradT<true>{da_out, mask, M}, BActT{a_in, CK}, CPartial2<false>{partial, M, N1}, M,
-                                   N1, (int)V, splits, ks, prec, st, sh);
-    return run_gemm<kOpFoldGrad>(AGradT<false>{da_out, nullptr, M}, BActT{a_in, CK}, CPartial2<false>{partial, M, N1},
-                                 M, N1, (int)V, splits, ks, prec, st, sh);
-  }
-  if (mask)
-    return run_gemm<kOpFoldGrad>(AActT{a_in, CK}, BGradT<true>{da_out, mask, M}, CPartial2<true>{partial, M, N1}, N1, M,
-                                 (int)V, splits, ks, prec, st, sh);
-  return run_gemm<kOpFoldGrad>(AActT{a_in, CK}, BGradT<false>{da_out, nullptr, M}, CPartial2<true>{partial, M, N1}, N1,
-                               M, (int)V, splits, ks, prec, st, sh);
-}
-
 // --------------------------------------------------------- small kernels
 __global__ void reduce_weight_partials_kernel(const float *part, int splits, float *dW, float *db, int C, int O,
                                               int T, int accumulate) {

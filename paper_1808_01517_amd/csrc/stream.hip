@@ -2,18 +2,20 @@
 // (Sec. 2.3: resampling, cyclic-kernel dot and refit composed into one
 // matrix per layer) and its adjoints.
 //
-// These contractions do 15-60 flop per HBM byte: far below the bf16
-// matrix-core ridge (~300 flop/B), so the BF16 form is bandwidth-bound,
-// and above the fp32 ridge (~20 flop/B), so the FP32 form is bound by the
-// fp32 MFMA rate.  Both want the operand traffic off the register file and
-// out of the way of the matrix cores:
+// These contractions do 15-60 flop per HBM byte, far below the bf16
+// matrix-core ridge (~300 flop/B): BF16 is bandwidth-bound.  FP32 runs them in
+// six bfloat16 part products (parts.h), which puts it near the ridge: 1.0M
+// voxels of the K = 135 forward take 1.2 ms of matrix-core cycles and 1.3 ms
+// of HBM.  Both want the operand traffic off the register file and out of the
+// way of the matrix cores:
 //
 // * Operands travel from global memory straight into LDS with
 //   global_load_lds_dword / _dwordx4 (no register staging), through a ring of
 //   NS stages, so NS-1 slices of 32 k are in flight while one is multiplied.
-// * Float32 operands stay float32 in LDS and are rounded to bfloat16 (RNE)
-//   when a wave reads its MFMA fragment; bfloat16 tables and activations
-//   stored in bfloat16 are copied as is (the same values either way).
+// * Float32 operands stay float32 in LDS and are rounded to bfloat16 (RNE),
+//   or split into parts, when a wave reads its MFMA fragment (each row is read
+//   by one wave); bfloat16 tables, the FP32 tables' parts and activations
+//   stored in bfloat16 are copied as is.
 //   A stage wholly inside the reduction range copies from one wave-uniform
 //   base address plus per-lane 32-bit offsets computed once per block, so
 //   the loop spends a scalar add and one instruction per copy.  In the one
@@ -21,11 +23,7 @@
 //   4 KB zero buffer (spread over lanes, so no single cache line is hot).
 //   LDS thus holds the exact operands and fragment reads need no
 //   conditionals.  Rows beyond the matrix are clamped to valid rows (their
-//   outputs are never stored).  The weight gradient's ones row (its bias
-//   term) is one of them: in FP32 the wave whose tiles hold it sums the
-//   other operand's fragments as they pass, and the epilogue stores those
-//   sums in place of the row's MFMA results; BF16 sets the row's fragments
-//   to ones in registers.
+//   outputs are never stored).
 // * Every LDS layout is swizzled so that fragment reads avoid bank
 //   conflicts while each DMA instruction still fills 64 consecutive slots
 //   (the hardware writes lane i of an instruction to base + i * size).
@@ -36,15 +34,11 @@
 //   DMA, after the second-to-last stage's wait, when they fit in registers;
 //   only the last stage's wait then covers them.
 //
-// MFMA, B fragment first, so each accumulator is the transposed 16 x 16
-// tile (a lane holds four consecutive output columns of one row), the same
-// epilogue as the register-staged cores:
-//   BF16: v_mfma_f32_16x16x32_bf16, lane (q16, g4) holds k = 8 g4 .. 8 g4 + 7;
-//   FP32: v_mfma_f32_16x16x4_f32 over each 16-k group: lane (q16, g4) reads
-//         k = 4 g4 .. 4 g4 + 3 of the group at once and MFMA j takes k = 4 g4
-//         + j (a permutation of the reduction index, the same for A and B).
-// The ring is three stages deep in BF16 (latency-bound) and two in FP32
-// (one stage of fp32 MFMA work outlasts a load).
+// MFMA v_mfma_f32_16x16x32_bf16, B fragment first, so each accumulator is the
+// transposed 16 x 16 tile (a lane holds four consecutive output columns of one
+// row), the same epilogue as the register-staged cores; lane (q16, g4) holds
+// k = 8 g4 .. 8 g4 + 7.  The ring is three stages deep in BF16 (latency-bound)
+// and two in FP32 (one stage of part products outlasts a load).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,6 +46,7 @@
 
 #include "gemm_common.h"
 #include "internal.h"
+#include "parts.h"
 
 namespace dlm {
 namespace streaming {
@@ -154,120 +149,14 @@ struct SKc {
     const floatx4 hi = *reinterpret_cast<const floatx4 *>(row + (((2 * g4 + 1) ^ (r & 7)) << 2));
     return to_bf16x8(lo, hi);
   }
-  // float32 values k = 16 h + 4 g4 .. + 3 of the stage for row rg*16 + q16
   template <int BR>
-  __device__ floatx4 frag4(const char *lds, int rg, int q16, int g4, int h) const {
+  __device__ void frag3(const char *lds, int rg, int q16, int g4, bf16x8 (&v)[3]) const {
     const int r = rg * 16 + q16;
     const float *row = reinterpret_cast<const float *>(lds) + r * SBK;
-    return *reinterpret_cast<const floatx4 *>(row + (((4 * h + g4) ^ (r & 7)) << 2));
+    split3(*reinterpret_cast<const floatx4 *>(row + (((2 * g4) ^ (r & 7)) << 2)),
+           *reinterpret_cast<const floatx4 *>(row + (((2 * g4 + 1) ^ (r & 7)) << 2)), v);
   }
-};
-
-// Row-contiguous float32: element (r, k) at p[k * ld + r], valid for
-// r < rows, k < kend; with ONES, row `ones` (if >= 0) stands for a row of
-// ones (bind() locates it in the block's tile).  VEC needs 16-byte aligned k-lines and rows % 4 == 0.
-// LDS: a stage (32 k x BR rows) in windows of 16 rows of one k (64 bytes).
-// With k = 16 h + 4 q + j (h = bit 4, q = bits 2-3, j = bits 0-1) and
-// NG = BR / 16 row groups, window (k, rg) sits at window index
-// 4 ((4 h + j) NG + rg) + c(k), c(k) = (bit2 ^ bit3) + 2 (bit3 ^ bit4).
-// The four k of one fragment read (FP32: 16 h + 4 g4 + j over g4; BF16:
-// 8 g4 + e over g4) have four different c, so a 32-bit read covers 64
-// banks once; and the two k of each half-wave (g4 = 0, 1 and 2, 3) have c
-// of different parity, so each half-wave also covers 32 banks once.  (A
-// 32-bit LDS read behaves as 32 banks per half-wave here: with c = 2 bit3
-// + (bit2 ^ bit4), conflict-free over 64 banks, the BF16 reads measured
-// 2.3e8 conflict cycles per weight gradient.)  A DMA instruction fills
-// whole windows: 4 k x 16 rows (4-byte lanes) or 4 k x 64 rows (16-byte
-// lanes).
-template <bool VEC, bool ONES>
-struct SRc {
-  const float *p;
-  int64_t ld, rows, ones;
-  int orel = -1;  // row `ones` relative to the bound tile, -1 if outside
-  static constexpr int kUnit = VEC ? 16 : 4;
-  static constexpr bool kOnes = ONES;  // the operand may hold the ones row
-  template <int BR>
-  static constexpr int bytes() { return BR * SBK * 4; }
-  template <int BR>
-  static constexpr int slots() { return bytes<BR>() / kUnit; }
-  // rows beyond the matrix (the ones row among them) copy the last row, or
-  // for 16-byte lanes the last chunk
-  static constexpr int kLast = VEC ? 4 : 1;
-  __device__ int64_t clamp(int64_t gr) const { return gr < rows ? gr : rows - kLast; }
-  // A tile may start at or past the last row (the ones row is row `rows`),
-  // so full-stage addresses are taken relative to the clamped tile start,
-  // never above any clamped row: offsets stay non-negative.
-  __device__ int64_t rbase(int64_t r0) const { return r0 < rows - kLast ? r0 : rows - kLast; }
-  __device__ const char *base(int64_t r0, int k0) const {
-    return reinterpret_cast<const char *>(p + (int64_t)k0 * ld + rbase(r0));
-  }
-  // (k, first row) within the stage and tile of slot s
-  template <int BR>
-  __device__ static void slot_kr(int s, int &k, int &r) {
-    static_assert(BR % 16 == 0, "row tile");
-    constexpr int NG = BR / 16;
-    const int w = VEC ? s >> 2 : s >> 4;
-    const int t = VEC ? (s & 3) << 2 : s & 15;
-    const int idx = w >> 2, c = w & 3;
-    const int hj = idx / NG, rg = idx - hj * NG;
-    const int h = hj >> 2, j = hj & 3;
-    const int b3 = (c >> 1) ^ h, b2 = (c & 1) ^ b3;  // c = (b2 ^ b3) + 2 (b3 ^ h)
-    k = 16 * h + 8 * b3 + 4 * b2 + j;
-    r = 16 * rg + t;
-  }
-  template <int BR>
-  __device__ uint32_t lane_off(int s, int64_t r0) const {
-    int k, r;
-    slot_kr<BR>(s, k, r);
-    return (uint32_t)(((int64_t)k * ld + (clamp(r0 + r) - rbase(r0))) * 4);
-  }
-  template <int BR>
-  __device__ static int k_of(int s) {
-    int k, r;
-    slot_kr<BR>(s, k, r);
-    return k;
-  }
-  __device__ void bind(int64_t r0) {
-    const int64_t ro = ones - r0;
-    orel = ones >= 0 && ro >= 0 && ro < 1 << 20 ? (int)ro : -1;
-  }
-  // Element (k = 16 h + 4 q + j, row 16 rg + q16) sits at float
-  // 64 ((4 h + j) NG + rg) + 16 c(k) + q16: a per-lane part (h, c, q16), a
-  // wave-uniform part (rg) and a constant (j), added in that order so that
-  // the constant stays an instruction offset.
-  // BF16 fragments of the ones row are set to ones here (FP32 sums instead)
-  __device__ bool ones_lane(int rg, int q16) const { return ONES && orel >= 0 && orel == 16 * rg + q16; }
-  template <int BR>
-  __device__ bf16x8 frag(const char *lds, int rg, int q16, int g4) const {
-    constexpr int NG = BR / 16;
-    const float *t = reinterpret_cast<const float *>(lds) + 64 * rg;
-    // k = 8 g4 + e: h = g4 >> 1, bit 3 = g4 & 1, bit 2 = 0 (lo) or 1 (hi)
-    const int h = g4 >> 1, b3 = g4 & 1, c2 = 2 * (b3 ^ h);
-    const float *lo_p = t + (256 * NG * h + 16 * (b3 + c2) + q16);
-    const float *hi_p = t + (256 * NG * h + 16 * ((1 ^ b3) + c2) + q16);
-    floatx4 lo, hi;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      lo[e] = lo_p[64 * NG * e];
-      hi[e] = hi_p[64 * NG * e];
-    }
-    bf16x8 v = to_bf16x8(lo, hi);
-    if (ones_lane(rg, q16))
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (__bf16)1.0f;
-    return v;
-  }
-  template <int BR>
-  __device__ floatx4 frag4(const char *lds, int rg, int q16, int g4, int h) const {
-    constexpr int NG = BR / 16;
-    // k = 16 h + 4 g4 + j: bit 2 = g4 & 1, bit 3 = g4 >> 1
-    const int c = ((g4 & 1) ^ (g4 >> 1)) + 2 * ((g4 >> 1) ^ h);
-    const float *p0 = reinterpret_cast<const float *>(lds) + 64 * rg + (256 * NG * h + 16 * c + q16);
-    floatx4 v;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = p0[64 * NG * j];
-    return v;
-  }
+  __device__ float at(int64_t r, int k) const { return p[(r < rows ? r : rows - 1) * ld + k]; }
 };
 
 // bfloat16 table: element (r, k) at p[r * ldp + k], ldp a multiple of 32,
@@ -302,6 +191,44 @@ struct SKh {
   }
 };
 
+// The three-part float32 table: part i of element (r, k) at p[r * 3 ldp + i ldp
+// + k], each part as an SKh table.  LDS: the parts' tiles one after another.
+struct SK3 {
+  const uint16_t *p;
+  int64_t ldp, rows;
+  static constexpr int kUnit = 16;
+  static constexpr bool kOnes = false;
+  template <int BR>
+  static constexpr int bytes() { return 3 * BR * SBK * 2; }
+  template <int BR>
+  static constexpr int slots() { return bytes<BR>() / kUnit; }
+  __device__ const char *base(int64_t r0, int k0) const {
+    return reinterpret_cast<const char *>(p + r0 * 3 * ldp + k0);
+  }
+  template <int BR>
+  __device__ uint32_t lane_off(int s, int64_t r0) const {
+    const int part = s / (BR * 4), q = s - part * (BR * 4);
+    const int r = q >> 2, c = (q & 3) ^ ((r >> 1) & 3);
+    const int64_t gr = r0 + r < rows ? r0 + r : rows - 1;
+    return (uint32_t)(((gr - r0) * 3 * ldp + part * ldp + 8 * c) * 2);
+  }
+  template <int BR>
+  __device__ static int k_of(int) { return 0; }
+  __device__ void bind(int64_t) {}
+  template <int BR>
+  __device__ void frag3(const char *lds, int rg, int q16, int g4, bf16x8 (&v)[3]) const {
+    const int r = rg * 16 + q16;
+    const char *t = lds + r * 64 + ((g4 ^ ((r >> 1) & 3)) << 4);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) v[i] = *reinterpret_cast<const bf16x8 *>(t + i * BR * SBK * 2);
+  }
+  __device__ float at(int64_t r, int k) const {
+    const uint16_t *q = p + (r < rows ? r : rows - 1) * 3 * ldp + k;
+    auto f = [](uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); };
+    return (f(q[0]) + f(q[ldp])) + f(q[2 * ldp]);
+  }
+};
+
 // bfloat16 k-contiguous rows (activations stored in bfloat16): element
 // (r, k) at p[r * ldp + k], valid for r < rows, k < kend; ldp a multiple of 8
 // with 16-byte aligned rows and kend a multiple of 8, so a 16-byte chunk
@@ -314,135 +241,36 @@ struct SKb : SKh {
   }
 };
 
-// bfloat16 row-contiguous (activations stored in bfloat16, reduced over
-// voxels): element (r, k) at p[k * ld + r], valid for r < rows, k < kend;
-// with ONES, row `ones` (if >= 0) stands for a row of ones, as in SRc.  A 16-byte
-// lane copies 8 consecutive rows of one k, so ld and rows are multiples of 8
-// and k-lines are 16-byte aligned.  LDS: [32][BR] bf16; the 8-row chunk c of
-// k-line k sits at chunk (c + 2 g(k)) mod (BR / 8), g(k) = (k >> 3) & 3, so
-// the four k of one fragment read (8 g4 + e, g4 = 0..3) land 32 bytes apart.
-template <bool ONES>
-struct SRb {
-  const uint16_t *p;
-  int64_t ld, rows, ones;
-  int orel = -1;
-  static constexpr int kUnit = 16;
-  static constexpr bool kOnes = ONES;
-  template <int BR>
-  static constexpr int bytes() { return BR * SBK * 2; }
-  template <int BR>
-  static constexpr int slots() { return bytes<BR>() / kUnit; }
-  __device__ static int rot(int k) { return 2 * ((k >> 3) & 3); }
-  // rows beyond the matrix copy its last 8-row chunk (never stored)
-  __device__ int64_t clamp(int64_t gr) const { return gr < rows ? gr : rows - 8; }
-  __device__ int64_t rbase(int64_t r0) const { return r0 < rows - 8 ? r0 : rows - 8; }
-  __device__ const char *base(int64_t r0, int k0) const {
-    return reinterpret_cast<const char *>(p + (int64_t)k0 * ld + rbase(r0));
-  }
-  template <int BR>
-  __device__ uint32_t lane_off(int s, int64_t r0) const {
-    static_assert(BR % 16 == 0 && BR / 8 > 6, "row tile");
-    constexpr int NC = BR / 8;
-    const int k = s / NC;
-    int c = s - k * NC - rot(k);
-    if (c < 0) c += NC;
-    return (uint32_t)(((int64_t)k * ld + (clamp(r0 + 8 * c) - rbase(r0))) * 2);
-  }
-  template <int BR>
-  __device__ static int k_of(int s) { return s / (BR / 8); }
-  __device__ void bind(int64_t r0) {
-    const int64_t ro = ones - r0;
-    orel = ones >= 0 && ro >= 0 && ro < 1 << 20 ? (int)ro : -1;
-  }
-  // Lane (q16, g4) needs row r at k = 8 g4 .. + 7, eight k-lines apart.  It
-  // reads the whole dword holding rows r & ~1 and r | 1 of each k-line (the
-  // lanes of rows 2i and 2i + 1 read the same dword: a broadcast) and keeps
-  // its half with one byte permute per pair of k-lines, in place of sixteen
-  // 16-bit reads into register halves (measured: 4% faster weight gradient).
-  template <int BR>
-  __device__ bf16x8 frag(const char *lds, int rg, int q16, int g4) const {
-    constexpr int NC = BR / 8;
-    const uint32_t *t = reinterpret_cast<const uint32_t *>(lds);
-    const int r = rg * 16 + q16, c = r >> 3, w = r & 7;
-    int pc = c + 2 * g4;  // rot(8 g4 + e) = 2 g4 for every e
-    if (pc >= NC) pc -= NC;
-    const uint32_t *p = t + ((8 * g4) * BR + pc * 8 + (w & ~1)) / 2;
-    // bytes of the lane's half from two dwords (lo halves, or hi halves)
-    const uint32_t sel = (w & 1) ? 0x07060302u : 0x05040100u;
-    uint32_t d[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) d[e] = p[e * (BR / 2)];
-    uint32_t u[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) u[i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], sel);
-    bf16x8 v = __builtin_bit_cast(bf16x8, u);
-    if (ONES && orel >= 0 && orel == r)  // the ones row (a BF16 fragment: set here)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (__bf16)1.0f;
-    return v;
-  }
-};
-
 // ------------------------------------------------------------------ core
 template <int BM_, int BN_, int WM_, int WN_, int NS_>
 struct SCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_;
   static constexpr int TM = BM / (WM * 16), TN = BN / (WN * 16);
-  static_assert(WM * WN == 4, "four waves per block");
+  static constexpr int NW = WM * WN;  // waves per block
+  static_assert(NW == 4 || NW == 8, "waves per block");
   static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "tile shape");
   static_assert(NS >= 2 && NS <= 4, "ring depth");
 };
 
-// Sums standing in for the weight gradient's ones row in FP32.  The MFMAs
-// read that row's slots as copied (a clamped row), so the wave whose tiles
-// hold the row adds up the other operand's fragments instead: rs[i] the
-// k-sums of its A rows (ones row in B: an output column), cs[j] those of
-// its B rows (ones row in A: an output row), per lane over the lane's k;
-// the epilogue finishes the sums across lanes and stores them in place of
-// the row's MFMA results.  Flags are wave-uniform.  (Setting the row's
-// fragments to ones instead costs a select per fragment value: 44 per 72
-// MFMAs in the 128 x 144 tile.  BF16, bound by memory rather than by the
-// matrix cores, keeps those selects, which measured faster there than the
-// sums.)
-template <class CF>
-struct OnesSum {
-  bool a_on = false, b_on = false;  // ones row in this wave's A / B tiles
-  int rel = 0;                      // its row, relative to the wave's first row on that side
-  float rs[CF::TM], cs[CF::TN];
-};
-
-__device__ __forceinline__ float sum4(floatx4 v) { return (v[0] + v[1]) + (v[2] + v[3]); }
-
-// One stage (32 k) of MFMAs for a wave's TM x TN tiles.  FP32 runs the
-// stage's nh (1 or 2) groups of 16 k through one MFMA sequence (a last stage
-// ending within its first group needs one); BF16 ignores nh.
+// One stage (32 k) of MFMAs for a wave's TM x TN tiles.  FP32 works in part
+// products (parts.h), the B tiles two at a time, so that consecutive
+// instructions go to 2 TM accumulators and the B parts stay within 24
+// registers.
 template <class CF, bool F32, class AO, class BO>
 __device__ __forceinline__ void mma_stage(const AO &ao, const BO &bo, const char *sa, const char *sb, int wm, int wn,
-                                          int q16, int g4, int nh, floatx4 (&acc)[CF::TM][CF::TN],
-                                          OnesSum<CF> &os) {
+                                          int q16, int g4, floatx4 (&acc)[CF::TM][CF::TN],
+                                          floatx4 (&low)[F32 ? CF::TM : 1][CF::TN]) {
   constexpr int BM = CF::BM, BN = CF::BN;
   if constexpr (F32) {
-#pragma unroll 1
-    for (int h = 0; h < nh; ++h) {
-      floatx4 a[CF::TM], b[CF::TN];
+    bf16x8 a[CF::TM][3];
 #pragma unroll
-      for (int i = 0; i < CF::TM; ++i) a[i] = ao.template frag4<BM>(sa, wm * CF::TM + i, q16, g4, h);
+    for (int i = 0; i < CF::TM; ++i) ao.template frag3<BM>(sa, wm * CF::TM + i, q16, g4, a[i]);
 #pragma unroll
-      for (int j = 0; j < CF::TN; ++j) b[j] = bo.template frag4<BN>(sb, wn * CF::TN + j, q16, g4, h);
-      if constexpr (BO::kOnes)  // every wave of a tile with the ones column: no branch
-#pragma unroll
-        for (int i = 0; i < CF::TM; ++i) os.rs[i] += sum4(a[i]);
-      if constexpr (AO::kOnes)
-        if (os.a_on)
-#pragma unroll
-          for (int j = 0; j < CF::TN; ++j) os.cs[j] += sum4(b[j]);
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-        for (int i = 0; i < CF::TM; ++i)
-#pragma unroll
-          for (int j = 0; j < CF::TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][jj], a[i][jj], acc[i][j], 0, 0, 0);
+    for (int j = 0; j < CF::TN; j += 2) {
+      bf16x8 b[2][3];
+      bo.template frag3<BN>(sb, wn * CF::TN + j, q16, g4, b[0]);
+      if (j + 1 < CF::TN) bo.template frag3<BN>(sb, wn * CF::TN + j + 1, q16, g4, b[1]);
+      mma_parts(a, b, acc, low, j);
     }
   } else {
     bf16x8 a[CF::TM], b[CF::TN];
@@ -455,64 +283,6 @@ __device__ __forceinline__ void mma_stage(const AO &ao, const BO &bo, const char
 #pragma unroll
       for (int j = 0; j < CF::TN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-  }
-}
-
-// Start the ones-row sums of a wave: locate the row in its A or B tiles.
-template <class CF, class AO, class BO>
-__device__ __forceinline__ void ones_begin(const AO &aw, const BO &bw, int wm, int wn, OnesSum<CF> &os) {
-  static_assert(!(AO::kOnes && BO::kOnes), "one operand with a ones row");
-  if constexpr (AO::kOnes) {
-    os.rel = aw.orel - wm * CF::TM * 16;
-    os.a_on = aw.orel >= 0 && os.rel >= 0 && os.rel < CF::TM * 16;
-  }
-  if constexpr (BO::kOnes) {
-    os.rel = bw.orel - wn * CF::TN * 16;
-    os.b_on = bw.orel >= 0 && os.rel >= 0 && os.rel < CF::TN * 16;
-  }
-#pragma unroll
-  for (int i = 0; i < CF::TM; ++i) os.rs[i] = 0.f;
-#pragma unroll
-  for (int j = 0; j < CF::TN; ++j) os.cs[j] = 0.f;
-}
-
-// Finish the sums across the four lanes of a row (lanes q16 + 16 g4 hold
-// disjoint k) and store them in place of the ones row's MFMA results: a
-// ones row in B is output column `rel` (lane (q16, g4) holds columns
-// 4 g4 .. 4 g4 + 3 of each 16-column tile), a ones row in A is output row
-// `rel`, whose column n of tile j is the sum lane q16 = n holds.
-template <class CF>
-__device__ __forceinline__ void ones_end(OnesSum<CF> &os, floatx4 (&acc)[CF::TM][CF::TN], int q16, int g4) {
-  if (os.b_on) {
-    const int jo = os.rel >> 4, go = (os.rel & 15) >> 2, eo = os.rel & 3;
-#pragma unroll
-    for (int i = 0; i < CF::TM; ++i) {
-      float r = os.rs[i];
-      r += __shfl_xor(r, 16);
-      r += __shfl_xor(r, 32);
-#pragma unroll
-      for (int j = 0; j < CF::TN; ++j)
-        if (j == jo && g4 == go)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (e == eo) acc[i][j][e] = r;
-    }
-  }
-  if (os.a_on) {
-    const int io = os.rel >> 4, qo = os.rel & 15;
-#pragma unroll
-    for (int j = 0; j < CF::TN; ++j) {
-      float c = os.cs[j];
-      c += __shfl_xor(c, 16);
-      c += __shfl_xor(c, 32);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float v = __shfl(c, 4 * g4 + e);
-#pragma unroll
-        for (int i = 0; i < CF::TM; ++i)
-          if (i == io && q16 == qo) acc[i][j][e] = v;
-      }
-    }
   }
 }
 
@@ -713,15 +483,15 @@ __device__ __forceinline__ void dma_stage_full(const char *base, const uint32_t 
 // their share of every stage's DMA and compute.  Several blocks per CU keep
 // loads in flight while another block multiplies or stores.
 template <int OP, class CF, bool F32, class AO, class BO, class CS>
-__global__ __launch_bounds__(256) void gemm_stream_kernel(AO ao, BO bo, CS cs, int64_t M, int N, int K, int ksplit,
-                                                          int nbM, int nbN, int nz) {
-  constexpr int BM = CF::BM, BN = CF::BN;
+__global__ __launch_bounds__(64 * CF::NW) void gemm_stream_kernel(AO ao, BO bo, CS cs, int64_t M, int N, int K,
+                                                                  int ksplit, int nbM, int nbN, int nz) {
+  constexpr int BM = CF::BM, BN = CF::BN, NW = CF::NW;
   constexpr int AB = AO::template bytes<BM>(), BB = BO::template bytes<BN>(), SB = AB + BB;
   constexpr int NIA = (AO::template slots<BM>() + 63) / 64, NIB = (BO::template slots<BN>() + 63) / 64;
   // DMA instructions every wave issues per stage, at least (wave w issues
-  // instructions w, w + 4, ...); waits use this count, so a wave with more
+  // instructions w, w + NW, ...); waits use this count, so a wave with more
   // waits for slightly more than it needs.
-  constexpr int NIW = NIA / 4 + NIB / 4;
+  constexpr int NIW = NIA / NW + NIB / NW;
   // ring depth: two stages in FP32; in BF16 as configured while the pending
   // count fits vmcnt (6 bits)
   constexpr int NS = F32 ? 2 : ((CF::NS - 2) * NIW < 64 ? CF::NS : 2), D = NS - 1;
@@ -746,29 +516,30 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(AO ao, BO bo, CS cs, i
   BO bw = bo;
   aw.bind(m0);
   bw.bind(n0);
-  OnesSum<CF> os;
-  if constexpr (F32 && (AO::kOnes || BO::kOnes)) ones_begin<CF>(aw, bw, wm, wn, os);
-  constexpr int NWA = dma_per_wave<BM, AO>(4), NWB = dma_per_wave<BN, BO>(4);
+  constexpr int NWA = dma_per_wave<BM, AO>(NW), NWB = dma_per_wave<BN, BO>(NW);
   uint32_t offa[NWA], offb[NWB];
-  dma_offsets<BM>(ao, offa, wave, 4, lane, m0);
-  dma_offsets<BN>(bo, offb, wave, 4, lane, n0);
+  dma_offsets<BM>(ao, offa, wave, NW, lane, m0);
+  dma_offsets<BN>(bo, offb, wave, NW, lane, n0);
   auto issue = [&](int it) {
     char *sa = lds + (it % NS) * SB;
     const int k0 = kbeg + it * SBK;
     if (k0 + SBK <= kend) {
-      dma_stage_full<BM, AO, 4>(ao.base(m0, k0), offa, sa, wave, lane);
-      dma_stage_full<BN, BO, 4>(bo.base(n0, k0), offb, sa + AB, wave, lane);
+      dma_stage_full<BM, AO, NW>(ao.base(m0, k0), offa, sa, wave, lane);
+      dma_stage_full<BN, BO, NW>(bo.base(n0, k0), offb, sa + AB, wave, lane);
     } else {  // the range ends inside this stage: zeros beyond it
-      dma_stage_tail<BM, AO, 4>(ao.base(m0, k0), offa, sa, wave, lane, kend - k0);
-      dma_stage_tail<BN, BO, 4>(bo.base(n0, k0), offb, sa + AB, wave, lane, kend - k0);
+      dma_stage_tail<BM, AO, NW>(ao.base(m0, k0), offa, sa, wave, lane, kend - k0);
+      dma_stage_tail<BN, BO, NW>(bo.base(n0, k0), offb, sa + AB, wave, lane, kend - k0);
     }
   };
 
-  floatx4 acc[CF::TM][CF::TN];
+  floatx4 acc[CF::TM][CF::TN], low[F32 ? CF::TM : 1][CF::TN];
 #pragma unroll
   for (int i = 0; i < CF::TM; ++i)
 #pragma unroll
-    for (int j = 0; j < CF::TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < CF::TN; ++j) {
+      acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (F32) low[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
 
 #pragma unroll
   for (int s = 0; s < D; ++s)
@@ -798,10 +569,13 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(AO ao, BO bo, CS cs, i
     if constexpr (SidePre<CF, CS>::kOn)
       if (it == side_it) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4, z);
     const char *sa = lds + (it % NS) * SB;
-    const int nh = kend - (kbeg + it * SBK) > 16 ? 2 : 1;
-    mma_stage<CF, F32>(aw, bw, sa, sa + AB, wm, wn, q16, g4, nh, acc, os);
+    mma_stage<CF, F32>(aw, bw, sa, sa + AB, wm, wn, q16, g4, acc, low);
   }
-  if constexpr (F32 && (AO::kOnes || BO::kOnes)) ones_end<CF>(os, acc, q16, g4);
+  if constexpr (F32) {
+    add_parts(acc, low);
+    if (const uint64_t bad = bad_tiles(acc))
+      redo_tiles<false>(ao, bo, m0 + wm * CF::TM * 16, (int64_t)n0 + wn * CF::TN * 16, kbeg, kend, bad, acc);
+  }
   if constexpr (SidePre<CF, CS>::kOn)
     if (niter == 0) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4, z);
   store_tiles<CF>(cs, acc, M, N, m0, n0, wm, wn, q16, g4, z, sp);
@@ -813,8 +587,8 @@ int run_stream(AO ao, BO bo, CS cs, int64_t M, int N, int K, int Z, int ksplit, 
   const int64_t nbM = (M + CF::BM - 1) / CF::BM;
   const int nbN = (N + CF::BN - 1) / CF::BN;
   if (nbM * nbN * Z > 0x7fffffff) return -4;
-  hipLaunchKernelGGL((gemm_stream_kernel<OP, CF, F32, AO, BO, CS>), dim3((unsigned)(nbM * nbN * Z)), dim3(256), 0, st,
-                     ao, bo, cs, M, N, K, ksplit, (int)nbM, nbN, Z);
+  hipLaunchKernelGGL((gemm_stream_kernel<OP, CF, F32, AO, BO, CS>), dim3((unsigned)(nbM * nbN * Z)),
+                     dim3(64 * CF::NW), 0, st, ao, bo, cs, M, N, K, ksplit, (int)nbM, nbN, Z);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -1046,9 +820,6 @@ namespace astat {
 #ifndef DLM_ASTAT_BN_F32
 #define DLM_ASTAT_BN_F32 32
 #endif
-#ifndef DLM_ASTAT_NACC
-#define DLM_ASTAT_NACC 1
-#endif
 #ifndef DLM_ASTAT_D_BF16
 #define DLM_ASTAT_D_BF16 3
 #endif
@@ -1057,19 +828,24 @@ namespace astat {
 #endif
 
 constexpr int TM = DLM_ASTAT_TM;  // 16-row groups per wave
-constexpr int BM = 64 * TM;       // rows per block: four waves
+// Waves per block: the FP32 form's three-part tiles leave LDS for one block
+// per CU, so it has eight waves in it; BF16 has two or three blocks of four.
+template <bool F32>
+constexpr int NW = F32 ? 8 : 4;
+template <bool F32>
+constexpr int BM = 16 * TM * NW<F32>;  // rows per block
 constexpr int KS = 5;             // 32-k slices (128 < K <= 160)
 constexpr int kMaxN = 1440;       // columns whose side data fit in LDS
 
-// BF16: lane (q16, g4) holds A[row][32 s + 8 g4 .. + 7] rounded to bfloat16;
-// FP32: A[row][16 g + 4 g4 .. + 3], g < 2 KS (row = 16 i + q16 of the wave).
+// Lane (q16, g4) holds A[row][32 s + 8 g4 .. + 7] (row = 16 i + q16 of the
+// wave) rounded to bfloat16, in FP32 its three parts.
 template <bool F32>
 struct AFrag {
-  bf16x8 v[TM][KS];
+  bf16x8 v[KS][TM];
 };
 template <>
 struct AFrag<true> {
-  floatx4 v[TM][2 * KS];
+  bf16x8 v[KS][TM][3];
 };
 
 // NV consecutive values of a row from k0 on, zeros at and beyond K.
@@ -1096,20 +872,15 @@ __device__ __forceinline__ void load_a(const float *A, int64_t lda, int64_t M, i
     int64_t r = r0 + i * 16 + q16;
     if (r >= M) r = M - 1;  // rows beyond M read a valid row and are never stored
     const float *row = A + r * lda;
-    if constexpr (F32) {
 #pragma unroll
-      for (int g = 0; g < 2 * KS; ++g) {
-        float t[4];
-        load_run<4>(row, 16 * g + 4 * g4, K, t);
-        a.v[i][g] = floatx4{t[0], t[1], t[2], t[3]};
-      }
-    } else {
+    for (int s = 0; s < KS; ++s) {
+      float t[8];
+      load_run<8>(row, 32 * s + 8 * g4, K, t);
+      if constexpr (F32) {
+        split3(floatx4{t[0], t[1], t[2], t[3]}, floatx4{t[4], t[5], t[6], t[7]}, a.v[s][i]);
+      } else {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        float t[8];
-        load_run<8>(row, 32 * s + 8 * g4, K, t);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a.v[i][s][e] = (__bf16)t[e];
+        for (int e = 0; e < 8; ++e) a.v[s][i][e] = (__bf16)t[e];
       }
     }
   }
@@ -1119,9 +890,9 @@ template <class CS>
 constexpr int bias_bytes() {
   return CS::kBias ? kMaxN * 4 : 0;
 }
-template <class CS>
+template <class CS, int ROWS>
 constexpr int side_bytes() {
-  constexpr int b = bias_bytes<CS>() + ((CS::kMask || CS::kBits == 1) ? BM * (kMaxN / 16) * 2 : 0);
+  constexpr int b = bias_bytes<CS>() + ((CS::kMask || CS::kBits == 1) ? ROWS * (kMaxN / 16) * 2 : 0);
   return b > 0 ? b : 16;
 }
 
@@ -1168,10 +939,10 @@ __device__ __forceinline__ void store_pair_bf16(uint16_t *C, int64_t ldc, int64_
   __builtin_memcpy(C + r * ldc + col, out, 16);
 }
 
-template <bool F32, int BN, int D, int NACC, bool RELU, class BO, class CS>
-__global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda, int64_t M, int K, BO bo, CS cs,
-                                                    int N) {
-  constexpr int TN = BN / 16, NS = D + 1;
+template <bool F32, int BN, int D, bool RELU, class BO, class CS>
+__global__ __launch_bounds__(64 * NW<F32>) void astat_kernel(const float *A, int64_t lda, int64_t M, int K, BO bo,
+                                                             CS cs, int N) {
+  constexpr int TN = BN / 16, NS = D + 1, NWV = astat::NW<F32>, NT_ = 64 * NWV, BM = astat::BM<F32>;
   constexpr bool kHalf = CS::kHalf, kMaskIn = CS::kMask, kBitsOut = CS::kBits == 1;
   static_assert(!CS::kMask || CS::kBits == 2, "masks from ReLU bits only");
   constexpr int SLAB = BO::template bytes<BN>();  // one 32-k slice of a column tile
@@ -1179,15 +950,15 @@ __global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda,
   constexpr int NSL = BO::template slots<BN>();
   static_assert(BO::kUnit == 16 && NSL % 64 == 0, "whole 16-byte DMA instructions per slice");
   constexpr int NI = NSL / 64;        // DMA instructions per slice
-  constexpr int NIT = KS * NI;        // per tile, dealt round-robin to the four waves
-  constexpr int KW = (NIT + 3) / 4;   // per wave per tile, at most
-  constexpr int IW = NIT / 4;         // and at least
-  constexpr int KB = BO::template bytes<1>() / SBK;  // bytes per table entry
+  constexpr int NIT = KS * NI;        // per tile, dealt round-robin to the waves
+  constexpr int KW = (NIT + NWV - 1) / NWV;  // per wave per tile, at most
+  constexpr int IW = NIT / NWV;              // and at least
+  constexpr int KB = F32 ? 2 : BO::template bytes<1>() / SBK;  // bytes from one k to the next
   // stores per wave per tile, at least: one per pair of bfloat16 tiles (and
   // per odd tile), or one per float32 tile
   constexpr int SW = TM * (kHalf ? (TN + 1) / 2 : TN);
   static_assert(D >= 1 && D <= 3 && D * SW + (D - 1) * IW < 64, "vmcnt range");
-  __shared__ __attribute__((aligned(16))) char lds[NS * TILE + side_bytes<CS>()];
+  __shared__ __attribute__((aligned(16))) char lds[NS * TILE + side_bytes<CS, BM>()];
   static_assert((NS * TILE + bias_bytes<CS>()) % 16 == 0, "16-byte aligned bit words in LDS");
   float *sbias = reinterpret_cast<float *>(lds + NS * TILE);
   uint16_t *sbits = reinterpret_cast<uint16_t *>(lds + NS * TILE + bias_bytes<CS>());
@@ -1197,25 +968,27 @@ __global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda,
   const int q16 = lane & 15, g4 = lane >> 4;
   const int64_t m0 = (int64_t)blockIdx.x * BM;
   const int64_t r0 = m0 + wave * 16 * TM;
-  const int NT = N / BN;
+  // the block's column tiles: all of them, or its share of a split grid
+  const int T0 = (int)((int64_t)(N / BN) * blockIdx.y / gridDim.y);
+  const int NT = (int)((int64_t)(N / BN) * (blockIdx.y + 1) / gridDim.y) - T0;
   const int wpr = N / 16;  // ReLU-bit words per row
   const bool full = m0 + BM <= M;
 
-  // The wave's DMA instructions of a tile (q = wave + 4k: slice q / NI,
+  // The wave's DMA instructions of a tile (q = wave + NWV k: slice q / NI,
   // instruction q % NI of it): per-lane byte offsets from the tile's first
   // table row, and LDS offsets in the slot (the same for every tile: N is a
   // multiple of BN, so no row is clamped).
   uint32_t voff[KW];
   int loff[KW];
-  const int nq = (NIT - wave + 3) / 4;
+  const int nq = (NIT - wave + NWV - 1) / NWV;
 #pragma unroll
   for (int k = 0; k < KW; ++k) {
-    const int q = wave + 4 * k, sl = q / NI, ins = q - sl * NI;
+    const int q = wave + NWV * k, sl = q / NI, ins = q - sl * NI;
     voff[k] = q < NIT ? bo.template lane_off<BN>(ins * 64 + lane, 0) + uint32_t(sl * SBK * KB) : 0u;
     loff[k] = sl * SLAB + ins * 64 * 16;
   }
-  const char *gtab = bo.base(0, 0);
-  const int64_t tstride = bo.base(BN, 0) - gtab;  // bytes between column tiles
+  const int64_t tstride = bo.base(BN, 0) - bo.base(0, 0);  // bytes between column tiles
+  const char *gtab = bo.base(0, 0) + T0 * tstride;
   auto issue = [&](int t) {
     const char *src = gtab + (int64_t)t * tstride;
     char *dst = lds + (t % NS) * TILE;
@@ -1236,17 +1009,17 @@ __global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda,
   for (int t = 0; t < D; ++t)
     if (t < NT) issue(t);
   if constexpr (CS::kBias)
-    for (int c = tid; c < N; c += 256) sbias[c] = cs.bias_n[c];
+    for (int c = tid; c < N; c += NT_) sbias[c] = cs.bias_n[c];
   if constexpr (kMaskIn) {
     // the block's bit words are one run of memory: 16-byte copies when it
     // is whole and aligned (LDS side: the tiles and the bias are multiples
     // of 16 bytes), else word by word with rows clamped
     const uint16_t *src = cs.mbits + m0 * wpr;
     if (full && (BM * wpr) % 8 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-      for (int c = tid; c < BM * wpr / 8; c += 256)
+      for (int c = tid; c < BM * wpr / 8; c += NT_)
         __builtin_memcpy(reinterpret_cast<uint4 *>(sbits) + c, reinterpret_cast<const uint4 *>(src) + c, 16);
     } else {
-      for (int c = tid; c < BM * wpr; c += 256) {
+      for (int c = tid; c < BM * wpr; c += NT_) {
         const int rr = c / wpr;
         int64_t r = m0 + rr;
         if (r >= M) r = M - 1;
@@ -1291,34 +1064,22 @@ __global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda,
     if (t + D < NT) issue(t + D);
 
     const char *tile = lds + (t % NS) * TILE;
-    floatx4 acc[NACC][TM][TN];
+    floatx4 acc[TM][TN], low[F32 ? TM : 1][TN];
 #pragma unroll
-    for (int u = 0; u < NACC; ++u)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[u][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < TN; ++j) {
+        acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (F32) low[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
 #pragma unroll
     for (int sl = 0; sl < KS; ++sl) {
       const char *sb = tile + sl * SLAB;
       if constexpr (F32) {
-        const int nh = K - SBK * sl > 16 ? 2 : 1;
+        bf16x8 b[TN][3];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (h < nh) {
-            floatx4 b[TN];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = bo.template frag4<BN>(sb, j, q16, g4, h);
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-              for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                  acc[jj % NACC][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][jj], a.v[i][2 * sl + h][jj],
-                                                                              acc[jj % NACC][i][j], 0, 0, 0);
-          }
-        }
+        for (int j = 0; j < TN; ++j) bo.template frag3<BN>(sb, j, q16, g4, b[j]);
+        mma_parts(a.v[sl], b, acc, low, 0);
       } else {
         bf16x8 b[TN];
 #pragma unroll
@@ -1327,18 +1088,17 @@ __global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda,
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[0][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a.v[i][sl], acc[0][i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a.v[sl][i], acc[i][j], 0, 0, 0);
       }
     }
-#pragma unroll
-    for (int u = 1; u < NACC; ++u)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[0][i][j] += acc[u][i][j];
+    if constexpr (F32) {
+      add_parts(acc, low);
+      if (const uint64_t bad = bad_tiles(acc))
+        redo_tiles<false>(SKc<false>{A, lda, M}, bo, r0, (int64_t)(T0 + t) * BN, 0, K, bad, acc);
+    }
 
     // epilogue: bias, ReLU, mask, rounding, bits; then the stores
-    const int n0 = t * BN;
+    const int n0 = (T0 + t) * BN;
     floatx4 cbv[TN];
     if constexpr (CS::kBias) {
 #pragma unroll
@@ -1351,7 +1111,7 @@ __global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda,
       floatx4 v[TN];
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        v[j] = acc[0][i][j];
+        v[j] = acc[i][j];
         unsigned mnib = 15u;
         if constexpr (kMaskIn) mnib = (unsigned)sbits[rr * wpr + n0 / 16 + j] >> (4 * g4);
 #pragma unroll
@@ -1410,18 +1170,26 @@ __global__ __launch_bounds__(256) void astat_kernel(const float *A, int64_t lda,
 
   if constexpr (kBitsOut) {
     // the block's bit words, rows m0 .. m0 + BM - 1 (those below M): one
-    // contiguous run of memory
+    // contiguous run of memory, or its columns' words of each row
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int64_t rows = min((int64_t)BM, M - m0);
-    const int64_t nw = rows * wpr;
     uint16_t *dst = cs.obits + m0 * wpr;
+    if (gridDim.y > 1) {
+      const int w0 = T0 * (BN / 16), nw = NT * (BN / 16);
+      for (int64_t c = tid; c < rows * nw; c += NT_) {
+        const int64_t at = c / nw * wpr + w0 + c % nw;
+        dst[at] = sbits[at];
+      }
+      return;
+    }
+    const int64_t nw = rows * wpr;
     if (((reinterpret_cast<uintptr_t>(dst)) & 15) == 0) {
       const int64_t n16 = nw / 8;
-      for (int64_t c = tid; c < n16; c += 256)
+      for (int64_t c = tid; c < n16; c += NT_)
         __builtin_memcpy(dst + 8 * c, reinterpret_cast<const uint4 *>(sbits) + c, 16);
-      for (int64_t c = 8 * n16 + tid; c < nw; c += 256) dst[c] = sbits[c];
+      for (int64_t c = 8 * n16 + tid; c < nw; c += NT_) dst[c] = sbits[c];
     } else {
-      for (int64_t c = tid; c < nw; c += 256) dst[c] = sbits[c];
+      for (int64_t c = tid; c < nw; c += NT_) dst[c] = sbits[c];
     }
   }
 }
@@ -1444,26 +1212,32 @@ template <bool F32>
 bool ok(const TableGemm &t) {
   constexpr int BN = F32 ? DLM_ASTAT_BN_F32 : DLM_ASTAT_BN_BF16;
   return DLM_ASTAT != 0 && !tiled_only() && t.A != nullptr && t.Ah == nullptr && t.K > SBK * (KS - 1) && t.K <= SBK * KS &&
-         t.N % BN == 0 && t.N <= kMaxN && t.N % 16 == 0 && t.M > 0 && (t.M + BM - 1) / BM <= 0x7fffffff;
+         t.N % BN == 0 && t.N <= kMaxN && t.N % 16 == 0 && t.M > 0 && (t.M + BM<F32> - 1) / BM<F32> <= 0x7fffffff;
 }
 
 template <bool F32, class BO, class CS>
 int run(const TableGemm &t, BO bo, CS cs, hipStream_t st) {
   constexpr int BN = F32 ? DLM_ASTAT_BN_F32 : DLM_ASTAT_BN_BF16;
   constexpr int D = F32 ? DLM_ASTAT_D_F32 : DLM_ASTAT_D_BF16;
-  constexpr int NACC = F32 ? DLM_ASTAT_NACC : 1;
-  const unsigned blocks = (unsigned)((t.M + BM - 1) / BM);
+  const unsigned blocks = (unsigned)((t.M + BM<F32> - 1) / BM<F32>);
+  // FP32, whose blocks have a compute unit each: batches with fewer blocks
+  // than that share a row block's columns among several (the rows are read
+  // once more for each)
+  unsigned share = 1;
+  if constexpr (F32)
+    if (blocks < 256) share = std::min<unsigned>(256 / blocks, unsigned(t.N / BN));
+  const dim3 grid(blocks, share), threads(64 * NW<F32>);
   if constexpr (CS::kBias) {  // the forward: ReLU fused or not
     if (t.relu)
-      hipLaunchKernelGGL((astat_kernel<F32, BN, D, NACC, true, BO, CS>), dim3(blocks), dim3(256), 0, st, t.A, t.lda,
-                         t.M, t.K, bo, cs, t.N);
+      hipLaunchKernelGGL((astat_kernel<F32, BN, D, true, BO, CS>), grid, threads, 0, st, t.A, t.lda, t.M, t.K, bo, cs,
+                         t.N);
     else
-      hipLaunchKernelGGL((astat_kernel<F32, BN, D, NACC, false, BO, CS>), dim3(blocks), dim3(256), 0, st, t.A, t.lda,
-                         t.M, t.K, bo, cs, t.N);
+      hipLaunchKernelGGL((astat_kernel<F32, BN, D, false, BO, CS>), grid, threads, 0, st, t.A, t.lda, t.M, t.K, bo, cs,
+                         t.N);
   } else {
     if (t.relu) return -3;  // an input gradient never fuses a ReLU
-    hipLaunchKernelGGL((astat_kernel<F32, BN, D, NACC, false, BO, CS>), dim3(blocks), dim3(256), 0, st, t.A, t.lda,
-                       t.M, t.K, bo, cs, t.N);
+    hipLaunchKernelGGL((astat_kernel<F32, BN, D, false, BO, CS>), grid, threads, 0, st, t.A, t.lda, t.M, t.K, bo, cs,
+                       t.N);
   }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -1474,23 +1248,27 @@ int run(const TableGemm &t, BO bo, CS cs, hipStream_t st) {
 // configuration; for the K = 135 GEMMs it also amortises a block's fixed
 // cost (DMA offsets, first loads, epilogue) over 1.5x the output of 128 x 96
 using SCfgNarrow = SCfg<128, 144, 4, 1, 3>;
-// FP32, N > 144 (two-stage ring): 64-row tiles hold four blocks per CU, which
-// keeps the matrix cores fed through the short (K = 135) reduction and the
-// epilogue
-using SCfgWideF32 = SCfg<64, 96, 2, 2, 2>;
 using SCfgSmall = SCfg<128, 48, 4, 1, 3>;   // N <= 96
-// weight gradient: two float32 operands per stage (34 KB); a two-stage ring
-// keeps two blocks per CU
-using SCfgGrad = SCfg<128, 144, 4, 1, 2>;
-
+// FP32: eight waves of 32 rows, one block per CU (two stages of 60 or 51 KB);
+// the rows share a table tile three times the size of BF16's.  96 columns
+// beyond N = 144: 1440 and 2880 are 15 and 30 tiles, and 8192 rows then give
+// 480 or 960 blocks, 94% of whole rounds of the chip.  Against the float32
+// matrix instructions: 8192 x 2880 x 1440 591 -> 390 us (174 TFLOP/s, 1.05
+// PFLOP/s of part products), K = 1440 onto 135 at 1M voxels 3.30 -> 2.18 ms,
+// the K = 135 kernel below 3.82 -> 2.55 ms.
+using SCfgF144 = SCfg<256, 144, 8, 1, 2>;
+using SCfgF96 = SCfg<256, 96, 8, 1, 2>;
 template <int OP, bool F32, class AO, class BO, class CS>
 int stream_table_c(AO ao, BO bo, CS cs, const TableGemm &t, hipStream_t st) {
   if constexpr (astat::takes<CS>())
     if (astat::ok<F32>(t)) return astat::run<F32>(t, bo, cs, st);
   if (t.N <= 96) return run_stream<OP, SCfgSmall, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
-  if constexpr (F32)
-    if (t.N > 144) return run_stream<OP, SCfgWideF32, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
-  return run_stream<OP, SCfgNarrow, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+  if constexpr (F32) {
+    if (t.N > 144) return run_stream<OP, SCfgF96, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+    return run_stream<OP, SCfgF144, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+  } else {
+    return run_stream<OP, SCfgNarrow, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+  }
 }
 
 // the forward GEMM adds the folded bias; the input-gradient GEMM may mask
@@ -1535,8 +1313,7 @@ int stream_table(AO ao, BO bo, const TableGemm &t, hipStream_t st) {
 
 template <int OP, bool F32, class AO>
 int stream_table_b(AO ao, const TableGemm &t, hipStream_t st) {
-  // float32 tables are read as k-contiguous float32 rows of stride ldb_f
-  if constexpr (F32) return stream_table<OP, true>(ao, SKc<true>{t.Bf, t.ldb_f, t.N}, t, st);
+  if constexpr (F32) return stream_table<OP, true>(ao, SK3{t.B3, t.ldb_h, t.N}, t, st);
   else return stream_table<OP, false>(ao, SKh{t.Bh, t.ldb_h, t.N}, t, st);
 }
 
@@ -1547,11 +1324,6 @@ int stream_table_op(const TableGemm &t, hipStream_t st) {
   const bool vec = t.lda % 4 == 0 && t.K % 4 == 0 && aligned16(t.A);
   if (vec) return stream_table_b<OP, F32>(SKc<true>{t.A, t.lda, t.M}, t, st);
   return stream_table_b<OP, F32>(SKc<false>{t.A, t.lda, t.M}, t, st);
-}
-
-template <bool F32, class AO, class BO, class CS>
-int stream_grad(AO ao, BO bo, CS cs, int64_t rows, int cols, int64_t V, int splits, int ks, hipStream_t st) {
-  return run_stream<kOpFoldGrad, SCfgGrad, F32>(ao, bo, cs, rows, cols, (int)V, splits, ks, st);
 }
 
 }  // namespace streaming
@@ -1576,9 +1348,8 @@ bool stream_table_ok(const TableGemm &t, dlm_precision prec) {
   }
   if (t.lda >= kMaxStreamLd || t.ldb_f >= kMaxStreamLd || t.ldb_h >= kMaxStreamLd) return false;
   if (t.op == kOpFoldFwd ? (t.bias_n == nullptr || t.out_mask != nullptr) : t.bias_n != nullptr) return false;
-  if (prec == DLM_BF16)
-    return t.Bh != nullptr && t.ldb_h > 0 && t.ldb_h % SBK == 0 && t.ldb_h >= t.K && aligned16(t.Bh);
-  return t.Bf != nullptr && t.ldb_f > 0 && t.ldb_f % SBK == 0 && t.ldb_f >= t.K && aligned16(t.Bf);
+  const uint16_t *B = prec == DLM_BF16 ? t.Bh : t.B3;
+  return B != nullptr && t.ldb_h > 0 && t.ldb_h % SBK == 0 && t.ldb_h >= t.K && aligned16(B);
 }
 
 int launch_stream_table(const TableGemm &t, dlm_precision prec, void *stream) {
@@ -1591,59 +1362,6 @@ int launch_stream_table(const TableGemm &t, dlm_precision prec, void *stream) {
       return f32 ? stream_table_op<kOpFoldBwdData, true>(t, st) : stream_table_op<kOpFoldBwdData, false>(t, st);
     default: return -3;
   }
-}
-
-// dT[m][n] = sum_v g[v][m] * act[v][n] over voxel slices, act with a ones
-// column at n = CK (the bias term); the larger of M and CK + 1 on the row side.
-// g and act each come as float32 (g, a) or, in BF16, bfloat16 (gh, ah).
-struct GradArgs {
-  int64_t V;
-  int M, CK, splits, ksplit;
-  float *partial;
-  hipStream_t st;
-};
-
-template <bool F32, class GO, class AOp>
-static int grad_orient(GO go, AOp aop, const GradArgs &x) {
-  const int N1 = x.CK + 1;
-  if (x.M >= N1)
-    return stream_grad<F32>(go, aop, CPartial2<false>{x.partial, x.M, N1}, x.M, N1, x.V, x.splits, x.ksplit, x.st);
-  return stream_grad<F32>(aop, go, CPartial2<true>{x.partial, x.M, N1}, N1, x.M, x.V, x.splits, x.ksplit, x.st);
-}
-
-template <bool F32, class GO>
-static int grad_act(GO go, const float *a, const uint16_t *ah, const GradArgs &x) {
-  const int CK = x.CK;
-  if constexpr (!F32)
-    if (ah) return grad_orient<F32>(go, SRb<true>{ah, CK, CK, CK}, x);
-  if (CK % 4 == 0 && aligned16(a)) return grad_orient<F32>(go, SRc<true, true>{a, CK, CK, CK}, x);
-  return grad_orient<F32>(go, SRc<false, true>{a, CK, CK, CK}, x);
-}
-
-template <bool F32>
-static int stream_grad_p(const float *g, const uint16_t *gh, const float *a, const uint16_t *ah, const GradArgs &x) {
-  const int M = x.M;
-  if constexpr (!F32)
-    if (gh) return grad_act<F32>(SRb<false>{gh, M, M, -1}, a, ah, x);
-  if (M % 4 == 0 && aligned16(g)) return grad_act<F32>(SRc<true, false>{g, M, M, -1}, a, ah, x);
-  return grad_act<F32>(SRc<false, false>{g, M, M, -1}, a, ah, x);
-}
-
-bool stream_grad_ok(int M, int CK, int ksplit) {
-  return ksplit % SBK == 0 && M < kMaxStreamLd && CK < kMaxStreamLd;
-}
-
-bool stream_grad_bf16_ok(const uint16_t *gh, const uint16_t *ah, int M, int CK) {
-  return (!gh || (M % 8 == 0 && aligned16(gh))) && (!ah || (CK % 8 == 0 && aligned16(ah)));
-}
-
-int launch_stream_grad(const float *g, const uint16_t *gh, const float *a, const uint16_t *ah, int64_t V, int M,
-                       int CK, int splits, int ksplit, float *partial, dlm_precision prec, void *stream) {
-  if (!stream_grad_ok(M, CK, ksplit)) return -2;
-  if ((gh || ah) && (prec != DLM_BF16 || !stream_grad_bf16_ok(gh, ah, M, CK))) return -3;
-  const GradArgs x{V, M, CK, splits, ksplit, partial, (hipStream_t)stream};
-  if (prec == DLM_BF16) return stream_grad_p<false>(g, gh, a, ah, x);
-  return stream_grad_p<true>(g, nullptr, a, nullptr, x);
 }
 
 }  // namespace dlm
