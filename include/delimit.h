@@ -286,6 +286,30 @@ typedef enum { DLM_IO_IN_BF16 = 1, DLM_IO_OUT_BF16 = 2 } dlm_io_flags;
  * written whole by the forward, read by the backward; NULL = not used.
  * Needs the folded form (DLM_EINVAL otherwise). */
 
+/* Images: the layers on [B][channels][P] device arrays (B subjects, the
+ * channels of the layer, P = H*W*D voxels, contiguous), read and written as
+ * they are: the channel index of a signal is the shell-major volume, of
+ * coefficients shell * K + coefficient (channel * K for an LSC).  The same
+ * arithmetic as the voxel-major calls.  B in [1, 128], P in [1, 2^24).
+ * dlm_sh_image: Signal2SH, SH2Signal or an adjoint, at most 128 directions per
+ * shell and 128 coefficients. */
+typedef enum { DLM_SIGNAL2SH_FWD = 0, DLM_SIGNAL2SH_BWD = 1, DLM_SH2SIGNAL_FWD = 2, DLM_SH2SIGNAL_BWD = 3 } dlm_sh_op;
+int dlm_sh_image_supported(const dlm_sh_plan *plan, int64_t B, int64_t P);
+dlm_status dlm_sh_image(const dlm_sh_plan *plan, dlm_sh_op op, const float *in, float *out, int64_t B,
+                        int64_t P, dlm_precision prec, void *stream);
+/* The folded LSC layer and its adjoint on images; workspace as for the folded
+ * form.  relu_bits: NULL, or (needs fuse_relu) a device array of uint16
+ * [B][O*K_out][(P+15)/16] whose bit v % 16 of word [..][v / 16] the forward
+ * sets to 1 iff the output there is > 0; the backward masks da_out by it (the
+ * gradient of a layer whose forward fused a ReLU). */
+dlm_status dlm_lsc_fwd_image(const dlm_lsc_plan *plan, const float *a_in, int C, const float *W,
+                             const float *bias, int O, float *a_out, int64_t B, int64_t P, int fuse_relu,
+                             uint16_t *relu_bits, void *ws, size_t ws_bytes, dlm_precision prec, void *stream);
+dlm_status dlm_lsc_bwd_image(const dlm_lsc_plan *plan, const float *a_in, int C, const float *W, int O,
+                             const uint16_t *relu_bits, const float *da_out, float *da_in, float *dW,
+                             float *dbias, int64_t B, int64_t P, void *ws, size_t ws_bytes,
+                             dlm_precision prec, void *stream);
+
 /* dlm_lsc_fwd with activation storage chosen by io_flags (void pointers to
  * float32 or bfloat16 data as the flags say); io_flags = 0 is dlm_lsc_fwd.
  * relu_bits (NULL or as above, needs fuse_relu) receives the output's ReLU

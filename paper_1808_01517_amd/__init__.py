@@ -385,6 +385,78 @@ def lsc_bwd(plan: LSCPlan, a_in: torch.Tensor, W: torch.Tensor, da_out: torch.Te
     return da_in, (dW if need_weight_grad else None), db
 
 
+# ----------------------------------------------------------------- images
+SIGNAL2SH_FWD, SIGNAL2SH_BWD, SH2SIGNAL_FWD, SH2SIGNAL_BWD = range(4)
+MAX_IMAGES, MAX_IMAGE_VOXELS = 128, 1 << 24  # exclusive for the voxels
+
+
+def sh_image_supported(plan: SHPlan, B: int, P: int) -> bool:
+    """Whether sh_image takes this plan on B images of P voxels."""
+    return bool(lib().dlm_sh_image_supported(plan.handle, B, P))
+
+
+def sh_image(plan: SHPlan, op: int, x: torch.Tensor, precision="fp32") -> torch.Tensor:
+    """Signal2SH, SH2Signal or an adjoint (`op`) of x [B][channels][...voxels],
+    channels = n_dw or n_shells * K, to the other, in the same layout."""
+    x = _f32_dev(x, "input")
+    to_coef = op in (SIGNAL2SH_FWD, SH2SIGNAL_BWD)
+    ch = (plan.n_dw, plan.n_shells * plan.K) if to_coef else (plan.n_shells * plan.K, plan.n_dw)
+    if x.dim() < 3 or x.shape[1] != ch[0]:
+        raise ValueError(f"input must be [B, {ch[0]}, voxels]")
+    out = torch.empty((x.shape[0], ch[1], *x.shape[2:]), dtype=torch.float32, device=x.device)
+    check(lib().dlm_sh_image(plan.handle, op, _ptr(x), _ptr(out), x.shape[0], x.shape[2:].numel(),
+                             precision_code(precision), _stream(x)))
+    return out
+
+
+def image_bits_like(out: torch.Tensor) -> torch.Tensor:
+    """An int16 buffer for the ReLU bits of an image [B][channels][...voxels]."""
+    return torch.empty((out.shape[0], out.shape[1], (out.shape[2:].numel() + 15) // 16), dtype=torch.int16,
+                       device=out.device)
+
+
+def lsc_fwd_image(plan: LSCPlan, a: torch.Tensor, W: torch.Tensor, bias=None, relu: bool = False, precision="fp32",
+                  need_bits: bool = False):
+    """(a_out [B][O*K_out][...voxels], its ReLU bits or None) of the folded
+    layer on a [B][C*K_in][...voxels], W [O][C][T]."""
+    a = _f32_dev(a, "a_in")
+    W = _f32_dev(W, "W").reshape(W.shape[0], W.shape[1], -1)
+    O, Cin, T = W.shape
+    if a.dim() < 3 or a.shape[1] != Cin * plan.K_in or T != plan.T:
+        raise ValueError(f"shapes: a_in {tuple(a.shape)}, W {tuple(W.shape)}, plan K_in={plan.K_in} T={plan.T}")
+    if bias is not None:
+        bias = _f32_dev(bias, "bias")
+        if bias.numel() != O:
+            raise ValueError("bias must have O entries")
+    prec = precision_code(precision)
+    B, P = a.shape[0], a.shape[2:].numel()
+    ws = _default_ws(plan, Cin, O, B * P, prec, a.device, "folded")
+    out = torch.empty((B, O * plan.K_out, *a.shape[2:]), dtype=torch.float32, device=a.device)
+    bits = image_bits_like(out) if need_bits and relu else None
+    check(lib().dlm_lsc_fwd_image(plan.handle, _ptr(a), Cin, _ptr(W), _ptr(bias), O, _ptr(out), B, P, int(bool(relu)),
+                                  _ptr(bits), ws.ptr(), ws.nbytes, prec, _stream(a)))
+    return out, bits
+
+
+def lsc_bwd_image(plan: LSCPlan, a: torch.Tensor, W: torch.Tensor, g: torch.Tensor, bits=None, need_input_grad=True,
+                  need_weight_grad=True, need_bias_grad=True, precision="fp32"):
+    """(da_in or None, dW [O][C][T] or None, dbias [O] or None) of lsc_fwd_image
+    for the output gradient g, masked by the forward's ReLU bits."""
+    a, g = _f32_dev(a, "a_in"), _f32_dev(g, "da_out")
+    W = _f32_dev(W, "W").reshape(W.shape[0], W.shape[1], -1)
+    O, Cin, _ = W.shape
+    prec = precision_code(precision)
+    B, P = a.shape[0], a.shape[2:].numel()
+    ws = _default_ws(plan, Cin, O, B * P, prec, a.device, "folded")
+    da = torch.empty_like(a) if need_input_grad else None
+    need_dW = need_weight_grad or need_bias_grad
+    dW = torch.empty((O, Cin, plan.T), dtype=torch.float32, device=a.device) if need_dW else None
+    db = torch.empty((O,), dtype=torch.float32, device=a.device) if need_bias_grad else None
+    check(lib().dlm_lsc_bwd_image(plan.handle, _ptr(a), Cin, _ptr(W), O, _ptr(bits), _ptr(g), _ptr(da), _ptr(dW),
+                                  _ptr(db), B, P, ws.ptr(), ws.nbytes, prec, _stream(a)))
+    return da, (dW if need_weight_grad else None), db
+
+
 # --------------------------------------------------------------- training
 def mse_fwd_bwd(pred: torch.Tensor, target: torch.Tensor, need_grad: bool = True, outs=None):
     """(loss device scalar, dpred) for loss = mean((pred - target)^2).

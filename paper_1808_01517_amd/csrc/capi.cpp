@@ -994,6 +994,27 @@ dlm_status lsc_fwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
   return launched(launch_table_gemm(t, prec, stream));
 }
 
+// dW and dbias from `splits` partial gradients of the folded matrix.  Few of
+// them are added up as the unfold reads them; many (the narrow layers' 100 MB
+// of them), and none, go through a pass of their own that spreads over the
+// chip, which O C blocks would not.
+dlm_status unfold_weights(const dlm_lsc_plan *p, int C, int O, const FoldWs &w, int splits, float *dW, float *dbias,
+                          void *stream) {
+  const int M = O * p->K_out, N1 = C * p->K_in + 1;
+  const float *dT = w.part;
+  if (splits > kUnfoldSplits || splits == 0) {
+    TimedScope ts("lsc_fold_reduce", stream, double(M) * N1 * 4.0, double(splits) * M * N1);
+    dlm_status s = launched(launch_sum_partials(w.part, splits, int64_t(M) * N1, w.dTw, stream));
+    if (s != DLM_OK) return s;
+    dT = w.dTw;
+    splits = 1;
+  }
+  TimedScope ts("lsc_unfold", stream, (double(M) * N1 + p->T * double(p->K_out) * p->K_in + double(O) * C * p->T) * 4.0,
+                2.0 * O * C * p->T * double(p->K_out) * p->K_in);
+  return launched(launch_lsc_unfold(dT, splits, p->dQ.f32, p->dpm1.f32, C, O, p->T, p->K_in, p->K_out, dW, dbias,
+                                    stream));
+}
+
 dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const float *W, int O, const void *a_out,
                           const void *da_out, void *da_in, float *dW, float *dbias, int64_t V, int relu_flags, int io,
                           const uint16_t *relu_bits, void *ws, size_t ws_bytes, dlm_precision prec, void *stream) {
@@ -1061,21 +1082,7 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
       s = launched(launch_lsc_fold_grad(x, prec, stream));
       if (s != DLM_OK) return s;
     }
-    // Few partial matrices are added up as the unfold reads them; many (the
-    // narrow layers' 100 MB of them) go through a pass of their own that
-    // spreads over the chip, which O C blocks would not.
-    const float *dT = w.part;
-    if (splits > kUnfoldSplits || splits == 0) {
-      TimedScope ts("lsc_fold_reduce", stream, double(M) * N1 * 4.0, double(splits) * M * N1);
-      if ((s = launched(launch_sum_partials(w.part, splits, int64_t(M) * N1, w.dTw, stream))) != DLM_OK) return s;
-      dT = w.dTw;
-      splits = 1;
-    }
-    TimedScope ts("lsc_unfold", stream, (double(M) * N1 + p->T * double(p->K_out) * p->K_in + double(O) * C * p->T) * 4.0,
-                  2.0 * O * C * p->T * double(p->K_out) * p->K_in);
-    if ((s = launched(launch_lsc_unfold(dT, splits, p->dQ.f32, p->dpm1.f32, C, O, p->T, p->K_in, p->K_out, dW, dbias,
-                                        stream))) != DLM_OK)
-      return s;
+    return unfold_weights(p, C, O, w, splits, dW, dbias, stream);
   }
   return DLM_OK;
 }
@@ -1102,6 +1109,142 @@ dlm_status io_check(const dlm_lsc_plan *p, int C, int O, int io, dlm_lsc_form fo
   return DLM_OK;
 }
 }  // namespace
+
+namespace {
+dlm_status image_check(int64_t B, int64_t P) {
+  if (B < 1 || P < 1 || !image_ok(B, P))
+    return fail(DLM_EINVAL, "%lld images of %lld voxels: needs 1..128 images of fewer than 2^24", (long long)B,
+                (long long)P);
+  return DLM_OK;
+}
+}  // namespace
+
+int dlm_sh_image_supported(const dlm_sh_plan *p, int64_t B, int64_t P) {
+  if (!p || !image_ok(B, P) || p->K > 128) return 0;
+  for (int s = 0; s < p->S; ++s)
+    if (p->dirs[s] > 128) return 0;
+  return 1;
+}
+
+dlm_status dlm_sh_image(const dlm_sh_plan *p, dlm_sh_op op, const float *in, float *out, int64_t B, int64_t P,
+                        dlm_precision prec, void *stream) {
+  if (!p) return fail(DLM_EINVAL, "plan is NULL");
+  if (prec != DLM_FP32 && prec != DLM_BF16) return fail(DLM_EINVAL, "unknown precision %d", int(prec));
+  if (int(op) < 0 || int(op) > 3) return fail(DLM_EINVAL, "unknown transform %d", int(op));
+  if ((op == DLM_SIGNAL2SH_FWD || op == DLM_SIGNAL2SH_BWD) && !p->fit_ok) return no_fit(p);
+  dlm_status st = image_check(B, P);
+  if (st != DLM_OK) return st;
+  if (!dlm_sh_image_supported(p, B, P)) return fail(DLM_EINVAL, "more than 128 directions per shell or coefficients");
+  if (!in || !out) return fail(DLM_EINVAL, "null device pointer");
+  const bool to_coef = op == DLM_SIGNAL2SH_FWD || op == DLM_SH2SIGNAL_BWD;
+  static const char *const tags[] = {"signal2sh_fwd", "signal2sh_bwd", "sh2signal_fwd", "sh2signal_bwd"};
+  const int K = p->K, S = p->S, ti = int(op);
+  for (int s0 = 0; s0 < (p->uniform ? 1 : S); ++s0) {
+    const int N = int(p->dirs[s0]);
+    const int64_t sig = p->uniform ? 0 : p->offs[s0], coef = p->uniform ? 0 : int64_t(s0) * K;
+    ShellImage x;
+    x.in = in + (to_coef ? sig : coef) * P;
+    x.out = out + (to_coef ? coef : sig) * P;
+    x.in_ch = int(to_coef ? p->n_dw : int64_t(S) * K);
+    x.out_ch = int(to_coef ? int64_t(S) * K : p->n_dw);
+    x.a_gs = to_coef ? N : K;
+    x.c_gs = to_coef ? K : N;
+    x.ncol = to_coef ? K : N;
+    x.nred = to_coef ? N : K;
+    x.groups = p->uniform ? S : 1;
+    x.B = int(B);
+    x.P = P;
+    x.frag_f = p->fragF[ti] + p->frag_offF[ti][s0];
+    x.frag_h = p->fragH[ti] + p->frag_offH[ti][s0];
+    x.frag_gs_f = int64_t(shell_frag_floats(x.ncol, x.nred) * sizeof(float));
+    x.frag_gs_h = int64_t(shell_frag_halves(x.ncol, x.nred) * sizeof(uint16_t));
+    const double n = double(B) * double(P) * x.groups;
+    TimedScope ts(tags[ti], stream, n * (double(N) + K) * 4.0, 2.0 * n * N * K);
+    if ((st = launched(launch_shell_image(x, prec, stream))) != DLM_OK) return st;
+  }
+  return ok();
+}
+
+dlm_status dlm_lsc_fwd_image(const dlm_lsc_plan *p, const float *a_in, int C, const float *W, const float *bias, int O,
+                             float *a_out, int64_t B, int64_t P, int fuse_relu, uint16_t *relu_bits, void *ws,
+                             size_t ws_bytes, dlm_precision prec, void *stream) {
+  dlm_status s = lsc_check(p, C, O, P, prec);
+  if (s != DLM_OK) return s;
+  if ((s = image_check(B, P)) != DLM_OK) return s;
+  if (relu_bits && !fuse_relu) return fail(DLM_EINVAL, "ReLU bits need fuse_relu");
+  if (!a_in || !W || !a_out || !ws) return fail(DLM_EINVAL, "null device pointer");
+  if (ws_bytes < fold_ws_need(p, C, O))
+    return fail(DLM_EWORKSPACE, "workspace of %zu bytes is below the %zu-byte minimum", ws_bytes, fold_ws_need(p, C, O));
+  FoldWs w = fold_ws_carve(p, C, O, ws);
+  if ((s = fold_weights(p, C, O, W, bias, w, false, false, prec, stream)) != DLM_OK) return s;
+  ImageGemm x;
+  x.in = a_in;
+  x.table = prec == DLM_BF16 ? w.Twh : w.parts;
+  x.K = C * p->K_in;
+  x.N = O * p->K_out;
+  x.ldb = int64_t(pad32(size_t(x.K)));
+  x.bias = w.bvec;
+  x.relu = fuse_relu ? 1 : 0;
+  x.out = a_out;
+  x.obits = relu_bits;
+  x.B = int(B);
+  x.P = P;
+  x.op = kOpFoldFwd;
+  const double V = double(B) * double(P);
+  TimedScope ts("lsc_folded_fwd", stream, V * (4.0 * x.K + 4.0 * x.N + (relu_bits ? x.N / 8.0 : 0.0)),
+                2.0 * V * x.N * x.K);
+  s = launched(launch_image_gemm(x, prec, stream));
+  return s == DLM_OK ? ok() : s;
+}
+
+dlm_status dlm_lsc_bwd_image(const dlm_lsc_plan *p, const float *a_in, int C, const float *W, int O,
+                             const uint16_t *relu_bits, const float *da_out, float *da_in, float *dW, float *dbias,
+                             int64_t B, int64_t P, void *ws, size_t ws_bytes, dlm_precision prec, void *stream) {
+  dlm_status s = lsc_check(p, C, O, P, prec);
+  if (s != DLM_OK) return s;
+  if ((s = image_check(B, P)) != DLM_OK) return s;
+  if (dbias && !dW) return fail(DLM_EINVAL, "dbias without dW is not supported");
+  if (!a_in || !W || !da_out || !ws) return fail(DLM_EINVAL, "null device pointer");
+  if (ws_bytes < fold_ws_need(p, C, O))
+    return fail(DLM_EWORKSPACE, "workspace of %zu bytes is below the %zu-byte minimum", ws_bytes, fold_ws_need(p, C, O));
+  FoldWs w = fold_ws_carve(p, C, O, ws);
+  const int M = O * p->K_out, CK = C * p->K_in;
+  const double V = double(B) * double(P), bits = relu_bits ? M / 8.0 : 0.0;
+  if (da_in) {
+    if ((s = fold_weights(p, C, O, W, nullptr, w, true, false, prec, stream)) != DLM_OK) return s;
+    ImageGemm x;
+    x.in = da_out;
+    x.ibits = relu_bits;
+    x.table = prec == DLM_BF16 ? w.TwTh : w.parts;
+    x.K = M;
+    x.N = CK;
+    x.ldb = int64_t(pad32(size_t(M)));
+    x.out = da_in;
+    x.B = int(B);
+    x.P = P;
+    x.op = kOpFoldBwdData;
+    TimedScope ts("lsc_folded_bwd_data", stream, V * (4.0 * M + bits + 4.0 * CK), 2.0 * V * M * CK);
+    if ((s = launched(launch_image_gemm(x, prec, stream))) != DLM_OK) return s;
+  }
+  if (dW) {
+    ImageGrad x;
+    x.g = da_out;
+    x.gbits = relu_bits;
+    x.a = a_in;
+    x.M = M;
+    x.CK = CK;
+    x.B = int(B);
+    x.P = P;
+    x.slices = image_grad_slices(int(B), P, M, CK + 1);
+    x.partial = w.part;
+    {
+      TimedScope ts("lsc_folded_grad", stream, V * (4.0 * M + bits + 4.0 * CK), 2.0 * V * M * (CK + 1));
+      if ((s = launched(launch_image_grad(x, prec, stream))) != DLM_OK) return s;
+    }
+    if ((s = unfold_weights(p, C, O, w, x.B * x.slices, dW, dbias, stream)) != DLM_OK) return s;
+  }
+  return ok();
+}
 
 dlm_status dlm_lsc_fwd_io(const dlm_lsc_plan *p, const void *a_in, int C, const float *W, const float *bias, int O,
                           void *a_out, int64_t V, int fuse_relu, int io_flags, uint16_t *relu_bits, dlm_lsc_form form,

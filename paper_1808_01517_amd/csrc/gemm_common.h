@@ -96,4 +96,15 @@ struct CRowMajor {
   }
 };
 
+// The 16-bit ReLU word of 16 consecutive elements held by four lanes (q16,
+// g4), each with the nibble of its four: two row swaps OR them together in
+// every lane.
+__device__ __forceinline__ unsigned bits_word(unsigned nib, int g4) {
+  unsigned w = nib << (4 * g4);
+  const auto s16 = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  w = s16[0] | s16[1];
+  const auto s32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return s32[0] | s32[1];
+}
+
 }  // namespace dlm

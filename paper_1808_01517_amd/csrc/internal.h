@@ -111,6 +111,50 @@ struct GradGemm {
 };
 int launch_lsc_fold_grad(const GradGemm &x, dlm_precision prec, void *stream);
 int fold_grad_splits(int64_t V, int M, int N1);
+// The folded layer on images [B][channels][P voxels] (csrc/tile.hip):
+//   out[b][n][v] = sum_k table[n][k] in[b][k][v] + bias[n], optional ReLU,
+// the table bfloat16 (BF16) or three-part (FP32), rows of ldb entries a part.
+// ibits: in is zeroed where its ReLU bit is clear; obits receives the
+// output's.  ReLU bits of an image: bit v % 16 of word [b][n][v / 16].
+struct ImageGemm {
+  const float *in = nullptr;
+  const uint16_t *ibits = nullptr;
+  const uint16_t *table = nullptr;
+  int64_t ldb = 0;
+  const float *bias = nullptr;
+  float *out = nullptr;
+  uint16_t *obits = nullptr;
+  int64_t P = 0;
+  int B = 0, N = 0, K = 0, relu = 0;
+  KernelOp op = kOpFoldFwd;
+};
+bool image_ok(int64_t B, int64_t P);  // whether the image kernels take these sizes
+int launch_image_gemm(const ImageGemm &x, dlm_precision prec, void *stream);
+// partial[b * slices + s][m][n] = sum over slice s of image b of g[b][m][v] a[b][n][v], a's row CK all ones
+struct ImageGrad {
+  const float *g = nullptr, *a = nullptr;
+  const uint16_t *gbits = nullptr;
+  int64_t P = 0;
+  int B = 0, M = 0, CK = 0, slices = 1;
+  float *partial = nullptr;
+};
+int image_grad_slices(int B, int64_t P, int M, int N1);
+int launch_image_grad(const ImageGrad &x, dlm_precision prec, void *stream);
+// Per-shell SH contraction on images: c[b][g*c_gs + n][v] = sum_k Bt_g[n][k]
+// in[b][g*a_gs + k][v], the tables in fragment order as for ShellGemm;
+// in_ch / out_ch channels per image, nred <= 128.
+struct ShellImage {
+  const float *in = nullptr;
+  float *out = nullptr;
+  int in_ch = 0, out_ch = 0, a_gs = 0, c_gs = 0;
+  const float *frag_f = nullptr;
+  const uint16_t *frag_h = nullptr;
+  int64_t frag_gs_f = 0, frag_gs_h = 0;
+  int ncol = 0, nred = 0, groups = 1, B = 0;
+  int64_t P = 0;
+};
+int launch_shell_image(const ShellImage &x, dlm_precision prec, void *stream);
+
 // Per-shell SH contraction, one wave per 16 voxels x one shell (groups
 // shells of equal size in one launch):
 //   C[v][g*c_gs + n] = sum_k A[v][g*a_gs + k] * Bt_g[n][k],  n < ncol, k < nred

@@ -904,17 +904,6 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, h2));
 }
 
-// The 16-bit ReLU word of one row's 16-column tile: each of the row's four
-// lanes (q16, g4) holds the nibble of its four columns; two row swaps OR
-// them together in every lane.
-__device__ __forceinline__ unsigned bits_word(unsigned nib, int g4) {
-  unsigned w = nib << (4 * g4);
-  const auto s16 = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-  w = s16[0] | s16[1];
-  const auto s32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return s32[0] | s32[1];
-}
-
 // Two adjacent 16-column tiles of one row in bfloat16 (lane g4 holds
 // columns 4 g4 .. 4 g4 + 3 of both, two packed words each): a row swap
 // hands each lane 8 contiguous columns, stored with one 16-byte store.

@@ -7,8 +7,10 @@ sampled_gradients, sh_order_in, sh_order_out, kernel_sizes,
 angular_distance, lb_lambda) with its kernel at `lsc.sconv.weight`
 [O, C, 1, n+1] and `lsc.sconv.bias` [O].  Tensors are either the paper's
 5-D layout subjects x (#shells * #dirs or #channels * K) x H x W x D, or
-voxel-major [V, ...]; 5-D inputs are permuted to voxel-major for the
-library and back.  Forward and backward both run in the library's HIP
+voxel-major [V, ...].  The library's image kernels read and write 5-D tensors as they
+are; what they do not take (the resample form, more than 128 directions per
+shell) and 5-D inputs that already lie voxel-major in memory go through the
+voxel-major calls, permuted to and back.  Forward and backward both run in the library's HIP
 kernels; PyTorch only holds the memory.
 """
 from __future__ import annotations
@@ -17,8 +19,10 @@ import numpy as np
 import torch
 from torch import nn
 
-from . import (DEFAULT_FORM, LSCPlan, SHPlan, lsc_bwd, lsc_fwd, sh2signal_bwd, sh2signal_fwd, signal2sh_bwd,
-               signal2sh_fwd)
+from . import (DEFAULT_FORM, MAX_IMAGE_VOXELS, MAX_IMAGES, SH2SIGNAL_BWD, SH2SIGNAL_FWD, SIGNAL2SH_BWD, SIGNAL2SH_FWD,
+               LSCPlan, SHPlan, form_code, lsc_bwd, lsc_bwd_image, lsc_fwd, lsc_fwd_image, sh2signal_bwd, sh2signal_fwd,
+               sh_image, sh_image_supported, signal2sh_bwd, signal2sh_fwd)
+from ._lib import DLM_LSC_FOLDED
 
 
 def _to_voxels(t: torch.Tensor, channels: int):
@@ -36,6 +40,53 @@ def _from_voxels(v: torch.Tensor, info):
         return v
     B, H, W, D = info
     return v.reshape(B, H, W, D, -1).permute(0, 4, 1, 2, 3).contiguous()
+
+
+def _as_image(x: torch.Tensor, channels: int) -> bool:
+    """Whether a 5-D input goes to the image kernels: unless it already lies
+    voxel-major in memory (then the voxel-major form is a view of it)."""
+    if x.dim() != 5:
+        return False
+    B, ch, H, W, D = x.shape
+    if ch != channels:
+        raise ValueError(f"expected {channels} channels, got {ch}")
+    if not (x.is_cuda and x.dtype == torch.float32 and 1 <= B <= MAX_IMAGES and 1 <= H * W * D < MAX_IMAGE_VOXELS):
+        return False
+    return x.is_contiguous() or not x.permute(0, 2, 3, 4, 1).is_contiguous()
+
+
+class _SHImageFn(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, x, plan, op, adjoint, precision):
+        ctx.plan, ctx.adjoint, ctx.precision = plan, adjoint, precision
+        return sh_image(plan, op, x, precision=precision)
+
+    @staticmethod
+    def backward(ctx, g):
+        return sh_image(ctx.plan, ctx.adjoint, g, precision=ctx.precision), None, None, None, None
+
+
+class _LSCImageFn(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, a, W, b, plan, relu, precision, grad):
+        out, bits = lsc_fwd_image(plan, a, W, b, relu=relu, precision=precision, need_bits=grad)
+        if grad:
+            ctx.plan, ctx.precision = plan, precision
+            ctx.has_bias = b is not None
+            # a copy, as the voxel-major form keeps one: the caller may change
+            # its input (and the output) before the backward
+            ctx.save_for_backward(a.clone() if ctx.needs_input_grad[1] or ctx.needs_input_grad[2] else a, W, bits)
+        return out
+
+    @staticmethod
+    def backward(ctx, g):
+        a, W, bits = ctx.saved_tensors
+        need_a, need_W, need_b = ctx.needs_input_grad[0], ctx.needs_input_grad[1], ctx.needs_input_grad[2]
+        da, dW, db = lsc_bwd_image(ctx.plan, a, W, g, bits, need_input_grad=need_a, need_weight_grad=need_W,
+                                   need_bias_grad=need_b and ctx.has_bias, precision=ctx.precision)
+        if dW is not None:
+            dW = dW.view_as(W)
+        return da, dW, db, None, None, None, None
 
 
 class _Signal2SHFn(torch.autograd.Function):
@@ -98,6 +149,8 @@ class Signal2SH(nn.Module):
         self.precision = precision
 
     def forward(self, x):
+        if _as_image(x, self.plan.n_dw) and sh_image_supported(self.plan, x.shape[0], x.shape[2:].numel()):
+            return _SHImageFn.apply(x, self.plan, SIGNAL2SH_FWD, SIGNAL2SH_BWD, self.precision)
         v, info = _to_voxels(x, self.plan.n_dw)
         c = _Signal2SHFn.apply(v, self.plan, self.precision)
         return _from_voxels(c.reshape(c.shape[0], -1), info) if info else c
@@ -116,6 +169,8 @@ class SH2Signal(nn.Module):
 
     def forward(self, c):
         p = self.plan
+        if _as_image(c, p.n_shells * p.K) and sh_image_supported(p, c.shape[0], c.shape[2:].numel()):
+            return _SHImageFn.apply(c, p, SH2SIGNAL_FWD, SH2SIGNAL_BWD, self.precision)
         v, info = _to_voxels(c, p.n_shells * p.K)
         x = _SH2SignalFn.apply(v.reshape(-1, p.n_shells, p.K), p, self.precision)
         return _from_voxels(x, info) if info else x
@@ -144,9 +199,12 @@ class LocalSphericalConvolution(nn.Module):
 
     def forward(self, a):
         p = self.plan
-        v, info = _to_voxels(a, self.C * p.K_in)
         W = self.sconv.weight
         b = self.sconv.bias
+        if form_code(self.form) == DLM_LSC_FOLDED and _as_image(a, self.C * p.K_in):
+            return _LSCImageFn.apply(a, W.reshape(self.O, self.C, -1), b, p, self.relu, self.precision,
+                                     torch.is_grad_enabled())
+        v, info = _to_voxels(a, self.C * p.K_in)
         out = _LSCFn.apply(v.reshape(-1, self.C, p.K_in), W.reshape(self.O, self.C, -1), b, p, self.relu,
                            self.precision, self.form)
         return _from_voxels(out.reshape(out.shape[0], -1), info) if info else out
