@@ -488,6 +488,35 @@ namespace {
 
 enum class ShOp { S2shFwd, S2shBwd, Sh2sFwd, Sh2sBwd };
 
+// The plan's transform `op` on whole rows; S = 0 when the plan has more shells
+// than one launch takes.
+ShellRows shell_rows(const dlm_sh_plan *p, ShOp op, int64_t V) {
+  ShellRows x;
+  if (p->S > kMaxRowShells || p->n_dw > (1 << 20)) return x;
+  const bool to_coef = (op == ShOp::S2shFwd || op == ShOp::Sh2sBwd);
+  const int ti = int(op), SK = p->S * p->K;
+  x.V = V;
+  x.n_in = to_coef ? int(p->n_dw) : SK;
+  x.n_out = to_coef ? SK : int(p->n_dw);
+  x.S = p->S;
+  x.frag_f = p->fragF[ti];
+  x.frag_h = p->fragH[ti];
+  for (int s = 0; s < p->S; ++s) {
+    const int N = int(p->dirs[s]), off = int(p->offs[s]);
+    ShellRows::Shell &t = x.sh[s];
+    t.in_off = to_coef ? off : s * p->K;
+    t.out_off = to_coef ? s * p->K : off;
+    t.nred = to_coef ? N : p->K;
+    t.ncol = to_coef ? p->K : N;
+    t.unit0 = x.units;
+    t.frag_f = p->frag_offF[ti][s];
+    t.frag_h = p->frag_offH[ti][s];
+    x.units += (t.ncol + 15) / 16;
+    x.max_red = std::max(x.max_red, t.nred);
+  }
+  return x;
+}
+
 dlm_status sh_apply(const dlm_sh_plan *p, const float *in, float *out, int64_t V, dlm_precision prec, void *stream,
                     ShOp op) {
   if (!p) return fail(DLM_EINVAL, "plan is NULL");
@@ -503,6 +532,19 @@ dlm_status sh_apply(const dlm_sh_plan *p, const float *in, float *out, int64_t V
   const DevMat &tab = op == ShOp::S2shFwd ? p->dP : op == ShOp::S2shBwd ? p->dPt : op == ShOp::Sh2sFwd ? p->dB : p->dBt;
   static const char *const tags[] = {"signal2sh_fwd", "signal2sh_bwd", "sh2signal_fwd", "sh2signal_bwd"};
   static const KernelOp kops[] = {kOpS2shFwd, kOpS2shBwd, kOpSh2sFwd, kOpSh2sBwd};
+  // whole rows, every shell in one launch, unless the table is too long for it
+  // (512 volumes, 24 units of 16 columns, 16 shells, 128 directions a shell)
+  ShellRows rows = shell_rows(p, op, V);
+  if (shell_rows_ok(rows)) {
+    rows.in = in;
+    rows.out = out;
+    const double SK = double(S) * K;
+    double flops = 0;
+    for (int s = 0; s < S; ++s) flops += 2.0 * double(V) * double(p->dirs[s]) * K;
+    TimedScope ts(tags[int(op)], stream, double(V) * (double(ndw) + SK) * 4.0, flops);
+    const dlm_status st = launched(launch_shell_rows(rows, prec, stream));
+    return st == DLM_OK ? ok() : st;
+  }
   const int shells = p->uniform ? 1 : S;
   for (int s0 = 0; s0 < shells; ++s0) {
     const int64_t N = p->dirs[s0];
@@ -588,6 +630,19 @@ dlm_status dlm_signal2sh_fwd_raw(const dlm_sh_plan *p, const float *raw, float *
   if (ws_bytes < dlm_signal2sh_raw_workspace_bytes(V)) return fail(DLM_EWORKSPACE, "workspace too small");
   float *inv = static_cast<float *>(ws);
   const int K = p->K, S = p->S;
+  ShellRows rows = shell_rows(p, ShOp::S2shFwd, V);
+  rows.raw_n = p->n_total <= (1 << 20) ? int(p->n_total) : 0;
+  if (rows.raw_n && shell_rows_ok(rows)) {
+    rows.in = raw;
+    rows.out = c;
+    rows.dw = p->d_dwidx;
+    rows.b0 = p->d_b0idx;
+    rows.n_b0 = p->n_b0;
+    TimedScope ts("signal2sh_fwd_raw", stream, double(V) * (double(p->n_total) + double(S) * K) * 4.0,
+                  2.0 * double(V) * double(p->n_dw) * K);
+    const dlm_status st = launched(launch_shell_rows(rows, prec, stream));
+    return st == DLM_OK ? ok() : st;
+  }
   {
     TimedScope ts("b0_inverse_mean", stream, double(V) * (p->n_b0 + 1) * 4.0, double(V) * p->n_b0);
     if (launch_b0_inverse_mean(raw, p->n_total, p->d_b0idx, p->n_b0, V, inv, stream) != 0)

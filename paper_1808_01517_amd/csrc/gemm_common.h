@@ -107,4 +107,17 @@ __device__ __forceinline__ unsigned bits_word(unsigned nib, int g4) {
   return s32[0] | s32[1];
 }
 
+// One DMA lane copy of SIZE bytes from global memory into LDS; the LDS
+// address of lane i is lds + i * SIZE (lds must be wave-uniform).  The
+// builtin is only legal in the gfx950 device pass (the 16-byte form is a
+// gfx950 instruction), so the host pass sees an empty body.
+template <int SIZE>
+__device__ __forceinline__ void dma_to_lds(const void *src, void *lds) {
+  static_assert(SIZE == 4 || SIZE == 16, "DMA lane size");
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (SIZE == 16) __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)(lds), 16, 0, 0);
+  else __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)(lds), 4, 0, 0);
+#endif
+}
+
 }  // namespace dlm

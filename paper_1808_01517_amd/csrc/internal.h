@@ -155,6 +155,30 @@ struct ShellImage {
 };
 int launch_shell_image(const ShellImage &x, dlm_precision prec, void *stream);
 
+// SH transform of whole voxel rows, every shell in one launch (csrc/rows.hip):
+// out[v][out_off + n] = sum_k Bt[n][k] in[v][in_off + k] for each shell, the
+// tables in fragment order (element offsets frag_f / frag_h of the two
+// bases).  Units of 16 columns are numbered through the shells (unit0).
+// raw_n > 0: in is raw [V][raw_n]; row entry k is volume dw[k] over the mean of
+// the n_b0 volumes b0[].
+constexpr int kMaxRowShells = 16;
+struct ShellRows {
+  const float *in = nullptr;
+  float *out = nullptr;
+  int64_t V = 0;
+  int n_in = 0, n_out = 0, S = 0, units = 0, max_red = 0;
+  const float *frag_f = nullptr;
+  const uint16_t *frag_h = nullptr;
+  struct Shell {
+    int in_off, out_off, nred, ncol, unit0;
+    int64_t frag_f, frag_h;
+  } sh[kMaxRowShells];
+  int raw_n = 0, n_b0 = 0, lds_rows = 0;
+  const int32_t *dw = nullptr, *b0 = nullptr;
+};
+bool shell_rows_ok(const ShellRows &x);
+int launch_shell_rows(ShellRows x, dlm_precision prec, void *stream);
+
 // Per-shell SH contraction, one wave per 16 voxels x one shell (groups
 // shells of equal size in one launch):
 //   C[v][g*c_gs + n] = sum_k A[v][g*a_gs + k] * Bt_g[n][k],  n < ncol, k < nred

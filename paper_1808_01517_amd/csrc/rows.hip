@@ -1,0 +1,263 @@
+// Signal2SH, SH2Signal (Sec. 2.2) and their adjoints on voxel rows, every
+// shell of the table in one pass; Signal2SH also from raw acquisitions.
+//
+//   out[v][out_off_s + n] = sum_k Bt_s[n][k] in[v][in_off_s + k],  s = 0 .. S-1
+//
+// The transforms are streams (15 flop per byte): what bounds them is how
+// evenly whole cache lines move.  A row is n_in floats of all shells, so 32
+// rows are one contiguous run of memory on either side.  A block copies that
+// run into LDS as it is (DMA, 16 bytes a lane), its eight waves take the
+// (shell, 16 columns) units of the tile in turn with both groups of 16 rows,
+// keep the results in registers, write them to the same LDS once the inputs
+// have been read, and the block stores them as one contiguous run.  35 KB for
+// three shells of 90 directions leaves four blocks on a compute unit to cover
+// each other's latency (four waves a block measured 5-15% slower: two or three
+// units one after another are then the longest part of a block's life); a
+// unit's table fragments come from L2.
+// 450 000 voxels, three shells of 90: BF16 order 12 267 -> 200 us (4.9 TB/s)
+// either way, FP32 SH2Signal 256 -> 220 us, FP32 Signal2SH from raw volumes
+// 377 + 130 (the means in a pass of their own) -> 280 us; 100 003 voxels of 30
+// + 60 directions, FP32 order 6, 28 -> 18.5 us, against one wave per 16 voxels
+// and shell that reads its rows and writes its results straight from
+// registers, partial lines at every shell's edge, a launch per unequal shell.
+//
+// Fragments and the order of the sums are those of the other SH kernels: BF16
+// v_mfma_f32_16x16x32_bf16, lane (q16, g4) with k = 32 s + 8 g4 .. + 7; FP32
+// v_mfma_f32_16x16x4_f32, k = 16 h + 4 g4 + e for instruction e.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "gemm_common.h"
+#include "internal.h"
+
+namespace dlm {
+namespace rows {
+
+constexpr int kRows = 32;   // voxels per block
+constexpr int kWaves = 8;   // waves per block
+constexpr int kThreads = 64 * kWaves;
+constexpr int kUnits = 3;   // units per wave, at most
+constexpr int kMaxLds = 64 * 1024;
+constexpr int kMaxRow = 512;  // entries of a row, at most (64 KB a tile)
+
+// Copy n floats (a multiple of 4 but for the last tile) between global memory
+// and LDS; ALIGNED: the global side is 16-byte aligned.
+template <bool ALIGNED>
+__device__ __forceinline__ void copy_in(float *lds, const float *src, int n) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n4 = n >> 2;
+  if constexpr (ALIGNED) {
+    for (int i = wave * 64; i < n4; i += kThreads)
+      if (i + lane < n4) dma_to_lds<16>(src + 4 * (int64_t)(i + lane), lds + 4 * i);
+  } else {
+    for (int i = threadIdx.x; i < n4; i += kThreads) *reinterpret_cast<floatx4 *>(lds + 4 * i) = ld4(src + 4 * (int64_t)i);
+  }
+  if ((int)threadIdx.x < (n & 3)) lds[4 * n4 + threadIdx.x] = src[4 * n4 + threadIdx.x];
+}
+
+__device__ __forceinline__ void copy_out(float *dst, const float *lds, int n) {
+  const int n4 = n >> 2;
+  for (int i = threadIdx.x; i < n4; i += kThreads) {
+    const floatx4 v = *reinterpret_cast<const floatx4 *>(lds + 4 * i);
+    __builtin_memcpy(dst + 4 * (int64_t)i, &v, 16);
+  }
+  if ((int)threadIdx.x < (n & 3)) dst[4 * n4 + threadIdx.x] = lds[4 * n4 + threadIdx.x];
+}
+
+// Four entries of an LDS row from k (a multiple of 4 beyond the row's shell
+// start, so at any dword), zeros at and beyond nred.
+__device__ __forceinline__ floatx4 run4(const float *row, int k, int nred) {
+  floatx4 v;
+  __builtin_memcpy(&v, row + k, 16);
+  if (k + 3 >= nred)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = k + e < nred ? v[e] : 0.0f;
+  return v;
+}
+
+// HM: 16-k groups of the longest shell (an even number in BF16).  RAW: rows of
+// x.raw_n volumes in acquisition order, divided by the mean of their b = 0
+// volumes on the way (in LDS, as one pass from the raw tile to the row tile).
+template <bool F32, bool RAW, bool ALIGNED, int HM>
+__global__ __launch_bounds__(kThreads) void sh_rows_kernel(ShellRows x) {
+  extern __shared__ __attribute__((aligned(16))) float tile[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q16 = lane & 15, g4 = lane >> 4;
+  const int64_t v0 = (int64_t)blockIdx.x * kRows;
+  const int nv = x.V - v0 < kRows ? (int)(x.V - v0) : kRows;
+  float *in = tile;
+  if constexpr (RAW) {
+    float *raw = tile, *inv = tile + x.lds_rows;
+    copy_in<ALIGNED>(raw, x.in + v0 * x.raw_n, nv * x.raw_n);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid < nv) {
+      float s = 0.0f;
+#pragma unroll 6
+      for (int i = 0; i < x.n_b0; ++i) s += raw[tid * x.raw_n + x.b0[i]];
+      inv[tid] = (float)x.n_b0 / s;
+    }
+    __syncthreads();
+    // half the block takes the even rows, half the odd ones; a thread entries
+    // k, k + kThreads / 2, .. of each, through registers: the row tile takes
+    // the raw tile's place
+    constexpr int kHalf = kThreads / 2, kCols = kMaxRow / kHalf;
+    const int k0 = tid & (kHalf - 1), odd = tid / kHalf;
+    float val[kCols][kRows / 2];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+      const int k = k0 + c * kHalf;
+      if (k >= x.n_in) break;
+      const int d = x.dw[k];
+#pragma unroll
+      for (int r = 0; r < kRows / 2; ++r) val[c][r] = raw[(2 * r + odd) * x.raw_n + d] * inv[2 * r + odd];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+      const int k = k0 + c * kHalf;
+      if (k >= x.n_in) break;
+#pragma unroll
+      for (int r = 0; r < kRows / 2; ++r) in[(2 * r + odd) * x.n_in + k] = val[c][r];
+    }
+  } else {
+    copy_in<ALIGNED>(in, x.in + v0 * x.n_in, nv * x.n_in);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  __syncthreads();
+
+  const float *r0 = in + q16 * x.n_in, *r1 = r0 + 16 * x.n_in;
+  floatx4 acc[kUnits][2];
+  int shell = 0;
+#pragma unroll
+  for (int u = 0; u < kUnits; ++u) {
+    const int unit = wave + kWaves * u;
+    if (unit < x.units) {
+      while (shell + 1 < x.S && unit >= x.sh[shell + 1].unit0) ++shell;
+      const ShellRows::Shell s = x.sh[shell];
+      const int j = unit - s.unit0;
+      acc[u][0] = acc[u][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (F32) {
+        const int H = (s.nred + 15) / 16;
+        const floatx4 *fr = reinterpret_cast<const floatx4 *>(x.frag_f + s.frag_f) + (int64_t)j * H * 64 + lane;
+        floatx4 b[HM];
+#pragma unroll
+        for (int h = 0; h < HM; ++h)
+          if (h < H) b[h] = fr[h * 64];
+#pragma unroll
+        for (int h = 0; h < HM; ++h) {
+          if (h >= H) break;
+          const int k = 16 * h + 4 * g4;
+          const floatx4 a0 = run4(r0 + s.in_off, k, s.nred), a1 = run4(r1 + s.in_off, k, s.nred);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            acc[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[h][e], a0[e], acc[u][0], 0, 0, 0);
+            acc[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[h][e], a1[e], acc[u][1], 0, 0, 0);
+          }
+        }
+      } else {
+        constexpr int SM = HM / 2;
+        const int S = (s.nred + 31) / 32;
+        const bf16x8 *fr = reinterpret_cast<const bf16x8 *>(x.frag_h + s.frag_h) + (int64_t)j * S * 64 + lane;
+        bf16x8 b[SM];
+#pragma unroll
+        for (int t = 0; t < SM; ++t)
+          if (t < S) b[t] = fr[t * 64];
+#pragma unroll
+        for (int t = 0; t < SM; ++t) {
+          if (t >= S) break;
+          const int k = 32 * t + 8 * g4;
+          bf16x8 a[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const float *r = (i ? r1 : r0) + s.in_off;
+            const floatx4 lo = run4(r, k, s.nred), hi = run4(r, k + 4, s.nred);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              a[i][e] = (__bf16)lo[e];
+              a[i][4 + e] = (__bf16)hi[e];
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i) acc[u][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[t], a[i], acc[u][i], 0, 0, 0);
+        }
+      }
+    }
+  }
+  __syncthreads();  // the inputs have been read: the tile takes the results
+  shell = 0;
+#pragma unroll
+  for (int u = 0; u < kUnits; ++u) {
+    const int unit = wave + kWaves * u;
+    if (unit < x.units) {
+      while (shell + 1 < x.S && unit >= x.sh[shell + 1].unit0) ++shell;
+      const ShellRows::Shell s = x.sh[shell];
+      const int n = 16 * (unit - s.unit0) + 4 * g4;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        float *o = tile + (q16 + 16 * i) * x.n_out + s.out_off + n;
+        if (n + 3 < s.ncol) {
+          __builtin_memcpy(o, &acc[u][i], 16);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (n + e < s.ncol) o[e] = acc[u][i][e];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  copy_out(x.out + v0 * x.n_out, tile, nv * x.n_out);
+}
+
+template <bool F32, bool RAW, bool ALIGNED, int HM>
+int run(const ShellRows &x, size_t lds, hipStream_t st) {
+  const int64_t blocks = (x.V + kRows - 1) / kRows;
+  if (blocks > 0x7fffffff) return -4;
+  hipLaunchKernelGGL((sh_rows_kernel<F32, RAW, ALIGNED, HM>), dim3((unsigned)blocks), dim3(kThreads), lds, st, x);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <bool F32, bool RAW, bool ALIGNED>
+int run_h(const ShellRows &x, size_t lds, hipStream_t st) {
+  if (x.max_red <= 32) return run<F32, RAW, ALIGNED, 2>(x, lds, st);
+  if (x.max_red <= 64) return run<F32, RAW, ALIGNED, 4>(x, lds, st);
+  if (x.max_red <= 96) return run<F32, RAW, ALIGNED, 6>(x, lds, st);
+  return run<F32, RAW, ALIGNED, 8>(x, lds, st);
+}
+
+// Floats of LDS: the tile (raw rows, inputs, then results; its last run may be
+// read up to 15 entries beyond the last row) and behind it, for RAW, the
+// voxels' inverse means.
+size_t row_floats(const ShellRows &x) {
+  return (size_t(kRows) * std::max(std::max(x.n_in, x.n_out), x.raw_n) + 128 + 3) / 4 * 4;
+}
+size_t lds_floats(const ShellRows &x) { return row_floats(x) + (x.raw_n ? kRows : 0); }
+
+}  // namespace rows
+
+// Tables with more units than four waves hold, and tiles that leave a compute
+// unit fewer than two blocks, stay on the tiled core.
+bool shell_rows_ok(const ShellRows &x) {
+  return x.S >= 1 && x.S <= kMaxRowShells && x.units <= rows::kWaves * rows::kUnits && x.max_red <= 128 && x.n_in <= rows::kMaxRow &&
+         rows::lds_floats(x) * 4 <= size_t(rows::kMaxLds);
+}
+
+int launch_shell_rows(ShellRows x, dlm_precision prec, void *stream) {
+  if (!shell_rows_ok(x)) return -3;
+  if (x.V <= 0) return 0;
+  x.lds_rows = (int)rows::row_floats(x);
+  const size_t lds = rows::lds_floats(x) * 4;
+  hipStream_t st = (hipStream_t)stream;
+  const bool al = (reinterpret_cast<uintptr_t>(x.in) & 15) == 0, f32 = prec != DLM_BF16;
+  using namespace rows;
+  if (x.raw_n) {
+    if (f32) return al ? run_h<true, true, true>(x, lds, st) : run_h<true, true, false>(x, lds, st);
+    return al ? run_h<false, true, true>(x, lds, st) : run_h<false, true, false>(x, lds, st);
+  }
+  if (f32) return al ? run_h<true, false, true>(x, lds, st) : run_h<true, false, false>(x, lds, st);
+  return al ? run_h<false, false, true>(x, lds, st) : run_h<false, false, false>(x, lds, st);
+}
+
+}  // namespace dlm

@@ -57,8 +57,6 @@ constexpr int SBK = 32;  // reduction entries per stage (one MFMA deep)
 #define DLM_ASTAT 1  // the short-reduction kernel below (0: tiled core only)
 #endif
 
-#define DLM_LDS(p) ((__attribute__((address_space(3))) void *)(p))
-
 // Source of the DMA lanes that fill padding (zero-initialised, never written).
 __device__ __attribute__((aligned(16))) float kZeros[1024];
 __device__ __forceinline__ const float *zeros_for(int s) { return kZeros + ((s & 255) << 2); }
@@ -69,19 +67,6 @@ template <int N>
 __device__ __forceinline__ void wait_barrier() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-// One DMA lane copy of SIZE bytes from global memory into LDS; the LDS
-// address of lane i is lds + i * SIZE (lds must be wave-uniform).  The
-// builtin is only legal in the gfx950 device pass (the 16-byte form is a
-// gfx950 instruction), so the host pass sees an empty body.
-template <int SIZE>
-__device__ __forceinline__ void dma_to_lds(const void *src, void *lds) {
-  static_assert(SIZE == 4 || SIZE == 16, "DMA lane size");
-#if defined(__HIP_DEVICE_COMPILE__)
-  if constexpr (SIZE == 16) __builtin_amdgcn_global_load_lds(src, DLM_LDS(lds), 16, 0, 0);
-  else __builtin_amdgcn_global_load_lds(src, DLM_LDS(lds), 4, 0, 0);
-#endif
 }
 
 __device__ __forceinline__ bf16x8 to_bf16x8(floatx4 lo, floatx4 hi) {
