@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -67,23 +68,65 @@ bool have_device() {
   return hipGetDeviceCount(&n) == hipSuccess && n > 0;
 }
 
-bool upload(DevMat &d, const std::vector<double> &h, int rows, int cols, hipStream_t st, std::vector<float> &sf,
-            std::vector<uint16_t> &sh) {
-  const size_t n = size_t(rows) * cols;
-  d.rows = rows;
-  d.cols = cols;
-  if (!d.f32 && hipMalloc(&d.f32, std::max<size_t>(n, 1) * sizeof(float)) != hipSuccess) return false;
-  if (!d.bf16 && hipMalloc(&d.bf16, std::max<size_t>(n, 1) * sizeof(uint16_t)) != hipSuccess) return false;
-  sf.resize(n);
-  sh.resize(n);
-  for (size_t i = 0; i < n; ++i) {
-    sf[i] = float(h[i]);
-    sh[i] = f64_to_bf16_rne(h[i]);
+// Tables that go to the device together: one allocation, one copy, and the
+// transposes made there (an allocation and a copy of its own for each table
+// and precision, and the transposes on the host, cost an LSC plan 0.4 ms).
+struct Slab {
+  struct Part {
+    DevMat *d;
+    const std::vector<double> *src;  // null: the transpose of `of`'s `batch` matrices
+    const DevMat *of;
+    int batch, r, c;  // r x c the slices before
+    size_t f, h;
+    bool bf16;
+  };
+  std::vector<Part> parts;
+  size_t bytes = 0, copied = 0;
+  void place(DevMat &d, const std::vector<double> *src, const DevMat *of, int batch, int r, int c, bool bf16) {
+    const size_t n = size_t(d.rows) * d.cols;
+    parts.push_back(Part{&d, src, of, batch, r, c, bytes, bytes + align256(n * 4), bf16});
+    bytes += align256(n * 4) + (bf16 ? align256(n * 2) : 0);
   }
-  if (hipMemcpyAsync(d.f32, sf.data(), n * sizeof(float), hipMemcpyHostToDevice, st) != hipSuccess) return false;
-  if (hipMemcpyAsync(d.bf16, sh.data(), n * sizeof(uint16_t), hipMemcpyHostToDevice, st) != hipSuccess) return false;
-  return true;
-}
+  void add(DevMat &d, const std::vector<double> &src, int rows, int cols, bool bf16 = true) {
+    d.rows = rows;
+    d.cols = cols;
+    place(d, &src, nullptr, 1, 0, 0, bf16);
+    copied = bytes;
+  }
+  // after every add(): `of` as `batch` matrices of r x c, each transposed
+  void add_transposed(DevMat &d, const DevMat &of, int batch, int r, int c, bool bf16 = true) {
+    d.rows = batch * c;
+    d.cols = r;
+    place(d, nullptr, &of, batch, r, c, bf16);
+  }
+  // the device copy, or null; the tables' pointers point into it
+  void *upload() {
+    std::unique_ptr<char[]> host(new (std::nothrow) char[copied]);
+    char *dev = nullptr;
+    if (!host || hipMalloc(&dev, bytes) != hipSuccess) return nullptr;
+    for (const Part &p : parts) {
+      p.d->f32 = reinterpret_cast<float *>(dev + p.f);
+      if (p.bf16) p.d->bf16 = reinterpret_cast<uint16_t *>(dev + p.h);
+      if (!p.src) continue;
+      const size_t n = size_t(p.d->rows) * p.d->cols;
+      float *f = reinterpret_cast<float *>(host.get() + p.f);
+      for (size_t i = 0; i < n; ++i) f[i] = float((*p.src)[i]);
+      uint16_t *h = reinterpret_cast<uint16_t *>(host.get() + p.h);
+      if (p.bf16)
+        for (size_t i = 0; i < n; ++i) h[i] = f64_to_bf16_rne((*p.src)[i]);
+    }
+    bool good = hipMemcpyAsync(dev, host.get(), copied, hipMemcpyHostToDevice, nullptr) == hipSuccess;
+    for (const Part &p : parts) {
+      if (p.src || !good) continue;
+      good = launch_transpose(p.of->f32, p.d->f32, p.batch, p.r, p.c, 4, nullptr) == 0 &&
+             (!p.bf16 || launch_transpose(p.of->bf16, p.d->bf16, p.batch, p.r, p.c, 2, nullptr) == 0);
+    }
+    good = hipStreamSynchronize(nullptr) == hipSuccess && good;
+    if (good) return dev;
+    (void)hipFree(dev);
+    return nullptr;
+  }
+};
 
 void release(DevMat &d) {
   if (d.f32) (void)hipFree(d.f32);
@@ -150,6 +193,7 @@ struct dlm_lsc_plan {
   std::vector<double> g, points, Bnb, Pm;
   std::vector<double> Q, pm1;  // Q[t][k][j] = (P_m B_t)[k][j]; pm1 = P_m 1
   DevMat dBnb, dBnbT, dPm, dPmT, dQ, dQT, dpm1;  // dQT: [T][K_in][K_out]
+  void *slab = nullptr;                          // the device memory of all of them
 };
 
 namespace {
@@ -806,24 +850,16 @@ dlm_status dlm_lsc_plan_create(const double *sampled_gradients, int64_t m, int s
   p->pm1.assign(Ko, 0.0);
   for (int k = 0; k < Ko; ++k)
     for (int64_t i = 0; i < m; ++i) p->pm1[k] += p->Pm[size_t(k) * m + i];
-  std::vector<float> sf;
-  std::vector<uint16_t> shh;
-  bool good = upload(p->dQ, p->Q, T, Ko * Ki, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
-  {
-    std::vector<double> qt(p->Q.size());
-    for (int t = 0; t < T; ++t)
-      for (int k = 0; k < Ko; ++k)
-        for (int j = 0; j < Ki; ++j) qt[(size_t(t) * Ki + j) * Ko + k] = p->Q[(size_t(t) * Ko + k) * Ki + j];
-    good = good && upload(p->dQT, qt, T, Ko * Ki, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
-  }
-  good = good && upload(p->dpm1, p->pm1, 1, Ko, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
-  good = good && upload(p->dBnb, p->Bnb, int(P), p->K_in, nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
-  good = good && upload(p->dBnbT, transpose(p->Bnb, int(P), p->K_in), p->K_in, int(P), nullptr, sf, shh) &&
-         hipStreamSynchronize(nullptr) == hipSuccess;
-  good = good && upload(p->dPm, p->Pm, p->K_out, int(m), nullptr, sf, shh) && hipStreamSynchronize(nullptr) == hipSuccess;
-  good = good && upload(p->dPmT, transpose(p->Pm, p->K_out, int(m)), int(m), p->K_out, nullptr, sf, shh) &&
-         hipStreamSynchronize(nullptr) == hipSuccess;
-  if (!good) {
+  Slab slab;  // the folded tables are read as float32 only
+  slab.add(p->dQ, p->Q, T, Ko * Ki, false);
+  slab.add(p->dpm1, p->pm1, 1, Ko, false);
+  slab.add(p->dBnb, p->Bnb, int(P), Ki);
+  slab.add(p->dPm, p->Pm, Ko, int(m));
+  slab.add_transposed(p->dQT, p->dQ, T, Ko, Ki, false);
+  slab.add_transposed(p->dBnbT, p->dBnb, 1, int(P), Ki);
+  slab.add_transposed(p->dPmT, p->dPm, 1, Ko, int(m));
+  p->slab = slab.upload();
+  if (!p->slab) {
     dlm_lsc_plan_destroy(p);
     return fail(DLM_EDEVICE, "table upload failed: %s", hipGetErrorString(hipGetLastError()));
   }
@@ -850,13 +886,7 @@ dlm_status dlm_lsc_plan_tables(const dlm_lsc_plan *p, double *points, double *B_
 
 void dlm_lsc_plan_destroy(dlm_lsc_plan *p) {
   if (!p) return;
-  release(p->dBnb);
-  release(p->dBnbT);
-  release(p->dPm);
-  release(p->dPmT);
-  release(p->dQ);
-  release(p->dQT);
-  release(p->dpm1);
+  if (p->slab) (void)hipFree(p->slab);
   delete p;
 }
 
@@ -898,6 +928,16 @@ LscWs lsc_ws_carve(const dlm_lsc_plan *p, int C, int O, int64_t Vc, void *ws) {
   b += align256(size_t(Vc) * O * p->m * 4);
   w.part = reinterpret_cast<float *>(b);
   return w;
+}
+
+// Resample form: whether the channels are mixed before the resampling
+// (kernels.hip), by the multiplications per voxel of either order; Z then has
+// to fit where the neighbourhood matrices would be.  32 -> 3 channels at order
+// 8, 4096 voxels, forward and backward: 1794 us in the paper's order, 184 us in
+// the other.  BF16 keeps the paper's order, whose intermediate it rounds.
+bool lsc_mix_first(const dlm_lsc_plan *p, int C, int O, dlm_precision prec) {
+  const double K = p->K_in, m = double(p->m), T = p->T, CTO = double(C) * T * O;
+  return prec == DLM_FP32 && K <= m && C * m >= O * K && K * CTO + O * m * T * K < C * K * m * T + m * CTO;
 }
 
 // Largest chunk (multiple of kMinChunk unless V is smaller) whose workspace fits.
@@ -1365,13 +1405,25 @@ dlm_status dlm_lsc_fwd(const dlm_lsc_plan *p, const float *a_in, int C, const fl
   const int T = p->T, m = int(p->m);
   const int64_t P = p->m * T;
   const double CTO = double(C) * T * O;
+  const bool mix = lsc_mix_first(p, C, O, prec);
+  const int K = p->K_in;
   {
     TimedScope ts("lsc_prepare_weights", stream, CTO * 12.0, 0.0);
-    if ((s = launched(launch_prepare_weights(W, w.Wt, w.Wh, w.Wth, C, O, T, stream))) != DLM_OK) return s;
+    if ((s = launched(mix ? launch_mix_weights(W, w.Wt, reinterpret_cast<float *>(w.Wh), C, O, T, stream)
+                          : launch_prepare_weights(W, w.Wt, w.Wh, w.Wth, C, O, T, stream))) != DLM_OK)
+      return s;
   }
   for (int64_t v0 = 0; v0 < V; v0 += Vc) {
     const int64_t nv = std::min(Vc, V - v0);
     const double dnv = double(nv);
+    if (mix) {
+      {
+        TimedScope ts("lsc_contract_fwd", stream, dnv * K * (C + double(O) * T) * 4.0, 2.0 * dnv * K * CTO);
+        if ((s = launched(launch_mix_fwd(a_in + v0 * C * K, w.Wt, w.X, nv, C, O * T, K, stream))) != DLM_OK) return s;
+      }
+      TimedScope ts("lsc_resample", stream, dnv * O * (double(T) * K + m) * 4.0, 2.0 * dnv * O * K * double(P));
+      if ((s = launched(launch_mix_points(w.X, p->dBnb.f32, bias, w.y, nv, O, m, T * K, stream))) != DLM_OK) return s;
+    }
     TableGemm rs;  // resampling: X[(v,c)][p] = sum_j B_nb[p][j] a[(v,c)][j]
     rs.A = a_in + v0 * C * p->K_in;
     rs.lda = p->K_in;
@@ -1383,11 +1435,11 @@ dlm_status dlm_lsc_fwd(const dlm_lsc_plan *p, const float *a_in, int C, const fl
     rs.N = int(P);
     rs.K = p->K_in;
     rs.op = kOpResample;
-    {
+    if (!mix) {
       TimedScope ts("lsc_resample", stream, dnv * C * (p->K_in + double(P)) * 4.0, 2.0 * dnv * C * p->K_in * double(P));
       if ((s = launched(launch_table_gemm(rs, prec, stream))) != DLM_OK) return s;
     }
-    {
+    if (!mix) {
       TimedScope ts("lsc_contract_fwd", stream, dnv * (C * double(P) + double(O) * m) * 4.0, 2.0 * dnv * m * CTO);
       if ((s = launched(launch_lsc_contract_fwd(w.X, W, w.Wh, bias, w.y, nv, C, O, m, T, prec, stream))) != DLM_OK)
         return s;
@@ -1448,9 +1500,14 @@ dlm_status dlm_lsc_bwd(const dlm_lsc_plan *p, const float *a_in, int C, const fl
                 lsc_ws_need(p, C, O, std::min<int64_t>(V, kMinChunk)));
   LscWs w = lsc_ws_carve(p, C, O, Vc, ws);
   const double CTO = double(C) * T * O;
+  const bool mix = lsc_mix_first(p, C, O, prec);
+  const int K = p->K_in;
+  float *Wc = reinterpret_cast<float *>(w.Wh);  // 4 bytes an entry, over both bfloat16 copies
   {
     TimedScope ts("lsc_prepare_weights", stream, CTO * 12.0, 0.0);
-    if ((s = launched(launch_prepare_weights(W, w.Wt, w.Wh, w.Wth, C, O, T, stream))) != DLM_OK) return s;
+    if ((s = launched(mix ? launch_mix_weights(W, w.Wt, Wc, C, O, T, stream)
+                          : launch_prepare_weights(W, w.Wt, w.Wh, w.Wth, C, O, T, stream))) != DLM_OK)
+      return s;
   }
   for (int64_t v0 = 0; v0 < V; v0 += Vc) {
     const int64_t nv = std::min(Vc, V - v0);
@@ -1471,6 +1528,31 @@ dlm_status dlm_lsc_bwd(const dlm_lsc_plan *p, const float *a_in, int C, const fl
       TimedScope ts("lsc_refit_bwd", stream, dnv * O * (p->K_out * (rb.mask ? 2.0 : 1.0) + m) * 4.0,
                     2.0 * dnv * O * m * p->K_out);
       if ((s = launched(launch_table_gemm(rb, prec, stream))) != DLM_OK) return s;
+    }
+    if (mix) {
+      const float *a = a_in + v0 * C * K;
+      {
+        TimedScope ts("lsc_resample_bwd", stream, dnv * O * (m + double(T) * K) * 4.0, 2.0 * dnv * O * K * double(P));
+        if ((s = launched(launch_mix_points_bwd(w.y, p->dBnb.f32, w.X, nv * O, m, T * K, stream))) != DLM_OK) return s;
+      }
+      if (dW) {
+        const int splits = lsc_weight_splits(nv, K, kWeightSplitTarget);
+        {
+          TimedScope ts("lsc_bwd_weight", stream, dnv * K * (C + double(O) * T) * 4.0, 2.0 * dnv * K * CTO);
+          if ((s = launched(launch_mix_bwd_weight(w.X, a, w.part, nv, C, O * T, K, splits, stream))) != DLM_OK) return s;
+        }
+        TimedScope ts("lsc_reduce_weight", stream, (CTO + O) * 4.0, double(splits) * CTO);
+        if ((s = launched(launch_mix_reduce(w.part, splits, w.y, nv, m, w.part + size_t(kWeightSplitTarget) * C * T * O,
+                                            dW, dbias, C, O, T, v0 > 0, stream))) != DLM_OK)
+          return s;
+      }
+      if (da_in) {
+        TimedScope ts("lsc_bwd_data", stream, dnv * K * (C + double(O) * T) * 4.0, 2.0 * dnv * K * CTO);
+        if ((s = launched(launch_mix_bwd_data(w.X, Wc, (relu_flags & DLM_RELU_IN) ? a : nullptr, da_in + v0 * C * K, nv,
+                                              C, O * T, K, stream))) != DLM_OK)
+          return s;
+      }
+      continue;
     }
     if (dW) {
       TableGemm rs;  // recompute the neighbourhood matrices X

@@ -234,7 +234,29 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float *part, in
   out[i] = s;
 }
 
+// Tables are transposed once, when a plan is made: one entry per thread.
+template <class T>
+__global__ __launch_bounds__(256) void transpose_kernel(const T *src, T *dst, int64_t n, int rows, int cols) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int64_t slice = (int64_t)rows * cols, b = i / slice, e = i - b * slice, c = e / rows, r = e - c * rows;
+  dst[i] = src[b * slice + r * cols + c];
+}
+
 }  // namespace fold
+
+int launch_transpose(const void *src, void *dst, int batch, int rows, int cols, int size, void *stream) {
+  const int64_t n = (int64_t)batch * rows * cols, blocks = (n + 255) / 256;
+  if (n <= 0 || blocks > 0x7fffffff) return -4;
+  hipStream_t st = (hipStream_t)stream;
+  if (size == 4)
+    hipLaunchKernelGGL(fold::transpose_kernel<uint32_t>, dim3((unsigned)blocks), dim3(256), 0, st,
+                       static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst), n, rows, cols);
+  else
+    hipLaunchKernelGGL(fold::transpose_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0, st,
+                       static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst), n, rows, cols);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
 
 int launch_lsc_fold(const FoldOut &f, void *stream) {
   const int KK = f.Ko * f.Ki, pairs = f.C * f.O;

@@ -257,6 +257,25 @@ int launch_reduce_weight_partials(const float *partial, int splits, float *dW, f
 // Wt[(c*T+t)][o] = W[o][c][t] (+ bf16 copies of W and Wt when requested)
 int launch_prepare_weights(const float *W, float *Wt, uint16_t *Wh, uint16_t *Wth, int C, int O, int T,
                            void *stream);
+// The same layer with the channels mixed before the resampling (FP32):
+// Wot[(o*T+t)*C + c] and Wc[(c*O+o)*T + t] = W[o][c][t];
+// Z[v][(o,t)][j] = sum_c W[o][c][t] a[v][c][j]
+// y[v][o][i] = bias[o] + sum_(t,j) Bnb[i*T+t][j] Z[v][(o,t)][j]
+// U[r][(t,j)] = sum_i Bnb[i*T+t][j] dy[r][i], r = (v, o) < M
+// da[v][c][j] = sum_(o,t) W[o][c][t] U[v][(o,t)][j], zero where mask <= 0
+// partial[s][(o,t)][c] = sum over split s of (v, j) of U[v][(o,t)][j] a[v][c][j]
+// dW[o][c][t] (+)= sum_s partial[s][(o,t)][c]; db[o] (+)= sum_(v,i) dy[v][o][i] (bpart: 256 O floats)
+int launch_mix_weights(const float *W, float *Wot, float *Wc, int C, int O, int T, void *stream);
+int launch_mix_fwd(const float *a, const float *Wot, float *Z, int64_t V, int C, int OT, int K, void *stream);
+int launch_mix_points(const float *Z, const float *Bnb, const float *bias, float *y, int64_t V, int O, int m, int TK,
+                      void *stream);
+int launch_mix_points_bwd(const float *dy, const float *Bnb, float *U, int64_t M, int m, int TK, void *stream);
+int launch_mix_bwd_data(const float *U, const float *Wc, const float *mask, float *da, int64_t V, int C, int OT, int K,
+                        void *stream);
+int launch_mix_bwd_weight(const float *U, const float *a, float *partial, int64_t V, int C, int OT, int K, int splits,
+                          void *stream);
+int launch_mix_reduce(const float *part, int splits, const float *dy, int64_t V, int m, float *bpart, float *dW,
+                      float *db, int C, int O, int T, int accumulate, void *stream);
 int launch_mse(const float *pred, const float *target, int64_t n, float *loss, float *dpred, float *partials,
                int nblocks, void *stream);
 // relative form: errors weighted by 1 / (|target| + eps)
@@ -298,6 +317,9 @@ int launch_sum_partials(const float *part, int splits, int64_t n, float *out, vo
 // dW[(o*C+c)][t] = sum_{k,j} dT[(o*Ko+k)][c*Ki+j] Q[t][k][j];  db[o] = sum_k dT[(o*Ko+k)][C*Ki] pm1[k]
 int launch_lsc_unfold(const float *part, int splits, const float *Q, const float *pm1, int C, int O, int T, int Ki,
                       int Ko, float *dW, float *db, void *stream);
+
+// dst[b][c][r] = src[b][r][c] for `batch` matrices of rows x cols, 2- or 4-byte entries
+int launch_transpose(const void *src, void *dst, int batch, int rows, int cols, int size, void *stream);
 
 // ----------------------------------------------------------- status text
 // Set the thread's dlm_last_error() text and return s (for library sources

@@ -773,6 +773,193 @@ int lsc_weight_splits(int64_t V, int m, int target) {
   return s < 1 ? 1 : s;
 }
 
+// ------------------------------- LSC, channels mixed before the resampling
+// The resampling acts on the coefficient index and the kernel on the channel
+// and tap indices, so the paper's first two steps commute:
+//   Z[v][(o,t)][j] = sum_c W[o][c][t] a[v][c][j]
+//   y[v][o][i]     = bias[o] + sum_(t,j) B_nb[i T + t][j] Z[v][(o,t)][j]
+// and, with U[v][(o,t)][j] = sum_i B_nb[i T + t][j] dy[v][o][i], backward
+//   dW[o][c][t] = sum_(v,j) a[v][c][j] U[v][(o,t)][j]
+//   da[v][c][j] = sum_(o,t) W[o][c][t] U[v][(o,t)][j].
+// For layers with fewer outputs than inputs Z is much smaller than the
+// neighbourhood matrices (32 -> 3 channels, 90 directions, 17 taps: 2295
+// entries a voxel instead of 48960) and the products far fewer (280k instead
+// of 2.35M a voxel forward).  B_nb [m T][K] read as [m][T K] is the table of
+// both y and U.
+
+// Columns n of rows (v, j), m rows per voxel: out[(v N + n) m + j], zeroed
+// where mask (indexed as out) is not positive.
+struct CVoxelCols {
+  float *out;
+  const float *mask;
+  int m, N;
+  FastDiv fm;
+  __device__ void operator()(int64_t r, int n, int, float v) const {
+    const int vx = fm.div((int)r), j = (int)r - vx * m;
+    const int64_t o = ((int64_t)vx * N + n) * m + j;
+    out[o] = mask && !(mask[o] > 0.0f) ? 0.0f : v;
+  }
+  __device__ void store4(int64_t r, int n, int g, floatx4 v) const {
+    for (int q = 0; q < 4; ++q) (*this)(r, n + q, g, v[q]);
+  }
+};
+
+// Row (v, o) of y: the output channel's bias on every column.
+struct CRowBias {
+  float *y;
+  const float *bias;
+  int m, O;
+  FastDiv fO;
+  __device__ float b(int64_t r) const { return bias ? bias[(int)r - fO.div((int)r) * O] : 0.0f; }
+  __device__ void operator()(int64_t r, int n, int, float v) const { y[r * m + n] = v + b(r); }
+  __device__ void store4(int64_t r, int n, int, floatx4 v) const {
+    const float c = b(r);
+    for (int q = 0; q < 4; ++q) v[q] += c;
+    st4(y + r * m + n, v);
+  }
+};
+
+// Element (n, k) of a row-contiguous table at B[k ld + n].
+struct BTableT {
+  static constexpr bool kContig = false;
+  static constexpr bool kMask = false;
+  using type = float;
+  const float *B;
+  int ld;
+  __device__ float operator()(int n, int k, int) const { return B[(int64_t)k * ld + n]; }
+  __device__ floatx4 load4(int n, int k, int) const { return ld4(B + (int64_t)k * ld + n); }
+};
+
+// Row r over the reduction k = (v, j): p[(v N + r) m + j].
+struct AVoxelRows {
+  static constexpr bool kContig = true;
+  static constexpr bool kMask = false;
+  const float *p;
+  int m, N;
+  FastDiv fm;
+  __device__ float operator()(int64_t r, int k, int) const {
+    const int v = fm.div(k), j = k - v * m;
+    return p[((int64_t)v * N + r) * m + j];
+  }
+  __device__ floatx4 load4(int64_t r, int k, int g) const {
+    const int v = fm.div(k), j = k - v * m;
+    if (j + 3 < m) return ld4(p + ((int64_t)v * N + r) * m + j);
+    return floatx4{(*this)(r, k, g), (*this)(r, k + 1, g), (*this)(r, k + 2, g), (*this)(r, k + 3, g)};
+  }
+};
+
+__global__ void mix_weights_kernel(const float *W, float *Wot, float *Wc, int C, int O, int T) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= O * C * T) return;
+  const int o = idx / (C * T), ct = idx - o * C * T, c = ct / T, t = ct - c * T;
+  const float w = W[idx];
+  Wot[((int64_t)o * T + t) * C + c] = w;
+  Wc[((int64_t)c * O + o) * T + t] = w;
+}
+
+int launch_mix_weights(const float *W, float *Wot, float *Wc, int C, int O, int T, void *stream) {
+  const int n = O * C * T;
+  hipLaunchKernelGGL(mix_weights_kernel, dim3((n + 255) / 256), dim3(256), 0, (hipStream_t)stream, W, Wot, Wc, C, O, T);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_mix_fwd(const float *a, const float *Wot, float *Z, int64_t V, int C, int OT, int K, void *stream) {
+  const int64_t M = V * K;
+  if (M >= (int64_t(1) << 31)) return -4;
+  return run_gemm_p<kOpContractFwd, false>(ADy{a, K, C, FastDiv::make(K)}, BWeightF{Wot, C},
+                                           CVoxelCols{Z, nullptr, K, OT, FastDiv::make(K)}, M, OT, C, 1, 0,
+                                           (hipStream_t)stream, pick_shape(OT));
+}
+
+int launch_mix_points(const float *Z, const float *Bnb, const float *bias, float *y, int64_t V, int O, int m, int TK,
+                      void *stream) {
+  const int64_t M = V * O;
+  if (M >= (int64_t(1) << 31)) return -4;
+  return run_gemm_p<kOpResample, false>(ARowMajor{Z, nullptr, TK, 0}, BTableF{Bnb, 0, TK},
+                                        CRowBias{y, bias, m, O, FastDiv::make(O)}, M, m, TK, 1, 0, (hipStream_t)stream,
+                                        pick_shape(m));
+}
+
+int launch_mix_points_bwd(const float *dy, const float *Bnb, float *U, int64_t M, int m, int TK, void *stream) {
+  return run_gemm_p<kOpResampleBwd, false>(ARowMajor{dy, nullptr, m, 0}, BTableT{Bnb, TK},
+                                           CRowMajor{U, TK, 0, 0, nullptr}, M, TK, m, 1, 0, (hipStream_t)stream,
+                                           pick_shape(TK));
+}
+
+int launch_mix_bwd_data(const float *U, const float *Wc, const float *mask, float *da, int64_t V, int C, int OT, int K,
+                        void *stream) {
+  const int64_t M = V * K;
+  if (M >= (int64_t(1) << 31)) return -4;
+  return run_gemm_p<kOpContractBwdData, false>(ADy{U, K, OT, FastDiv::make(K)}, BWeightF{Wc, OT},
+                                               CVoxelCols{da, mask, K, C, FastDiv::make(K)}, M, C, OT, 1, 0,
+                                               (hipStream_t)stream, pick_shape(C));
+}
+
+int launch_mix_bwd_weight(const float *U, const float *a, float *partial, int64_t V, int C, int OT, int K, int splits,
+                          void *stream) {
+  const int64_t Kfull = V * K;
+  if (Kfull >= (int64_t(1) << 31)) return -4;
+  int ksplit = (int)((Kfull + splits - 1) / splits);
+  ksplit = (ksplit + 31) / 32 * 32;
+  if ((Kfull + ksplit - 1) / ksplit != splits) return -2;
+  return run_gemm_p<kOpContractBwdWeight, false>(AVoxelRows{U, K, OT, FastDiv::make(K)}, BDyT{a, K, C, FastDiv::make(K)},
+                                                 CPartial{partial, OT, C}, OT, C, (int)Kfull, splits, ksplit,
+                                                 (hipStream_t)stream, pick_shape(C));
+}
+
+// part[b][o] = sum of dy[(v, o)][i] over the block's voxels
+__global__ __launch_bounds__(256) void bias_sums_kernel(const float *dy, int64_t V, int O, int m, int64_t per,
+                                                        float *part) {
+  __shared__ float red[4];
+  const int o = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t v0 = blockIdx.x * per, v1 = v0 + per < V ? v0 + per : V;
+  float s = 0.0f;
+  for (int64_t v = v0 + wave; v < v1; v += 4)
+    for (int i = lane; i < m; i += 64) s += dy[(v * O + o) * m + i];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) part[(int64_t)blockIdx.x * O + o] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// dW[o][c][t] (+)= sum_s part[s][(o T + t)][c];  db[o] (+)= sum_s bpart[s][o]: one wave per output
+__global__ __launch_bounds__(256) void mix_reduce_kernel(const float *part, int splits, const float *bpart, int nb,
+                                                         float *dW, float *db, int C, int O, int T, int accumulate) {
+  const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, n = O * T * C;
+  if (w >= n + (db ? O : 0)) return;
+  const bool bias = w >= n;
+  const float *src = bias ? bpart + (w - n) : part + w;
+  const int stride = bias ? O : n, count = bias ? nb : splits;
+  float s = 0.0f;
+  for (int i = lane; i < count; i += 64) s += src[(int64_t)i * stride];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane != 0) return;
+  float *dst;
+  if (bias) {
+    dst = db + (w - n);
+  } else {
+    const int ot = w / C, c = w - ot * C, o = ot / T, t = ot - o * T;
+    dst = dW + ((int64_t)o * C + c) * T + t;
+  }
+  *dst = accumulate ? *dst + s : s;
+}
+
+int launch_mix_reduce(const float *part, int splits, const float *dy, int64_t V, int m, float *bpart, float *dW,
+                      float *db, int C, int O, int T, int accumulate, void *stream) {
+  hipStream_t st = (hipStream_t)stream;
+  int nb = 0;
+  if (db) {
+    const int64_t per = (V + 255) / 256;
+    nb = (int)((V + per - 1) / per);
+    hipLaunchKernelGGL(bias_sums_kernel, dim3(nb, O), dim3(256), 0, st, dy, V, O, m, per, bpart);
+    if (hipGetLastError() != hipSuccess) return -1;
+  }
+  const int outs = O * T * C + (db ? O : 0);
+  hipLaunchKernelGGL(mix_reduce_kernel, dim3((outs + 3) / 4), dim3(256), 0, st, part, splits, bpart, nb, dW, db, C, O, T,
+                     accumulate);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 // --------------------------------------------------------- small kernels
 __global__ void reduce_weight_partials_kernel(const float *part, int splits, float *dW, float *db, int C, int O,
                                               int T, int accumulate) {

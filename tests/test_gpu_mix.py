@@ -1,0 +1,59 @@
+"""The resample form with the channels mixed before the resampling (FP32
+layers for which that order takes fewer multiplications): the smallest and
+ragged batches, several passes through a small workspace, equal channel
+counts, the input-gradient mask, gradients left out.  Held to the FP64 oracle.
+"""
+import numpy as np
+import pytest
+import torch
+
+import datagen as dg
+import paper_1808_01517_amd as dl
+from oracle import lsc as olsc
+
+from parity_util import check
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def cuda(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(DEV)
+
+
+@pytest.mark.parametrize("case", [
+    (32, 3, 8, 8, (8, 8), 90, 1), (32, 3, 8, 8, (8, 8), 90, 67), (9, 1, 4, 2, (6,), 30, 33),
+    (16, 16, 4, 4, (6, 6), 60, 130), (5, 4, 2, 4, (3, 4, 5), 45, 257), (4, 3, 6, 6, (8,), 28, 50),
+])
+@pytest.mark.parametrize("relu_in", [False, True])
+def test_mixed_order_matches_oracle(case, relu_in):
+    C, O, L_in, L_out, ks, m, V = case
+    g = dg.fibonacci_hemisphere(m)
+    oplan = olsc.LSCPlan(g, L_in, L_out, ks, np.deg2rad(30), 0.006)
+    plan = dl.LSCPlan(g, L_in, L_out, ks, np.deg2rad(30), 0.006)
+    W, b = (x.astype(np.float32).astype(np.float64) for x in dg.lsc_weights(8, 0, C, O, plan.T))
+    rng = np.random.default_rng(8)
+    a = rng.standard_normal((V, C, plan.K_in)).astype(np.float32).astype(np.float64)
+    da_out = rng.standard_normal((V, O, plan.K_out)).astype(np.float32).astype(np.float64)
+    ref, z = olsc.lsc_forward(oplan, a, W, b, True)
+    da_ref, dW_ref, db_ref = olsc.lsc_backward(oplan, a, W, z, da_out, False)
+    if relu_in:
+        da_ref = da_ref * (a > 0)
+    ws = dl.Workspace(dl.lsc_workspace_bytes(plan, C, O, 64, "fp32", "resample"), DEV)  # 64 voxels a pass
+    for w in (None, ws):
+        check("out", dl.lsc_fwd(plan, cuda(a), cuda(W), cuda(b), relu=True, form="resample", workspace=w), ref, "fp32")
+        out = dl.lsc_fwd(plan, cuda(a), cuda(W), None, form="resample", workspace=w)
+        check("out without bias", out, olsc.lsc_forward(oplan, a, W, 0 * b, False)[0], "fp32")
+        da, dW, db = dl.lsc_bwd(plan, cuda(a), cuda(W), cuda(da_out), form="resample", relu_in=relu_in, workspace=w)
+        check("da", da, da_ref, "fp32")
+        check("dW", dW, dW_ref, "fp32", kind="sum")
+        check("db", db, db_ref, "fp32", kind="sum")
+        da, dW, db = dl.lsc_bwd(plan, cuda(a), cuda(W), cuda(da_out), form="resample", relu_in=relu_in, workspace=w,
+                                need_weight_grad=False, need_bias_grad=False)
+        assert dW is None and db is None
+        check("da alone", da, da_ref, "fp32")
+        da, dW, db = dl.lsc_bwd(plan, cuda(a), cuda(W), cuda(da_out), form="resample", workspace=w,
+                                need_input_grad=False, need_bias_grad=False)
+        assert da is None and db is None
+        check("dW alone", dW, dW_ref, "fp32", kind="sum")
