@@ -30,28 +30,39 @@ __all__ = [
 DEFAULT_FORM = "folded"
 
 
+# lookups, not comparisons: these run on every call
+_FORMS = {DLM_LSC_RESAMPLE: DLM_LSC_RESAMPLE, "resample": DLM_LSC_RESAMPLE,
+          DLM_LSC_FOLDED: DLM_LSC_FOLDED, "folded": DLM_LSC_FOLDED, None: DLM_LSC_FOLDED}
+_PRECISIONS = {DLM_FP32: DLM_FP32, "fp32": DLM_FP32, "f32": DLM_FP32, torch.float32: DLM_FP32, None: DLM_FP32,
+               DLM_BF16: DLM_BF16, "bf16": DLM_BF16, torch.bfloat16: DLM_BF16}
+
+
 def form_code(f) -> int:
-    if f in (DLM_LSC_RESAMPLE, "resample"):
-        return DLM_LSC_RESAMPLE
-    if f in (DLM_LSC_FOLDED, "folded", None):
-        return DLM_LSC_FOLDED
-    raise ValueError(f"unknown LSC form {f!r}")
+    try:
+        return _FORMS[f]
+    except (KeyError, TypeError):
+        raise ValueError(f"unknown LSC form {f!r}") from None
 
 
 def precision_code(p) -> int:
-    if p in (DLM_FP32, "fp32", "f32", torch.float32, None):
-        return DLM_FP32
-    if p in (DLM_BF16, "bf16", torch.bfloat16):
-        return DLM_BF16
-    raise ValueError(f"unknown precision {p!r}")
+    try:
+        return _PRECISIONS[p]
+    except (KeyError, TypeError):
+        raise ValueError(f"unknown precision {p!r}") from None
+
+
+# The raw handle of a device's current stream (a Stream object for it costs
+# 1.5 us a call, a tenth of a small fit).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+    (lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
 def _stream(t: torch.Tensor):
-    return C.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return _raw_stream(t.get_device())
 
 
 def _ptr(t):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _f32_dev(t: torch.Tensor, name: str) -> torch.Tensor:
@@ -134,6 +145,8 @@ class SHPlan:
             idx = np.zeros(nd.value, dtype=np.int64)
             check(lib().dlm_sh_plan_shell(h, s, None, None, idx.ctypes.data_as(C.POINTER(C.c_int64))))
             self.shells.append((nd.value, b.value, idx))
+        # whether any image fits the image kernels (asked on every 5-D call)
+        self.images = bool(lib().dlm_sh_image_supported(h, 1, 1))
 
     @property
     def handle(self):
@@ -185,6 +198,7 @@ class LSCPlan:
         self.T, self.K_in, self.K_out, self.m = T.value, Ki.value, Ko.value, m.value
         self.kernel_sizes = tuple(ks)
         self.sh_order_in, self.sh_order_out = int(sh_order_in), int(sh_order_out)
+        self.folded_ws = {}  # (C, O) -> workspace bytes of the folded form
 
     @property
     def handle(self):
@@ -236,8 +250,14 @@ def _default_ws(plan: LSCPlan, C_in: int, O: int, V: int, prec: int, device, for
     run in order, so they may share scratch; calls on different streams get
     their own.  Growing it frees the old buffer through torch's caching
     allocator, which reuses it only after the stream's queued work."""
-    need = lsc_workspace_bytes(plan, C_in, O, min(max(V, 1), 1 << 16), prec, form)
-    key = (str(device), torch.cuda.current_stream(device).cuda_stream)
+    if form_code(form) == DLM_LSC_FOLDED:  # the same for every V: asked once per plan and channels
+        need = plan.folded_ws.get((C_in, O))
+        if need is None:
+            need = plan.folded_ws[(C_in, O)] = lsc_workspace_bytes(plan, C_in, O, 1, prec, form)
+    else:
+        need = lsc_workspace_bytes(plan, C_in, O, min(max(V, 1), 1 << 16), prec, form)
+    index = torch.cuda.current_device() if device.index is None else device.index
+    key = (index, _raw_stream(index))
     ws = _ws_cache.get(key)
     if ws is None or ws.nbytes < need:
         ws = Workspace(need, device)
@@ -251,7 +271,9 @@ def _sh_call(fn, plan: SHPlan, inp: torch.Tensor, out_shape, out, precision):
     V = inp.shape[0]
     if out is None:
         out = torch.empty(out_shape, dtype=torch.float32, device=inp.device)
-    check(fn(plan.handle, _ptr(inp), _ptr(out), V, precision_code(precision), _stream(inp)))
+    status = fn(plan._h, inp.data_ptr(), out.data_ptr(), V, precision_code(precision), _stream(inp))
+    if status:
+        check(status)
     return out
 
 
@@ -392,7 +414,7 @@ MAX_IMAGES, MAX_IMAGE_VOXELS = 128, 1 << 24  # exclusive for the voxels
 
 def sh_image_supported(plan: SHPlan, B: int, P: int) -> bool:
     """Whether sh_image takes this plan on B images of P voxels."""
-    return bool(lib().dlm_sh_image_supported(plan.handle, B, P))
+    return plan.images and 1 <= B <= MAX_IMAGES and 1 <= P < MAX_IMAGE_VOXELS
 
 
 def sh_image(plan: SHPlan, op: int, x: torch.Tensor, precision="fp32") -> torch.Tensor:

@@ -21,7 +21,7 @@ from torch import nn
 
 from . import (DEFAULT_FORM, MAX_IMAGE_VOXELS, MAX_IMAGES, SH2SIGNAL_BWD, SH2SIGNAL_FWD, SIGNAL2SH_BWD, SIGNAL2SH_FWD,
                LSCPlan, SHPlan, form_code, lsc_bwd, lsc_bwd_image, lsc_fwd, lsc_fwd_image, sh2signal_bwd, sh2signal_fwd,
-               sh_image, sh_image_supported, signal2sh_bwd, signal2sh_fwd)
+               sh_image, signal2sh_bwd, signal2sh_fwd)
 from ._lib import DLM_LSC_FOLDED
 
 
@@ -149,7 +149,7 @@ class Signal2SH(nn.Module):
         self.precision = precision
 
     def forward(self, x):
-        if _as_image(x, self.plan.n_dw) and sh_image_supported(self.plan, x.shape[0], x.shape[2:].numel()):
+        if _as_image(x, self.plan.n_dw) and self.plan.images:
             return _SHImageFn.apply(x, self.plan, SIGNAL2SH_FWD, SIGNAL2SH_BWD, self.precision)
         v, info = _to_voxels(x, self.plan.n_dw)
         c = _Signal2SHFn.apply(v, self.plan, self.precision)
@@ -169,7 +169,7 @@ class SH2Signal(nn.Module):
 
     def forward(self, c):
         p = self.plan
-        if _as_image(c, p.n_shells * p.K) and sh_image_supported(p, c.shape[0], c.shape[2:].numel()):
+        if _as_image(c, p.n_shells * p.K) and p.images:
             return _SHImageFn.apply(c, p, SH2SIGNAL_FWD, SH2SIGNAL_BWD, self.precision)
         v, info = _to_voxels(c, p.n_shells * p.K)
         x = _SH2SignalFn.apply(v.reshape(-1, p.n_shells, p.K), p, self.precision)
