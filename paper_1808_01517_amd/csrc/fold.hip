@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm_common.h"
 #include "internal.h"
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *
       }
     return;
   }
-  __shared__ float taps[kPairs][kTaps];
+  __shared__ __attribute__((aligned(16))) float taps[kPairs][kTaps];
   static_assert(kPairs * kTaps == 256, "one tap per thread");
   const int KK = Ko * Ki, e = blockIdx.x * 256 + tid;
   const int nq = TR ? Ko : Ki, np = TR ? Ki : Ko;  // columns, rows of one pair's block
@@ -84,12 +85,14 @@ __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *
 #pragma unroll
   for (int i = 0; i < kPairs; ++i) acc[i] = 0.0f;
   for (int t0 = 0; t0 < T; t0 += kTaps) {
-    // the pairs' taps t0 .. t0 + kTaps - 1, zeros beyond T
+    // the pairs' taps t0 .. t0 + kTaps - 1 in the order of the sum (four to a
+    // 16-byte read), zeros beyond T
     __syncthreads();
     {
       const int i = tid / kTaps, t = tid - i * kTaps;
       const int x = (p0 + i) / Y, y = (p0 + i) - x * Y;
-      taps[i][t] = p0 + i < pairs && t0 + t < T ? W[((int64_t)(TR ? y : x) * C + (TR ? x : y)) * T + t0 + t] : 0.0f;
+      const int u = (t & 16) + 4 * (t & 3) + ((t >> 2) & 3);
+      taps[i][u] = p0 + i < pairs && t0 + t < T ? W[((int64_t)(TR ? y : x) * C + (TR ? x : y)) * T + t0 + t] : 0.0f;
     }
     float qv[kTaps];
 #pragma unroll
@@ -101,9 +104,11 @@ __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *
       for (int j = 0; j < 4; ++j) {
         if (t0 + h + j >= T) break;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int i = 0; i < kPairs; ++i) {
+          const floatx4 w = *reinterpret_cast<const floatx4 *>(&taps[i][h + 4 * j]);
 #pragma unroll
-          for (int i = 0; i < kPairs; ++i) acc[i] = fmaf(taps[i][h + 4 * g + j], qv[h + 4 * g + j], acc[i]);
+          for (int g = 0; g < 4; ++g) acc[i] = fmaf(w[g], qv[h + 4 * g + j], acc[i]);
+        }
       }
   }
   if (e >= KK) return;
@@ -119,14 +124,31 @@ __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *
   }
 }
 
+// Sum over the wave, in every lane, without LDS: within rows of 16 lanes by
+// data-parallel primitives, between rows by the lane swaps.
+__device__ __forceinline__ float wave_sum(float x) {
+  auto dpp = [](float v, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf,
+                                                                 0xf, false));
+  };
+  x += dpp(x, std::integral_constant<int, 0xb1>{});   // quad_perm 1 0 3 2
+  x += dpp(x, std::integral_constant<int, 0x4e>{});   // quad_perm 2 3 0 1
+  x += dpp(x, std::integral_constant<int, 0x141>{});  // row_half_mirror
+  x += dpp(x, std::integral_constant<int, 0x140>{});  // row_mirror
+  const Both s16 = swap16(__builtin_bit_cast(unsigned, x));
+  x = __builtin_bit_cast(float, s16.a) + __builtin_bit_cast(float, s16.b);
+  const Both s32 = swap32(__builtin_bit_cast(unsigned, x));
+  return __builtin_bit_cast(float, s32.a) + __builtin_bit_cast(float, s32.b);
+}
+
 // dW of PC channels c of one output channel per block: the block reads their
 // K_out x K_in gradients once (adding up the SP partial matrices as it reads),
 // keeps them in registers and runs through its taps of Q, TB at a time, which
 // the PC pairs share.  Few pairs (PC = 1) also split the taps over blocks.
 // It is bound by the latency of its loads and of the wave sums.  64 -> 64
 // channels 135 + 15 + 7 us (a wave per (o, c, t), the partial sums and the
-// bias gradient in kernels of their own) -> 41.6 us in one launch, 32 -> 64
-// with two partials 72.6 + 11 + 15 -> 28.4 us, 3 -> 32 15.5 + 15.2 -> 5.4 us.
+// bias gradient in kernels of their own) -> 33 us in one launch, 32 -> 64
+// with two partials 72.6 + 11 + 15 -> 26 us, 3 -> 32 15.5 + 15.2 -> 5.4 us.
 constexpr int kChunk = 2048;  // gradient entries held by a block at a time
 constexpr int kTapBlock = 4;  // taps per step
 
@@ -196,11 +218,10 @@ __global__ __launch_bounds__(256) void unfold_kernel(const float *part, int64_t 
 #pragma unroll
           for (int u = 0; u < TB; ++u) s[c][u] = fmaf(g[c][i], q[u][i], s[c][u]);
     }
-    for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
-      for (int c = 0; c < PC; ++c)
+    for (int c = 0; c < PC; ++c)
 #pragma unroll
-        for (int u = 0; u < TB; ++u) s[c][u] += __shfl_xor(s[c][u], off, 64);
+      for (int u = 0; u < TB; ++u) s[c][u] = wave_sum(s[c][u]);
     if (lane == 0)
 #pragma unroll
       for (int c = 0; c < PC; ++c)

@@ -96,15 +96,27 @@ struct CRowMajor {
   }
 };
 
+// A value and its neighbour's in another row of 16 lanes: both results of the
+// lane swap of x with itself (l with l ^ 16, and l with l ^ 32).
+struct Both {
+  unsigned a, b;
+};
+__device__ __forceinline__ Both swap16(unsigned x) {
+  const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return Both{s[0], s[1]};
+}
+__device__ __forceinline__ Both swap32(unsigned x) {
+  const auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return Both{s[0], s[1]};
+}
+
 // The 16-bit ReLU word of 16 consecutive elements held by four lanes (q16,
 // g4), each with the nibble of its four: two row swaps OR them together in
 // every lane.
 __device__ __forceinline__ unsigned bits_word(unsigned nib, int g4) {
-  unsigned w = nib << (4 * g4);
-  const auto s16 = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-  w = s16[0] | s16[1];
-  const auto s32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return s32[0] | s32[1];
+  const Both s16 = swap16(nib << (4 * g4));
+  const Both s32 = swap32(s16.a | s16.b);
+  return s32.a | s32.b;
 }
 
 // One DMA lane copy of SIZE bytes from global memory into LDS; the LDS

@@ -37,8 +37,9 @@
 // MFMA v_mfma_f32_16x16x32_bf16, B fragment first, so each accumulator is the
 // transposed 16 x 16 tile (a lane holds four consecutive output columns of one
 // row), the same epilogue as the register-staged cores; lane (q16, g4) holds
-// k = 8 g4 .. 8 g4 + 7.  The ring is three stages deep in BF16 (latency-bound)
-// and two in FP32 (one stage of part products outlasts a load).
+// k = 8 g4 .. 8 g4 + 7.  The ring's depth goes with the tile: two stages where a
+// stage of part products outlasts a load, up to eight where few rows leave the
+// chip idle.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -234,7 +235,7 @@ struct SCfg {
   static constexpr int NW = WM * WN;  // waves per block
   static_assert(NW == 4 || NW == 8, "waves per block");
   static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "tile shape");
-  static_assert(NS >= 2 && NS <= 4, "ring depth");
+  static_assert(NS >= 2 && NS <= 8, "ring depth");
 };
 
 // One stage (32 k) of MFMAs for a wave's TM x TN tiles.  FP32 works in part
@@ -477,9 +478,8 @@ __global__ __launch_bounds__(64 * CF::NW) void gemm_stream_kernel(AO ao, BO bo, 
   // instructions w, w + NW, ...); waits use this count, so a wave with more
   // waits for slightly more than it needs.
   constexpr int NIW = NIA / NW + NIB / NW;
-  // ring depth: two stages in FP32; in BF16 as configured while the pending
-  // count fits vmcnt (6 bits)
-  constexpr int NS = F32 ? 2 : ((CF::NS - 2) * NIW < 64 ? CF::NS : 2), D = NS - 1;
+  // ring depth as configured while the pending count fits vmcnt (6 bits)
+  constexpr int NS = (CF::NS - 2) * NIW < 64 ? CF::NS : 2, D = NS - 1;
   __shared__ __attribute__((aligned(16))) char lds[NS * SB];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -530,17 +530,10 @@ __global__ __launch_bounds__(64 * CF::NW) void gemm_stream_kernel(AO ao, BO bo, 
   for (int s = 0; s < D; ++s)
     if (s < niter) issue(s);
   auto wait_issue = [&](int it) {
-    const int after = min(D - 1, niter - 1 - it);  // stages issued after this one
-    if constexpr (D >= 3) {
-      if (after >= 2) wait_barrier<2 * NIW>();
-      else if (after == 1) wait_barrier<NIW>();
-      else wait_barrier<0>();
-    } else if constexpr (D == 2) {
-      if (after == 1) wait_barrier<NIW>();
-      else wait_barrier<0>();
-    } else {
-      wait_barrier<0>();
-    }
+    // D - 1 stages were issued after this one; near the end fewer, and by then
+    // they have had the time to arrive
+    if (it + D <= niter) wait_barrier<(D - 1) * NIW>();
+    else wait_barrier<0>();
     if (it + D < niter) issue(it + D);
   };
   // Side inputs of the epilogue go out after the wait of the second-to-last
@@ -593,11 +586,7 @@ __device__ __forceinline__ floatx4 bits_mask(const uint16_t *mbits, int64_t ldm,
 __device__ __forceinline__ void bits_store(uint16_t *obits, int64_t ldm, int64_t r, int n, unsigned nib) {
   // OR the nibbles of the four lanes of this row (lanes q16 + 16 g4): the
   // row swaps exchange lane l with l ^ 16, then with l ^ 32, in registers
-  unsigned w = nib << (n & 15);
-  const auto s16 = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-  w = s16[0] | s16[1];
-  const auto s32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  w = s32[0] | s32[1];
+  const unsigned w = bits_word(nib, (n & 15) >> 2);
   if ((n & 15) == 0) obits[r * ldm + n / 16] = (uint16_t)w;
 }
 
@@ -752,9 +741,9 @@ struct CRowSideH {
     uint32_t out[4];
     for (int q = 0; q < 2; ++q) {
       const uint32_t mine = odd ? w0[q] : w1[q];  // the half the partner stores
-      const auto x = __builtin_amdgcn_permlane16_swap(mine, mine, false, false);
+      const Both x = swap16(mine);
       // one of the two results is this lane's own value, the other the partner's
-      const uint32_t theirs = x[0] ^ x[1] ^ mine;
+      const uint32_t theirs = x.a ^ x.b ^ mine;
       if (odd) {
         out[q] = theirs;
         out[2 + q] = w1[q];
@@ -899,8 +888,8 @@ __device__ __forceinline__ void store_pair_bf16(uint16_t *C, int64_t ldc, int64_
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const uint32_t mine = odd ? w0[q] : w1[q];  // the half the partner stores
-    const auto x = __builtin_amdgcn_permlane16_swap(mine, mine, false, false);
-    const uint32_t theirs = x[0] ^ x[1] ^ mine;  // one result is this lane's own value
+    const Both x = swap16(mine);
+    const uint32_t theirs = x.a ^ x.b ^ mine;  // one result is this lane's own value
     if (odd) {
       out[q] = theirs;
       out[2 + q] = w1[q];
@@ -1223,24 +1212,71 @@ int run(const TableGemm &t, BO bo, CS cs, hipStream_t st) {
 // cost (DMA offsets, first loads, epilogue) over 1.5x the output of 128 x 96
 using SCfgNarrow = SCfg<128, 144, 4, 1, 3>;
 using SCfgSmall = SCfg<128, 48, 4, 1, 3>;   // N <= 96
-// FP32: eight waves of 32 rows, one block per CU (two stages of 60 or 51 KB);
-// the rows share a table tile three times the size of BF16's.  96 columns
-// beyond N = 144: 1440 and 2880 are 15 and 30 tiles, and 8192 rows then give
-// 480 or 960 blocks, 94% of whole rounds of the chip.  Against the float32
-// matrix instructions: 8192 x 2880 x 1440 591 -> 390 us (174 TFLOP/s, 1.05
-// PFLOP/s of part products), K = 1440 onto 135 at 1M voxels 3.30 -> 2.18 ms,
-// the K = 135 kernel below 3.82 -> 2.55 ms.
-using SCfgF144 = SCfg<256, 144, 8, 1, 2>;
-using SCfgF96 = SCfg<256, 96, 8, 1, 2>;
+// BF16, long reductions onto wide outputs without a mask to load: 64 x 96 per
+// wave reads 10 KB of LDS for 24 matrix instructions where 32 x 144 reads 11 KB
+// for 18 (8192 x 2880 x 2880 187 -> 175 us; with the mask, whose loads then do
+// not fit in registers ahead of the epilogue, 203 -> 228 us)
+using SCfgWide = SCfg<256, 96, 4, 1, 3>;
+// BF16, too few rows for a block per compute unit: small tiles, and a ring deep
+// enough that a block waits for memory once and not at every stage (8192 x 135
+// x 2880, 64 blocks: 47 -> 27 us; with a ring of four 36 us)
+using SCfgFew = SCfg<64, 48, 4, 1, 8>;
+// FP32: the tile that takes the fewest stage times for the batch at hand.  A
+// stage (32 k) of one block took, in us, with up to half of the chip's blocks
+// resident and with all of them (blocks per compute unit by LDS):
+//   256 x 144, eight waves  2.3  3.0   (one)
+//   256 x 96, eight waves   1.8  2.1   (one)
+//   64 x 144                1.1  1.85  (two)
+//   128 x 48                0.93 1.29  (two)
+//   64 x 48                 0.66 0.80  (two)
+// (1440 and 2880 inputs onto 135, 1440 and 2880 outputs, 256 to 65536 voxels,
+// e.g. 1440 onto 135: 256 voxels 109, 84, 55, 46, 33 us; 30000 voxels 112, 94,
+// 82, 97, 102; 65536 voxels 141, 205, 177, 194, 234.)  Large batches run at
+// 256 x 144: against the float32 matrix instructions 8192 x 2880 x 1440 591 ->
+// 383 us (177 TFLOP/s, 1.06 PFLOP/s of part products), K = 1440 onto 135 at 1M
+// voxels 3.30 -> 2.18 ms, the K = 135 kernel above 3.82 -> 2.55 ms.
+struct F32Tile {
+  int bm, bn, slots;  // slots: blocks of a chip of 256 compute units
+  double half, full;
+};
+inline int f32_tile(int64_t M, int N) {
+  static constexpr F32Tile kTiles[] = {
+      {256, 144, 256, 2.3, 3.0}, {256, 96, 256, 1.8, 2.1}, {64, 144, 512, 1.1, 1.85}, {128, 48, 512, 0.93, 1.29},
+      {64, 48, 512, 0.66, 0.80}};
+  int best = 0;
+  double least = 0.0;
+  for (int i = 0; i < 5; ++i) {
+    const F32Tile &c = kTiles[i];
+    const int64_t blocks = (M + c.bm - 1) / c.bm * ((N + c.bn - 1) / c.bn), rest = blocks % c.slots;
+    const double cost = double(blocks / c.slots) * c.full + (rest == 0 ? 0.0 : rest <= c.slots / 2 ? c.half : c.full);
+    if (i == 0 || cost < least) {
+      best = i;
+      least = cost;
+    }
+  }
+  return best;
+}
+
 template <int OP, bool F32, class AO, class BO, class CS>
 int stream_table_c(AO ao, BO bo, CS cs, const TableGemm &t, hipStream_t st) {
   if constexpr (astat::takes<CS>())
     if (astat::ok<F32>(t)) return astat::run<F32>(t, bo, cs, st);
-  if (t.N <= 96) return run_stream<OP, SCfgSmall, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
   if constexpr (F32) {
-    if (t.N > 144) return run_stream<OP, SCfgF96, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
-    return run_stream<OP, SCfgF144, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+    auto go = [&](auto cfg) { return run_stream<OP, decltype(cfg), F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st); };
+    switch (f32_tile(t.M, t.N)) {
+      case 0: return go(SCfg<256, 144, 8, 1, 2>{});
+      case 1: return go(SCfg<256, 96, 8, 1, 2>{});
+      case 2: return go(SCfg<64, 144, 4, 1, 2>{});
+      case 3: return go(SCfg<128, 48, 4, 1, 3>{});
+      default: return go(SCfg<64, 48, 4, 1, 4>{});
+    }
   } else {
+    if (t.N <= 96) return run_stream<OP, SCfgSmall, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+    if constexpr (!CS::kMask)
+      if (t.N > 144 && t.K > 256 && (t.M + 255) / 256 * ((t.N + 95) / 96) >= 512)
+        return run_stream<OP, SCfgWide, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+    if ((t.M + 127) / 128 * ((t.N + 143) / 144) < 128)
+      return run_stream<OP, SCfgFew, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
     return run_stream<OP, SCfgNarrow, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
   }
 }
