@@ -577,9 +577,10 @@ dlm_status sh_apply(const dlm_sh_plan *p, const float *in, float *out, int64_t V
   static const char *const tags[] = {"signal2sh_fwd", "signal2sh_bwd", "sh2signal_fwd", "sh2signal_bwd"};
   static const KernelOp kops[] = {kOpS2shFwd, kOpS2shBwd, kOpSh2sFwd, kOpSh2sBwd};
   // whole rows, every shell in one launch, unless the table is too long for it
-  // (512 volumes, 24 units of 16 columns, 16 shells, 128 directions a shell)
+  // (512 volumes, 24 units of 16 columns, 16 shells, 128 directions a shell) or
+  // the shells' own rows are the better split
   ShellRows rows = shell_rows(p, op, V);
-  if (shell_rows_ok(rows)) {
+  if (shell_rows_ok(rows) && shell_rows_pay(rows, prec)) {
     rows.in = in;
     rows.out = out;
     const double SK = double(S) * K;

@@ -173,10 +173,15 @@ struct ShellRows {
     int in_off, out_off, nred, ncol, unit0;
     int64_t frag_f, frag_h;
   } sh[kMaxRowShells];
-  int raw_n = 0, n_b0 = 0, lds_rows = 0;
+  int raw_n = 0, n_b0 = 0;
+  // set by launch_shell_rows: groups of 32 rows per block, LDS row strides, the
+  // magic numbers of their division, floats of the tile
+  int groups = 1, in_stride = 0, out_stride = 0, lds_rows = 0;
+  unsigned in_magic = 0, out_magic = 0;
   const int32_t *dw = nullptr, *b0 = nullptr;
 };
 bool shell_rows_ok(const ShellRows &x);
+bool shell_rows_pay(const ShellRows &x, dlm_precision prec);
 int launch_shell_rows(ShellRows x, dlm_precision prec, void *stream);
 
 // Per-shell SH contraction, one wave per 16 voxels x one shell (groups

@@ -14,6 +14,11 @@
 // each other's latency (four waves a block measured 5-15% slower: two or three
 // units one after another are then the longest part of a block's life); a
 // unit's table fragments come from L2.
+// Short rows are taken in several groups of 32, so that a block moves about as
+// much (30 volumes, order 2, 200 000 voxels, one group 15.3 us, six 10.5);
+// rows of a multiple of eight floats are padded by four in LDS (three shells
+// of 96, order 12, BF16, 200 000 voxels: Signal2SH 304 us with 16 rows of a
+// column in one bank, 95 padded).
 // 450 000 voxels, three shells of 90: BF16 order 12 267 -> 200 us (4.9 TB/s)
 // either way, FP32 SH2Signal 256 -> 220 us, FP32 Signal2SH from raw volumes
 // 377 + 130 (the means in a pass of their own) -> 280 us; 100 003 voxels of 30
@@ -39,30 +44,51 @@ constexpr int kWaves = 8;   // waves per block
 constexpr int kThreads = 64 * kWaves;
 constexpr int kUnits = 3;   // units per wave, at most
 constexpr int kMaxLds = 64 * 1024;
+constexpr int kGroupLds = 36 * 1024;
+constexpr int kSlots = 1024;  // blocks on the chip at a time, four per compute unit
 constexpr int kMaxRow = 512;  // entries of a row, at most (64 KB a tile)
 
-// Copy n floats (a multiple of 4 but for the last tile) between global memory
-// and LDS; ALIGNED: the global side is 16-byte aligned.
+// Copies between nv rows of n floats in global memory, one contiguous run, and
+// LDS rows of `stride` floats.  stride == n moves the run as it is; else n is a
+// multiple of 8 and the LDS rows have four floats more.  ALIGNED: the global
+// side is 16-byte aligned.
 template <bool ALIGNED>
-__device__ __forceinline__ void copy_in(float *lds, const float *src, int n) {
+__device__ __forceinline__ void copy_in(float *lds, const float *src, int nv, int n, int stride, unsigned magic) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n4 = n >> 2;
-  if constexpr (ALIGNED) {
-    for (int i = wave * 64; i < n4; i += kThreads)
-      if (i + lane < n4) dma_to_lds<16>(src + 4 * (int64_t)(i + lane), lds + 4 * i);
-  } else {
-    for (int i = threadIdx.x; i < n4; i += kThreads) *reinterpret_cast<floatx4 *>(lds + 4 * i) = ld4(src + 4 * (int64_t)i);
+  const int n4 = nv * stride >> 2, cs = stride >> 2, last = (n >> 2) - 1;
+  const bool pad = stride != n;
+  for (int i0 = wave * 64; i0 < n4; i0 += kThreads) {
+    const int i = i0 + lane;
+    int64_t from = 4 * (int64_t)i;
+    if (pad) {  // the LDS slot's row and 16-byte piece; the filler takes the last piece again
+      const int r = (int)__umulhi((unsigned)i, magic), c = i - r * cs;
+      from = (int64_t)r * n + 4 * (c < last ? c : last);
+    }
+    if (i < n4) {
+      if constexpr (ALIGNED)
+        dma_to_lds<16>(src + from, lds + 4 * i0);
+      else
+        *reinterpret_cast<floatx4 *>(lds + 4 * i) = ld4(src + from);
+    }
   }
-  if ((int)threadIdx.x < (n & 3)) lds[4 * n4 + threadIdx.x] = src[4 * n4 + threadIdx.x];
+  const int rest = nv * stride & 3;
+  if ((int)threadIdx.x < rest) lds[4 * n4 + threadIdx.x] = src[4 * n4 + threadIdx.x];
 }
 
-__device__ __forceinline__ void copy_out(float *dst, const float *lds, int n) {
-  const int n4 = n >> 2;
+__device__ __forceinline__ void copy_out(float *dst, const float *lds, int nv, int n, int stride, unsigned magic) {
+  const int n4 = nv * n >> 2, cs = n >> 2;
+  const bool pad = stride != n;
   for (int i = threadIdx.x; i < n4; i += kThreads) {
-    const floatx4 v = *reinterpret_cast<const floatx4 *>(lds + 4 * i);
+    int at = 4 * i;
+    if (pad) {
+      const int r = (int)__umulhi((unsigned)i, magic);
+      at = r * stride + 4 * (i - r * cs);
+    }
+    const floatx4 v = *reinterpret_cast<const floatx4 *>(lds + at);
     __builtin_memcpy(dst + 4 * (int64_t)i, &v, 16);
   }
-  if ((int)threadIdx.x < (n & 3)) dst[4 * n4 + threadIdx.x] = lds[4 * n4 + threadIdx.x];
+  const int rest = nv * n & 3;
+  if ((int)threadIdx.x < rest) dst[4 * n4 + threadIdx.x] = lds[4 * n4 + threadIdx.x];
 }
 
 // Four entries of an LDS row from k (a multiple of 4 beyond the row's shell
@@ -84,12 +110,18 @@ __global__ __launch_bounds__(kThreads) void sh_rows_kernel(ShellRows x) {
   extern __shared__ __attribute__((aligned(16))) float tile[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q16 = lane & 15, g4 = lane >> 4;
-  const int64_t v0 = (int64_t)blockIdx.x * kRows;
-  const int nv = x.V - v0 < kRows ? (int)(x.V - v0) : kRows;
+  const int rows = RAW ? kRows : kRows * x.groups;
+  const int64_t v0 = (int64_t)blockIdx.x * rows;
+  const int nv = x.V - v0 < rows ? (int)(x.V - v0) : rows;
+  const int units = RAW ? x.units : x.units * x.groups;
+  // BF16: the wave's first fragments are loaded along with the rows (FP32 has
+  // no registers for them: 66 and one block fewer per compute unit)
+  constexpr bool kAhead = !F32 && !RAW;
+  bf16x8 ahead[kAhead ? HM / 2 : 1];
   float *in = tile;
   if constexpr (RAW) {
     float *raw = tile, *inv = tile + x.lds_rows;
-    copy_in<ALIGNED>(raw, x.in + v0 * x.raw_n, nv * x.raw_n);
+    copy_in<ALIGNED>(raw, x.in + v0 * x.raw_n, nv, x.raw_n, x.raw_n, 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid < nv) {
@@ -119,24 +151,37 @@ __global__ __launch_bounds__(kThreads) void sh_rows_kernel(ShellRows x) {
       const int k = k0 + c * kHalf;
       if (k >= x.n_in) break;
 #pragma unroll
-      for (int r = 0; r < kRows / 2; ++r) in[(2 * r + odd) * x.n_in + k] = val[c][r];
+      for (int r = 0; r < kRows / 2; ++r) in[(2 * r + odd) * x.in_stride + k] = val[c][r];
     }
   } else {
-    copy_in<ALIGNED>(in, x.in + v0 * x.n_in, nv * x.n_in);
+    copy_in<ALIGNED>(in, x.in + v0 * x.n_in, nv, x.n_in, x.in_stride, x.in_magic);
+    if constexpr (kAhead)
+      if (wave < units) {
+        int unit = wave, shell = 0;
+        while (unit >= x.units) unit -= x.units;
+        while (shell + 1 < x.S && unit >= x.sh[shell + 1].unit0) ++shell;
+        const ShellRows::Shell s = x.sh[shell];
+        const int S = (s.nred + 31) / 32;
+        const bf16x8 *fr = reinterpret_cast<const bf16x8 *>(x.frag_h + s.frag_h) + (int64_t)(unit - s.unit0) * S * 64 + lane;
+#pragma unroll
+        for (int t = 0; t < HM / 2; ++t)
+          if (t < S) ahead[t] = fr[t * 64];
+      }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   __syncthreads();
 
-  const float *r0 = in + q16 * x.n_in, *r1 = r0 + 16 * x.n_in;
   floatx4 acc[kUnits][2];
-  int shell = 0;
 #pragma unroll
   for (int u = 0; u < kUnits; ++u) {
-    const int unit = wave + kWaves * u;
-    if (unit < x.units) {
+    int unit = wave + kWaves * u, row = q16;
+    if (unit < units) {
+      for (; unit >= x.units; unit -= x.units) row += kRows;
+      int shell = 0;
       while (shell + 1 < x.S && unit >= x.sh[shell + 1].unit0) ++shell;
       const ShellRows::Shell s = x.sh[shell];
       const int j = unit - s.unit0;
+      const float *r0 = in + row * x.in_stride, *r1 = r0 + 16 * x.in_stride;
       acc[u][0] = acc[u][1] = floatx4{0.f, 0.f, 0.f, 0.f};
       if constexpr (F32) {
         const int H = (s.nred + 15) / 16;
@@ -162,8 +207,14 @@ __global__ __launch_bounds__(kThreads) void sh_rows_kernel(ShellRows x) {
         const bf16x8 *fr = reinterpret_cast<const bf16x8 *>(x.frag_h + s.frag_h) + (int64_t)j * S * 64 + lane;
         bf16x8 b[SM];
 #pragma unroll
-        for (int t = 0; t < SM; ++t)
+        for (int t = 0; t < SM; ++t) {
+          if constexpr (kAhead)
+            if (u == 0) {
+              b[t] = ahead[t];
+              continue;
+            }
           if (t < S) b[t] = fr[t * 64];
+        }
 #pragma unroll
         for (int t = 0; t < SM; ++t) {
           if (t >= S) break;
@@ -186,17 +237,18 @@ __global__ __launch_bounds__(kThreads) void sh_rows_kernel(ShellRows x) {
     }
   }
   __syncthreads();  // the inputs have been read: the tile takes the results
-  shell = 0;
 #pragma unroll
   for (int u = 0; u < kUnits; ++u) {
-    const int unit = wave + kWaves * u;
-    if (unit < x.units) {
+    int unit = wave + kWaves * u, row = q16;
+    if (unit < units) {
+      for (; unit >= x.units; unit -= x.units) row += kRows;
+      int shell = 0;
       while (shell + 1 < x.S && unit >= x.sh[shell + 1].unit0) ++shell;
       const ShellRows::Shell s = x.sh[shell];
       const int n = 16 * (unit - s.unit0) + 4 * g4;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        float *o = tile + (q16 + 16 * i) * x.n_out + s.out_off + n;
+        float *o = tile + (row + 16 * i) * x.out_stride + s.out_off + n;
         if (n + 3 < s.ncol) {
           __builtin_memcpy(o, &acc[u][i], 16);
         } else {
@@ -208,12 +260,13 @@ __global__ __launch_bounds__(kThreads) void sh_rows_kernel(ShellRows x) {
     }
   }
   __syncthreads();
-  copy_out(x.out + v0 * x.n_out, tile, nv * x.n_out);
+  copy_out(x.out + v0 * x.n_out, tile, nv, x.n_out, x.out_stride, x.out_magic);
 }
 
 template <bool F32, bool RAW, bool ALIGNED, int HM>
 int run(const ShellRows &x, size_t lds, hipStream_t st) {
-  const int64_t blocks = (x.V + kRows - 1) / kRows;
+  const int rows = kRows * x.groups;
+  const int64_t blocks = (x.V + rows - 1) / rows;
   if (blocks > 0x7fffffff) return -4;
   hipLaunchKernelGGL((sh_rows_kernel<F32, RAW, ALIGNED, HM>), dim3((unsigned)blocks), dim3(kThreads), lds, st, x);
   return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -227,26 +280,86 @@ int run_h(const ShellRows &x, size_t lds, hipStream_t st) {
   return run<F32, RAW, ALIGNED, 8>(x, lds, st);
 }
 
+// LDS rows whose length is a multiple of eight floats are four floats longer:
+// sixteen rows read at one column then lie in all banks and not in two to
+// eight of them.
+int stride(int n) { return n % 8 == 0 ? n + 4 : n; }
+// i / d as the high word of i * magic, for i < 2^16 and 2 <= d < 2^8 (a tile
+// is at most 4096 pieces of 16 bytes)
+unsigned magic(int d) { return d < 2 ? 0u : unsigned(((uint64_t(1) << 32) + d - 1) / d); }
+
 // Floats of LDS: the tile (raw rows, inputs, then results; its last run may be
-// read up to 15 entries beyond the last row) and behind it, for RAW, the
+// read up to 31 entries beyond the last row) and behind it, for RAW, the
 // voxels' inverse means.
 size_t row_floats(const ShellRows &x) {
-  return (size_t(kRows) * std::max(std::max(x.n_in, x.n_out), x.raw_n) + 128 + 3) / 4 * 4;
+  return (size_t(kRows) * x.groups * std::max(std::max(stride(x.n_in), stride(x.n_out)), x.raw_n) + 128 + 3) / 4 * 4;
 }
 size_t lds_floats(const ShellRows &x) { return row_floats(x) + (x.raw_n ? kRows : 0); }
 
+// Groups of 32 rows per block, up to what the waves take units of and a quarter
+// of a compute unit's LDS holds: the number whose rounds of blocks over the
+// chip move the least, counting a block's fixed part as 10 KB (30 volumes,
+// order 2, 200 000 voxels: 7 rounds of 3.8 KB 15.3 us, 2 rounds of 23 KB 10.5;
+// 30 + 60 volumes, order 6, 100 003 voxels, both transforms and adjoints: 2
+// rounds of 34 KB 92 us, 2 of 23 KB 81).
+int groups(const ShellRows &x) {
+  if (x.raw_n) return 1;
+  const int64_t bytes = int64_t(4) * kRows * std::max(stride(x.n_in), stride(x.n_out));
+  const int most = int(std::min<int64_t>(kWaves * kUnits / std::max(x.units, 1), kGroupLds / bytes));
+  int best = 1;
+  int64_t least = 0;
+  for (int g = 1; g <= std::max(most, 1); ++g) {
+    const int64_t rounds = ((x.V + kRows * g - 1) / (kRows * g) + kSlots - 1) / kSlots, cost = rounds * (g * bytes + 10240);
+    if (g == 1 || cost < least) {
+      best = g;
+      least = cost;
+    }
+  }
+  return best;
+}
+
 }  // namespace rows
 
-// Tables with more units than four waves hold, and tiles that leave a compute
-// unit fewer than two blocks, stay on the tiled core.
+// Tables with more units than the waves hold, and tiles that leave a compute
+// unit fewer than two blocks, stay on the per-shell kernels.
 bool shell_rows_ok(const ShellRows &x) {
   return x.S >= 1 && x.S <= kMaxRowShells && x.units <= rows::kWaves * rows::kUnits && x.max_red <= 128 && x.n_in <= rows::kMaxRow &&
          rows::lds_floats(x) * 4 <= size_t(rows::kMaxLds);
 }
 
+// Where whole rows are the faster way.  Unequal shells: always (1.1 to 2.5
+// times; the per-shell kernels take a launch per shell).  Equal shells are one
+// launch there as well, of waves that need no barrier, and what decides is
+// whether their slices are whole 16-byte pieces on either side.  With neither,
+// rows win (three shells of 90, 200 000 voxels, order 8: BF16 Signal2SH 86 ->
+// 61 us, FP32 SH2Signal 115 -> 93; one shell only in BF16, 1.05 to 1.3 times
+// against 0.85 to 1.1 in FP32); with one or both only over many shells and
+// voxels (three shells of 96, order 12, BF16: 200 000 voxels 118 -> 95 us, 30 000
+// voxels 20.3 against 21.9; not for FP32 products that read such slices, order
+// 10 121 against 133; two shells of 45, order 6, 200 000 voxels, FP32
+// SH2Signal 28 against 33).  FP32 products of long reductions in more than two
+// units a wave outlast the copies and need later blocks to hide behind them
+// (three shells of 90, order 12, 30 000 voxels: 29.0 against 30.6 us; 200 000
+// voxels 191 -> 153).
+bool shell_rows_pay(const ShellRows &x, dlm_precision prec) {
+  constexpr int64_t kMany = 65536;
+  const bool f32 = prec != DLM_BF16;
+  for (int s = 1; s < x.S; ++s)
+    if (x.sh[s].nred != x.sh[0].nred || x.sh[s].ncol != x.sh[0].ncol) return true;
+  if (x.sh[0].nred % 4 == 0 || x.sh[0].ncol % 4 == 0)
+    return x.S > 2 && x.V >= kMany && !(f32 && x.sh[0].nred % 4 == 0);
+  if (f32 && x.V < kMany && x.units > 2 * rows::kWaves && x.max_red > 64) return false;
+  return x.S > 1 || !f32;
+}
+
 int launch_shell_rows(ShellRows x, dlm_precision prec, void *stream) {
   if (!shell_rows_ok(x)) return -3;
   if (x.V <= 0) return 0;
+  x.groups = rows::groups(x);
+  x.in_stride = rows::stride(x.n_in);
+  x.out_stride = rows::stride(x.n_out);
+  x.in_magic = rows::magic(x.in_stride / 4);
+  x.out_magic = rows::magic(x.n_out / 4);
   x.lds_rows = (int)rows::row_floats(x);
   const size_t lds = rows::lds_floats(x) * 4;
   hipStream_t st = (hipStream_t)stream;

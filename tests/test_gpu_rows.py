@@ -88,3 +88,29 @@ def test_specials_stay_in_their_voxel():
     assert torch.isnan(out[5, 0]).all() and not torch.isfinite(out[40, 0]).any() and torch.isnan(out[69, 1]).all()
     out[5, 0], out[40, 0], out[69, 1] = clean[5, 0], clean[40, 0], clean[69, 1]
     assert torch.equal(out, clean)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("table", [
+    ((30, 2), 0),              # two entries a voxel on one side
+    ((30, 18), 2),             # 48 volumes padded in LDS, 12 coefficients not
+    ((96, 64), 6),             # 160 and 56: padded on both sides
+    ((96, 96, 96), 8),         # equal shells of whole 16-byte pieces: both kernels
+    ((91,), 6), ((60,), 6),    # one shell, one side or both in 16-byte pieces
+    ((30, 31, 32), 2),
+])
+def test_strides_and_groups(table, prec):
+    # batches on either side of the second, third and fourth group of 32 voxels
+    # a block and of the voxel count that decides for equal shells
+    dirs, L = table
+    plan, _, _ = _plan(dirs, L)
+    mats = [tuple(torch.from_numpy(np.array(m)).double().to(DEV) for m in plan.matrices(s)) for s in range(plan.n_shells)]
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    for V, off in ((65535, 0), (65536 + 33, 0), (98304 + 95, 1), (131072 + 1, 0)):
+        x = torch.rand(off + V * plan.n_dw, device=DEV, generator=gen)[off:].view(V, plan.n_dw)
+        c = torch.randn(off + V * plan.n_shells * plan.K, device=DEV, generator=gen)[off:].view(V, plan.n_shells, plan.K)
+        xs = torch.split(x.double(), list(dirs), dim=1)
+        fit = torch.stack([xs[s] @ P.t() for s, (_, P) in enumerate(mats)], 1)
+        ev = torch.cat([c[:, s].double() @ B.t() for s, (B, _) in enumerate(mats)], 1)
+        check("signal2sh", dl.signal2sh_fwd(plan, x, precision=prec), fit, prec)
+        check("sh2signal", dl.sh2signal_fwd(plan, c, precision=prec), ev, prec)
