@@ -238,11 +238,13 @@ __global__ __launch_bounds__(256) void unfold_kernel(const float *part, int64_t 
 }
 
 // out[i] = sum_p part[p * n + i], in the order of p; eight loads in flight
-// per thread (one at a time took 55 us for 128 partials of 135 x 1441).
+// per thread (one at a time took 55 us for 128 partials of 135 x 1441).  The sum
+// is in 64 bits, which the loads hide: in 32 bits its roundings were a tenth of
+// a small layer's gradient error.
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float *part, int splits, int64_t n, float *out) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  float s = 0.0f;
+  double s = 0.0;
   int p = 0;
   for (; p + 8 <= splits; p += 8) {
     float v[8];
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float *part, in
     for (int u = 0; u < 8; ++u) s += v[u];
   }
   for (; p < splits; ++p) s += part[(int64_t)p * n + i];
-  out[i] = s;
+  out[i] = (float)s;
 }
 
 // Tables are transposed once, when a plan is made: one entry per thread.

@@ -76,10 +76,15 @@ __device__ __forceinline__ void mma_parts(const bf16x8 (&a)[NI][3], const bf16x8
 // zero, small ones first, and added to it in float32 (RNE).  It takes half the
 // accumulator registers and one vector add per value and step.  SWAP: the A
 // operand first (a lane holds four rows of one column, not four columns of a
-// row).
+// row).  The matrix unit cuts what lies below its sum off towards minus
+// infinity, which adds up over the steps where the sum itself hardly grows:
+// the caller negates A in every other step (flip_sign) and gives sign = -1 for
+// it, and the cuts cancel.  Weight gradient of 43 521 voxels, 1 -> 8 channels,
+// against 64 bits: 6e-7 without, 1.3e-7 with it (float32 instruction 3e-7); of
+// 1M voxels, 3 -> 32 channels, 3e-7 (1.1e-6).
 template <bool SWAP, int NI, int NJ, int TN>
 __device__ __forceinline__ void mma_parts_sum(const bf16x8 (&a)[NI][3], const bf16x8 (&b)[NJ][3],
-                                              floatx4 (&acc)[NI][TN], int j0) {
+                                              floatx4 (&acc)[NI][TN], int j0, float sign) {
   floatx4 c[NI][NJ];
 #pragma unroll
   for (int u = 0; u < kProducts; ++u)
@@ -95,7 +100,16 @@ __device__ __forceinline__ void mma_parts_sum(const bf16x8 (&a)[NI][3], const bf
   for (int j = 0; j < NJ; ++j)
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-      if (j0 + j < TN) acc[i][j0 + j] += c[i][j];
+      if (j0 + j < TN)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j0 + j][e] = fmaf(sign, c[i][j][e], acc[i][j0 + j][e]);
+}
+
+__device__ __forceinline__ bf16x8 flip_sign(bf16x8 v, unsigned mask) {  // mask 0 or 0x80008000
+  typedef unsigned words __attribute__((ext_vector_type(4)));
+  words w = __builtin_bit_cast(words, v);
+  w ^= mask;
+  return __builtin_bit_cast(bf16x8, w);
 }
 
 template <int TM, int TN>

@@ -469,7 +469,8 @@ __global__ __launch_bounds__(64 * CF::NW, 2) void tile_kernel(AO ao, BO bo, CS c
     xa.load(ao, kbeg, kend);
     xb.load(bo, kbeg, kend);
   }
-  for (int k0 = kbeg; k0 < kend; k0 += TBK) {
+  unsigned flip = 0;
+  for (int k0 = kbeg; k0 < kend; k0 += TBK, flip ^= 0x80008000u) {
     __syncthreads();  // the last stage's fragments have been read
     xa.store(ao, kend - k0, sa);
     xb.store(bo, kend - k0, sb);
@@ -483,7 +484,10 @@ __global__ __launch_bounds__(64 * CF::NW, 2) void tile_kernel(AO ao, BO bo, CS c
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int p = 0; p < P; ++p) a[i][p] = AO::template frag<BM>(sa, wm * TM + i, q16, g4, p);
+      for (int p = 0; p < P; ++p) {
+        a[i][p] = AO::template frag<BM>(sa, wm * TM + i, q16, g4, p);
+        if constexpr (P == 3) a[i][p] = flip_sign(a[i][p], flip);
+      }
 #pragma unroll
     for (int j = 0; j < TN; j += NJ) {
       bf16x8 b[NJ][P];
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(64 * CF::NW, 2) void tile_kernel(AO ao, BO bo, CS c
         for (int p = 0; p < P; ++p)
           if (j + u < TN) b[u][p] = BO::template frag<BN>(sb, wn * TN + j + u, q16, g4, p);
       if constexpr (P == 3) {
-        mma_parts_sum<SWAP>(a, b, acc, j);
+        mma_parts_sum<SWAP>(a, b, acc, j, flip ? -1.0f : 1.0f);
       } else {
 #pragma unroll
         for (int i = 0; i < TM; ++i)

@@ -111,3 +111,22 @@ def test_weight_gradient_edges(case, store):
         _, dW, db = dl.lsc_bwd(plan, ag, cuda(W), gg, a_out=cuda(mask), relu=True, need_input_grad=False)
         check("dW masked", dW, np.einsum("okcj,tkj->oct", G.reshape(O, plan.K_out, C, plan.K_in), Q), prec, kind="sum")
         check("db masked", db, gm.astype(np.float64).sum(0) @ Pm.sum(1), prec, kind="sum")
+
+
+@pytest.mark.parametrize("case", [(1, 8, 4), (3, 32, 4), (8, 3, 4)])
+def test_long_sums_do_not_drift(case):
+    # 131 072 voxels in slices of 1024 or more: 32 steps of 2^-24 each, at random,
+    # are 3.4e-7 of a slice's sum; a cut always to one side grows with the steps
+    C, O, L = case
+    V = 131072
+    plan = _plan(L, L)
+    W = dg.lsc_weights(8, 0, C, O, plan.T)[0]
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    a = torch.randn(V, C, plan.K_in, device=DEV, generator=gen)
+    g = torch.randn(V, O, plan.K_out, device=DEV, generator=gen)
+    _, Q = _folded(plan, W.astype(np.float64))
+    G = (g.reshape(V, -1).double().t() @ a.reshape(V, -1).double()).cpu().numpy()
+    ref = np.einsum("okcj,tkj->oct", G.reshape(O, plan.K_out, C, plan.K_in), Q)
+    _, dW, _ = dl.lsc_bwd(plan, a, cuda(W), g, need_input_grad=False)
+    err = np.linalg.norm(dW.double().cpu().numpy().reshape(ref.shape) - ref) / np.linalg.norm(ref)
+    assert err <= 3.4e-7, err
