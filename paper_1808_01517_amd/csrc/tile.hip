@@ -560,10 +560,10 @@ struct CPart {
 // is read once.  The larger side is on the rows.
 // Measured against the streaming core, which read eight k one by one for a
 // fragment and split or rounded them in every wave: FP32 with float32
-// instructions 3.65 -> 2.73 ms at 1M voxels x 1440 x 136 (0.52 of the matrix
-// cores' cycles; the same core with part products 4.3 ms), 632 -> 454 us for
-// 8192 x 2880 x 1441; BF16 1.10 -> 0.96 ms (3.7 TB/s) and, 8192 x 2881 x 2880
-// from bfloat16, 294 -> 221 us.
+// instructions 3.65 -> 2.8 ms at 1M voxels x 1440 x 136 (half of the matrix
+// cores' cycles, 2.7 before every other stage was negated; the same core with
+// part products 4.3 ms), 632 -> 454 us for 8192 x 2880 x 1441; BF16 1.10 ->
+// 0.96 ms (3.7 TB/s) and, 8192 x 2881 x 2880 from bfloat16, 294 -> 221 us.
 using GradCfg = Cfg<128, 144, 4, 1>;
 
 template <int P, class GO, class AO>
