@@ -1028,10 +1028,10 @@ namespace {
 
 // The folded matrix for one use: T and the folded bias (forward, `transposed`
 // false) or T^T (input gradient), in the storage its GEMM reads: bfloat16,
-// three parts (FP32), or float32 for the masked GEMMs of the register-staged
-// core (`masked`), with its row padding zeroed.
+// three parts (FP32, streaming and image cores), or float32 for the
+// register-staged core (`staged`), with its row padding zeroed.
 dlm_status fold_weights(const dlm_lsc_plan *p, int C, int O, const float *W, const float *bias, const FoldWs &w,
-                        bool transposed, bool masked, dlm_precision prec, void *stream) {
+                        bool transposed, bool staged, dlm_precision prec, void *stream) {
   const double KK = double(p->K_out) * p->K_in, M = double(O) * p->K_out, CK = double(C) * p->K_in;
   FoldOut f;
   f.W = W;
@@ -1042,7 +1042,7 @@ dlm_status fold_weights(const dlm_lsc_plan *p, int C, int O, const float *W, con
   f.Ki = p->K_in;
   f.Ko = p->K_out;
   f.transposed = transposed;
-  f.kind = prec == DLM_BF16 ? kFoldBf16 : masked ? kFoldF32 : kFoldParts;
+  f.kind = prec == DLM_BF16 ? kFoldBf16 : staged ? kFoldF32 : kFoldParts;
   f.out = f.kind == kFoldParts  ? (void *)w.parts
           : f.kind == kFoldBf16 ? (void *)(transposed ? w.TwTh : w.Twh)
                                 : (void *)(transposed ? w.TwT : w.Tw);
@@ -1057,22 +1057,31 @@ dlm_status fold_weights(const dlm_lsc_plan *p, int C, int O, const float *W, con
   return launched(launch_lsc_fold(f, stream));
 }
 
+// The folded matrix of the GEMM `t` in the storage that the core it will run
+// on reads: masked operands and workspaces that are not 16-byte aligned go to
+// the register-staged core.
+dlm_status fold_for(const dlm_lsc_plan *p, int C, int O, const float *W, const float *bias, const FoldWs &w,
+                    const TableGemm &t, dlm_precision prec, void *stream) {
+  const bool staged = !stream_table_ok(t, prec);
+  if (staged && stream_table_only(t)) return launched(-3);  // before anything is launched
+  return fold_weights(p, C, O, W, bias, w, t.op == kOpFoldBwdData, staged, prec, stream);
+}
+
 dlm_status lsc_fwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const float *W, const float *bias, int O,
                           void *a_out, int64_t V, int fuse_relu, int io, uint16_t *relu_bits, void *ws, size_t ws_bytes,
                           dlm_precision prec, void *stream) {
   if (ws_bytes < fold_ws_need(p, C, O))
     return fail(DLM_EWORKSPACE, "workspace of %zu bytes is below the %zu-byte minimum", ws_bytes, fold_ws_need(p, C, O));
   FoldWs w = fold_ws_carve(p, C, O, ws);
-  dlm_status s = fold_weights(p, C, O, W, bias, w, false, false, prec, stream);
-  if (s != DLM_OK) return s;
   const int M = O * p->K_out, CK = C * p->K_in;
   TableGemm t;  // a_out[v][(o,k)] = sum_{(c,j)} Tw[(o,k)][(c,j)] a_in[v][(c,j)] + bias[o] (P_m 1)[k]
   if (io & DLM_IO_IN_BF16) t.Ah = static_cast<const uint16_t *>(a_in);
   else t.A = static_cast<const float *>(a_in);
   t.lda = CK;
+  t.Bf = w.Tw;
   t.Bh = w.Twh;
   t.B3 = w.parts;
-  t.ldb_h = int64_t(pad32(size_t(CK)));
+  t.ldb_f = t.ldb_h = int64_t(pad32(size_t(CK)));
   if (io & DLM_IO_OUT_BF16) t.Ch = static_cast<uint16_t *>(a_out);
   else t.C = static_cast<float *>(a_out);
   t.ldc = M;
@@ -1083,6 +1092,8 @@ dlm_status lsc_fwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
   t.relu = fuse_relu ? 1 : 0;
   t.op = kOpFoldFwd;
   t.relu_bits_out = fuse_relu ? relu_bits : nullptr;
+  dlm_status s = fold_for(p, C, O, W, bias, w, t, prec, stream);
+  if (s != DLM_OK) return s;
   TimedScope ts("lsc_folded_fwd", stream,
                 double(V) * (CK * ((io & DLM_IO_IN_BF16) ? 2.0 : 4.0) + double(M) * ((io & DLM_IO_OUT_BF16) ? 2.0 : 4.0) +
                              (t.relu_bits_out ? M / 8.0 : 0.0)),
@@ -1124,7 +1135,6 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
   // DLM_RELU_OUT with a bfloat16 a_out is rejected by the caller
   const float *mask = (relu_flags & DLM_RELU_OUT) ? static_cast<const float *>(a_out) : nullptr;
   if (da_in && V > 0) {
-    if ((s = fold_weights(p, C, O, W, nullptr, w, true, mask != nullptr, prec, stream)) != DLM_OK) return s;
     TableGemm t;  // da_in[v][(c,j)] = sum_{(o,k)} Tw[(o,k)][(c,j)] (da_out * [a_out > 0])[v][(o,k)]
     if (out_h) t.Ah = static_cast<const uint16_t *>(da_out);
     else t.A = static_cast<const float *>(da_out);
@@ -1148,6 +1158,7 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
     t.N = CK;
     t.K = M;
     t.op = kOpFoldBwdData;
+    if ((s = fold_for(p, C, O, W, nullptr, w, t, prec, stream)) != DLM_OK) return s;
     const double ob = out_h ? 2.0 : 4.0, ib = in_h ? 2.0 : 4.0;  // bytes per element
     const bool omask = t.out_mask || t.out_mask_h;
     TimedScope ts("lsc_folded_bwd_data", stream,

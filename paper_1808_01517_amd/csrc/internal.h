@@ -96,6 +96,10 @@ int launch_table_gemm(const TableGemm &g, dlm_precision prec, void *stream);
 // no operand mask, the precision's table (three-part B3 / bfloat16 Bh) with
 // row stride ldb_h a multiple of 32 and zeros in columns K .. stride-1.
 bool stream_table_ok(const TableGemm &g, dlm_precision prec);
+// bfloat16 activations and ReLU bits, which no other core takes
+inline bool stream_table_only(const TableGemm &g) {
+  return g.Ah || g.Ch || g.out_mask_h || g.relu_bits_out || g.relu_bits_in;
+}
 int launch_stream_table(const TableGemm &g, dlm_precision prec, void *stream);
 // Weight gradient of the folded form over voxel slices of ksplit voxels:
 // partial[s][m][n] = sum_v g[v][m] a[v][n], with a ones column at n = CK (the

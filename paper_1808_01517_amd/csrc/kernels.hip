@@ -501,8 +501,7 @@ static int table_gemm_op(const TableGemm &t, dlm_precision prec, hipStream_t st)
 
 int launch_table_gemm(const TableGemm &t, dlm_precision prec, void *stream) {
   if (stream_table_ok(t, prec)) return launch_stream_table(t, prec, stream);
-  if (t.Ah || t.Ch || t.out_mask_h || t.relu_bits_out || t.relu_bits_in)
-    return -3;  // bfloat16 activations and ReLU bits: streaming core only
+  if (stream_table_only(t) || !(prec == DLM_BF16 ? (const void *)t.Bh : (const void *)t.Bf)) return -3;
   hipStream_t st = (hipStream_t)stream;
   switch (t.op) {
     case kOpS2shFwd: return table_gemm_op<kOpS2shFwd>(t, prec, st);
