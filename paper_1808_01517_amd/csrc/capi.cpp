@@ -1002,6 +1002,15 @@ FoldWs fold_ws_carve(const dlm_lsc_plan *p, int C, int O, void *ws) {
   return w;
 }
 
+// The values beside a three-part table, in rows without padding.  Both lie over
+// the tables above, of which a call makes one kind: 6 M pad32(CK) bytes of parts
+// and 4 M CK of values in 6 (M pad32(CK) + CK pad32(M)).
+float *fold_values(const dlm_lsc_plan *p, int C, int O, const FoldWs &w, bool transposed) {
+  const size_t M = size_t(O) * p->K_out, CK = size_t(C) * p->K_in;
+  const size_t n = transposed ? CK * pad32(M) : M * pad32(CK);
+  return reinterpret_cast<float *>(w.parts + 3 * n);
+}
+
 dlm_status lsc_check(const dlm_lsc_plan *p, int C, int O, int64_t V, dlm_precision prec) {
   if (!p) return fail(DLM_EINVAL, "plan is NULL");
   if (C < 1 || C > kMaxChannels || O < 1 || O > kMaxChannels)
@@ -1047,12 +1056,13 @@ dlm_status fold_weights(const dlm_lsc_plan *p, int C, int O, const float *W, con
           : f.kind == kFoldBf16 ? (void *)(transposed ? w.TwTh : w.Twh)
                                 : (void *)(transposed ? w.TwT : w.Tw);
   f.ld = int64_t(pad32(transposed ? size_t(O) * p->K_out : size_t(C) * p->K_in));
+  if (f.kind == kFoldParts) f.copy = fold_values(p, C, O, w, transposed);
   if (!transposed) {
     f.bias = bias;
     f.pm1 = p->dpm1.f32;
     f.bvec = w.bvec;
   }
-  TimedScope ts("lsc_fold", stream, (double(O) * C * p->T + p->T * KK) * 4.0 + M * CK * (f.kind == kFoldBf16 ? 2.0 : f.kind == kFoldParts ? 6.0 : 4.0),
+  TimedScope ts("lsc_fold", stream, (double(O) * C * p->T + p->T * KK) * 4.0 + M * CK * (f.kind == kFoldBf16 ? 2.0 : f.kind == kFoldParts ? 10.0 : 4.0),
                 2.0 * O * C * KK * p->T);
   return launched(launch_lsc_fold(f, stream));
 }
@@ -1081,6 +1091,7 @@ dlm_status lsc_fwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
   t.Bf = w.Tw;
   t.Bh = w.Twh;
   t.B3 = w.parts;
+  t.B3f = fold_values(p, C, O, w, false);
   t.ldb_f = t.ldb_h = int64_t(pad32(size_t(CK)));
   if (io & DLM_IO_OUT_BF16) t.Ch = static_cast<uint16_t *>(a_out);
   else t.C = static_cast<float *>(a_out);
@@ -1143,6 +1154,7 @@ dlm_status lsc_bwd_folded(const dlm_lsc_plan *p, const void *a_in, int C, const 
     t.Bf = w.TwT;
     t.Bh = w.TwTh;
     t.B3 = w.parts;
+    t.B3f = fold_values(p, C, O, w, true);
     t.ldb_f = t.ldb_h = int64_t(pad32(size_t(M)));
     const bool bits = (relu_flags & DLM_RELU_IN) && relu_bits;  // mask from the forward's ReLU bits
     if (in_h) {
@@ -1287,6 +1299,7 @@ dlm_status dlm_lsc_fwd_image(const dlm_lsc_plan *p, const float *a_in, int C, co
   ImageGemm x;
   x.in = a_in;
   x.table = prec == DLM_BF16 ? w.Twh : w.parts;
+  x.values = fold_values(p, C, O, w, false);
   x.K = C * p->K_in;
   x.N = O * p->K_out;
   x.ldb = int64_t(pad32(size_t(x.K)));
@@ -1323,6 +1336,7 @@ dlm_status dlm_lsc_bwd_image(const dlm_lsc_plan *p, const float *a_in, int C, co
     x.in = da_out;
     x.ibits = relu_bits;
     x.table = prec == DLM_BF16 ? w.TwTh : w.parts;
+    x.values = fold_values(p, C, O, w, true);
     x.K = M;
     x.N = CK;
     x.ldb = int64_t(pad32(size_t(M)));

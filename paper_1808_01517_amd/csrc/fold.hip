@@ -22,10 +22,15 @@ namespace fold {
 constexpr int kPairs = 8;  // (o, c) pairs per block of the fold
 constexpr int kTaps = 32;  // taps held in registers at a time
 
-// Store entry (row, col) of the folded matrix.
+// Store entry (row, col) of the folded matrix; of three parts also the value
+// itself, in rows of ldc: parts hold neither infinities, nor what rounds to
+// one, nor all bits of what is below 2^-109, and results that such entries
+// may have reached are computed again from it.
 template <int KIND>
-__device__ __forceinline__ void put(void *out, int64_t ld, int64_t row, int64_t col, float v) {
+__device__ __forceinline__ void put(void *out, int64_t ld, int64_t row, int64_t col, float v, float *copy = nullptr,
+                                    int64_t ldc = 0) {
   if constexpr (KIND == kFoldParts) {
+    if (copy) copy[row * ldc + col] = v;
     uint16_t *o = static_cast<uint16_t *>(out) + row * 3 * ld + col;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -56,8 +61,8 @@ __device__ __forceinline__ void put(void *out, int64_t ld, int64_t row, int64_t 
 // padding and the bias (2-5 us).
 template <bool TR, int KIND>
 __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *Q, int C, int O, int T, int Ki, int Ko,
-                                                   void *out, int64_t ld, const float *bias, const float *pm1,
-                                                   float *bvec, int nbE) {
+                                                   void *out, int64_t ld, float *copy, const float *bias,
+                                                   const float *pm1, float *bvec, int nbE) {
   const int tid = threadIdx.x;
   if ((int)blockIdx.x == nbE) {
     const int64_t id = (int64_t)blockIdx.y * 256 + tid, nth = (int64_t)gridDim.y * 256;
@@ -116,7 +121,7 @@ __global__ __launch_bounds__(256) void fold_kernel(const float *W, const float *
 #pragma unroll
   for (int i = 0; i < kPairs; ++i) {
     if (p0 + i >= pairs) break;
-    put<KIND>(out, ld, (int64_t)x * np + p, (int64_t)y * nq + q, acc[i]);
+    put<KIND>(out, ld, (int64_t)x * np + p, (int64_t)y * nq + q, acc[i], copy, (int64_t)Y * nq);
     if (++y == Y) {
       y = 0;
       ++x;
@@ -288,7 +293,7 @@ int launch_lsc_fold(const FoldOut &f, void *stream) {
   hipStream_t st = (hipStream_t)stream;
 #define DLM_FOLD(TR, BF)                                                                                          \
   hipLaunchKernelGGL((fold::fold_kernel<TR, BF>), grid, dim3(256), 0, st, f.W, f.Q, f.C, f.O, f.T, f.Ki, f.Ko, f.out, \
-                     f.ld, f.bias, f.pm1, f.bvec, nbE)
+                     f.ld, f.copy, f.bias, f.pm1, f.bvec, nbE)
   if (f.transposed) {
     if (f.kind == kFoldBf16) DLM_FOLD(true, kFoldBf16);
     else if (f.kind == kFoldParts) DLM_FOLD(true, kFoldParts);

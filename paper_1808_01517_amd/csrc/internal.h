@@ -68,6 +68,7 @@ struct TableGemm {
   const float *Bf = nullptr;
   const uint16_t *Bh = nullptr;
   const uint16_t *B3 = nullptr;  // three-part float32 table (streaming core in FP32), rows of 3 ldb_h
+  const float *B3f = nullptr;    // the values B3 is made of, rows of K
   int64_t b_gs = 0;
   int64_t ldb_f = 0;  // row stride of the float32 table (0: K)
   int64_t ldb_h = 0;  // row stride of the bfloat16 table or of one part of B3 (0: K)
@@ -124,6 +125,7 @@ struct ImageGemm {
   const float *in = nullptr;
   const uint16_t *ibits = nullptr;
   const uint16_t *table = nullptr;
+  const float *values = nullptr;  // what a three-part table is made of, rows of K
   int64_t ldb = 0;
   const float *bias = nullptr;
   float *out = nullptr;
@@ -305,7 +307,8 @@ int launch_adam(float *w, const float *g, float *m, float *v, int64_t n, float l
 // The folded matrix of a layer: out[(o*Ko+k)][(c*Ki+j)] = sum_t W[o][c][t]
 // Q[t][k][j], or its transpose out[(c*Ki+j)][(o*Ko+k)], in float32, bfloat16
 // or as the three bfloat16 parts of its float32 values (part i of a row i * ld
-// entries on, rows 3 ld apart); rows of stride ld, zeros in their padding.  With bvec, also
+// entries on, rows 3 ld apart, and `copy` the values themselves in rows without
+// padding); rows of stride ld, zeros in their padding.  With bvec, also
 // bvec[o*Ko+k] = bias[o] * pm1[k] (zeros when bias is null).  Q is [t][k][j],
 // for the transpose [t][j][k].
 enum FoldKind : int { kFoldF32 = 0, kFoldBf16, kFoldParts };
@@ -316,6 +319,7 @@ struct FoldOut {
   FoldKind kind = kFoldF32;
   void *out = nullptr;
   int64_t ld = 0;
+  float *copy = nullptr;
   const float *bias = nullptr, *pm1 = nullptr;
   float *bvec = nullptr;
 };

@@ -16,7 +16,9 @@
 //
 // Infinities, NaN and values that round to an infinite x0 end as NaN here;
 // kernels look for results that are not finite (bad_tiles) and compute those
-// tiles again with the float32 instructions, so that float32's rules hold.
+// tiles again with the float32 instructions from the values themselves
+// (activations, and the table's beside its parts), so that float32's rules
+// hold.
 #pragma once
 
 #include "gemm_common.h"

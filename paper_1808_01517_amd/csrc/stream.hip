@@ -182,6 +182,8 @@ struct SKh {
 struct SK3 {
   const uint16_t *p;
   int64_t ldp, rows;
+  const float *f;  // the values, rows of ldf
+  int64_t ldf;
   static constexpr int kUnit = 16;
   static constexpr bool kOnes = false;
   template <int BR>
@@ -208,11 +210,7 @@ struct SK3 {
 #pragma unroll
     for (int i = 0; i < 3; ++i) v[i] = *reinterpret_cast<const bf16x8 *>(t + i * BR * SBK * 2);
   }
-  __device__ float at(int64_t r, int k) const {
-    const uint16_t *q = p + (r < rows ? r : rows - 1) * 3 * ldp + k;
-    auto f = [](uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); };
-    return (f(q[0]) + f(q[ldp])) + f(q[2 * ldp]);
-  }
+  __device__ float at(int64_t r, int k) const { return f[(r < rows ? r : rows - 1) * ldf + k]; }
 };
 
 // bfloat16 k-contiguous rows (activations stored in bfloat16): element
@@ -1323,7 +1321,7 @@ int stream_table(AO ao, BO bo, const TableGemm &t, hipStream_t st) {
 
 template <int OP, bool F32, class AO>
 int stream_table_b(AO ao, const TableGemm &t, hipStream_t st) {
-  if constexpr (F32) return stream_table<OP, true>(ao, SK3{t.B3, t.ldb_h, t.N}, t, st);
+  if constexpr (F32) return stream_table<OP, true>(ao, SK3{t.B3, t.ldb_h, t.N, t.B3f, t.K}, t, st);
   else return stream_table<OP, false>(ao, SKh{t.Bh, t.ldb_h, t.N}, t, st);
 }
 
@@ -1359,6 +1357,7 @@ bool stream_table_ok(const TableGemm &t, dlm_precision prec) {
   if (t.lda >= kMaxStreamLd || t.ldb_f >= kMaxStreamLd || t.ldb_h >= kMaxStreamLd) return false;
   if (t.op == kOpFoldFwd ? (t.bias_n == nullptr || t.out_mask != nullptr) : t.bias_n != nullptr) return false;
   const uint16_t *B = prec == DLM_BF16 ? t.Bh : t.B3;
+  if (prec != DLM_BF16 && !t.B3f) return false;
   return B != nullptr && t.ldb_h > 0 && t.ldb_h % SBK == 0 && t.ldb_h >= t.K && aligned16(B);
 }
 

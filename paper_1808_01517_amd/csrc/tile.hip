@@ -287,12 +287,15 @@ struct Rows {
 };
 
 // A folded table in P bfloat16 parts: part i of (r, k) at p[r P ld + i ld + k],
-// zeros from K to ld (a multiple of 32); one table for every image.
+// zeros from K to ld (a multiple of 32); one table for every image.  P == 3:
+// the values themselves in f, rows of ldf.
 template <int P>
 struct Table {
   const uint16_t *p;
   int64_t ld;
   int rows;
+  const float *f;
+  int64_t ldf;
   template <int BR>
   static constexpr int size() { return P * BR * kRowLd; }
   template <int BR>
@@ -327,13 +330,7 @@ struct Table {
   __device__ static bf16x8 frag(const uint16_t *lds, int rg, int q16, int g4, int i) {
     return *reinterpret_cast<const bf16x8 *>(lds + i * BR * kRowLd + (rg * 16 + q16) * kRowLd + 8 * g4);
   }
-  __device__ float at(int64_t r, int k) const {
-    const uint16_t *q = p + least(r, rows - 1) * P * ld + k;
-    float v = 0.0f;
-#pragma unroll
-    for (int i = 0; i < P; ++i) v += __builtin_bit_cast(float, (uint32_t)q[i * ld] << 16);
-    return v;
-  }
+  __device__ float at(int64_t r, int k) const { return f[least(r, rows - 1) * ldf + k]; }
 };
 
 // bfloat16, contiguous along the rows (activations stored in bfloat16; ld and
@@ -640,7 +637,7 @@ struct CImage {
 // part products want the larger tile once it fills the chip.
 template <int OP, int P, class AO>
 int image_table(AO ao, const ImageGemm &x, hipStream_t st) {
-  const Table<P> tab{x.table, x.ldb, x.N};
+  const Table<P> tab{x.table, x.ldb, x.N, x.values, x.K};
   const int64_t words = (x.P + 15) / 16;
   const CImage cs{x.out, x.P, x.P * x.N, x.bias, x.relu, x.obits, words, words * x.N};
   const int64_t b64 = (x.P + 63) / 64 * x.B, b128 = (x.P + 127) / 128 * x.B, b256 = (x.P + 255) / 256 * x.B;
@@ -704,6 +701,7 @@ bool image_ok(int64_t B, int64_t P) { return B >= 1 && B <= 128 && P >= 1 && P <
 
 int launch_image_gemm(const ImageGemm &x, dlm_precision prec, void *stream) {
   if (!image_ok(x.B, x.P) || !x.table || (reinterpret_cast<uintptr_t>(x.table) & 15) || x.ldb % 32 != 0) return -3;
+  if (prec != DLM_BF16 && !x.values) return -3;
   hipStream_t st = (hipStream_t)stream;
   return prec == DLM_BF16 ? tile::image_gemm<1>(x, st) : tile::image_gemm<3>(x, st);
 }
