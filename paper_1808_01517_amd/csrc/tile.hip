@@ -315,7 +315,10 @@ struct Table {
   __device__ bool whole(int, int) const { return true; }
   template <int BR>
   __device__ void load(Raw &x, int, uint32_t o, int64_t r0, int k0) const {
-    __builtin_memcpy(&x.v, __builtin_assume_aligned(p + r0 * P * ld + k0 + o, 16), 16);
+    // not a memcpy: that kept the runs of some tiles in scratch memory, and a
+    // wait for each load right behind it (1440 -> 135 channels, 32 768 voxels,
+    // FP32 177 us; 106 in registers)
+    x.v = *reinterpret_cast<const u32x4 *>(p + r0 * P * ld + k0 + o);
   }
   template <int BR>
   __device__ void load_edge(Raw &, int, int64_t, int, int) const {}
@@ -324,7 +327,7 @@ struct Table {
   template <int BR>
   __device__ void store(const Raw &x, int e, int, int, uint16_t *lds) const {
     uint16_t *d = lds + e / (BR * 4) * BR * kRowLd + row_of<BR>(e) * kRowLd + k_of<BR>(e);
-    __builtin_memcpy(__builtin_assume_aligned(d, 16), &x.v, 16);
+    *reinterpret_cast<u32x4 *>(d) = x.v;
   }
   template <int BR>
   __device__ static bf16x8 frag(const uint16_t *lds, int rg, int q16, int g4, int i) {
