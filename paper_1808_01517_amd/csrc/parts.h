@@ -15,8 +15,8 @@
 // where eight 16x16x4 float32 ones take 256.
 //
 // Infinities, NaN and values that round to an infinite x0 end as NaN here;
-// kernels look for results that are not finite (bad_tiles) and compute those
-// tiles again with the float32 instructions from the values themselves
+// kernels look for results that are not finite (any_odd) and compute those
+// again with the float32 instructions from the values themselves
 // (activations, and the table's beside its parts), so that float32's rules
 // hold.
 #pragma once
@@ -122,10 +122,9 @@ __device__ __forceinline__ void add_parts(floatx4 (&hi)[TM][TN], const floatx4 (
     for (int j = 0; j < TN; ++j) hi[i][j] += lo[i][j];
 }
 
-// Which of a wave's tiles hold a value that is not finite, one bit each.
+// Whether a wave's tiles hold a value that is not finite.
 template <int TM, int TN>
-__device__ __forceinline__ uint64_t bad_tiles(const floatx4 (&acc)[TM][TN]) {
-  static_assert(TM * TN <= 64, "one bit per tile");
+__device__ __forceinline__ bool any_odd(const floatx4 (&acc)[TM][TN]) {
   float z = 0.0f;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -133,48 +132,167 @@ __device__ __forceinline__ uint64_t bad_tiles(const floatx4 (&acc)[TM][TN]) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) z = fmaf(acc[i][j][e], 0.0f, z);
-  if (!__any(z != z)) return 0;
-  uint64_t bad = 0;
+  return __any(z != z);
+}
+__device__ __forceinline__ bool is_odd(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7f800000u) == 0x7f800000u; }
+
+// The slow path reads its operands from global memory, 16 rows of four k at a
+// time: op.at(k, l) is the value of lane (q16, g4) of rows r .. r + 15 at
+// k + g4, k a multiple of 4 and the same in all lanes, with l = op.lane(r, q16,
+// g4) its place among them.  About kLoads of them are in flight: twice as many
+// cost the cores' own loops registers and gained nothing.
+constexpr int kLoads = 20;
+
+// Which of 16 rows have a NaN among their k, one bit each; stops once all of
+// `want` have.
+template <class OP>
+__device__ __forceinline__ unsigned nan_rows(const OP &op, int64_t r, int kbeg, int kend, unsigned want) {
+  constexpr int kSteps = 16;
+  const int lane = threadIdx.x & 63, q16 = lane & 15, g4 = lane >> 4;
+  unsigned found = 0;
+  auto add = [&](bool nan) {
+    const uint64_t m = __ballot(nan);
+    found |= (unsigned)(m | m >> 16 | m >> 32 | m >> 48) & 0xffffu;
+  };
+  const auto l = op.lane(r, q16, g4);
+  int k = kbeg;
+#pragma unroll 1
+  for (; k + 4 * kSteps <= kend && (found & want) != want; k += 4 * kSteps) {
+    bool nan = false;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int u = 0; u < kSteps; ++u) {
+      const float v = op.at(k + 4 * u, l);
+      nan |= v != v;
+    }
+    add(nan);
+  }
+#pragma unroll 1
+  for (; k < kend && (found & want) != want; k += 4) {
+    const float v = op.at(k, op.lane(r, q16, min(g4, kend - 1 - k)));
+    add(v != v);
+  }
+  return found;
+}
+
+// The same of 64 rows per word, a row per lane, in the first 16 k only (weights
+// that have gone NaN are so all over).
+template <int NM, class OP>
+__device__ __forceinline__ void nan_heads(const OP &op, int64_t r, int kbeg, int kend, uint64_t (&m)[NM]) {
+  const int lane = threadIdx.x & 63, q16 = lane & 15, g4 = lane >> 4;
+#pragma unroll
+  for (int p = 0; p < NM; ++p) {
+    bool nan = false;
+#pragma unroll 2
+    for (int k = kbeg; k < min(kend, kbeg + 16); k += 4)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float v = op.at(k, op.lane(r + 64 * p + 16 * g4, q16, min(g, kend - 1 - k)));
+        nan |= v != v;
+      }
+    m[p] = __ballot(nan);
+  }
+}
+
+// TN 16 x 16 tiles beside each other in float32 (16x16x4).
+template <bool SWAP, int TN, class AO, class BO>
+__device__ __forceinline__ void redo_row(const AO &ao, const BO &bo, int64_t ra, int64_t rb, int kbeg, int kend,
+                                         floatx4 (&c)[TN]) {
+  constexpr int kSteps = kLoads / (1 + TN);
+  const int lane = threadIdx.x & 63, q16 = lane & 15, g4 = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) c[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](int j, float a, float b) {
+    c[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(SWAP ? a : b, SWAP ? b : a, c[j], 0, 0, 0);
+  };
+  const auto la = ao.lane(ra, q16, g4);
+  int k = kbeg;
+#pragma unroll 1
+  for (; k + 4 * kSteps <= kend; k += 4 * kSteps) {
+    float a[kSteps], b[TN][kSteps];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) a[u] = ao.at(k + 4 * u, la);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const floatx4 v = acc[i][j];
-      const float y = ((v[0] * 0.0f + v[1] * 0.0f) + v[2] * 0.0f) + v[3] * 0.0f;
-      if (__any(y != y)) bad |= uint64_t(1) << (i * TN + j);
+      const auto lb = bo.lane(rb + 16 * j, q16, g4);
+#pragma unroll
+      for (int u = 0; u < kSteps; ++u) b[j][u] = bo.at(k + 4 * u, lb);
     }
-  return bad;
-}
-
-// Tiles `bad` of a wave again, in float32 from global memory (16x16x4, k in
-// order).  Never taken for finite results, so its speed does not matter.
-template <bool SWAP, class AO, class BO>
-__device__ __attribute__((noinline)) floatx4 redo_tile(const AO ao, const BO bo, int64_t ra, int64_t rb, int kbeg,
-                                                       int kend) {
-  const int lane = threadIdx.x & 63, q16 = lane & 15, g4 = lane >> 4;
-  floatx4 c{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-  for (int k0 = kbeg; k0 < kend; k0 += 4) {
-    const int k = k0 + g4;
-    const float a = k < kend ? ao.at(ra + q16, k) : 0.0f;
-    const float b = k < kend ? bo.at(rb + q16, k) : 0.0f;
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(SWAP ? a : b, SWAP ? b : a, c, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) mma(j, a[u], b[j][u]);
   }
-  return c;
+#pragma unroll 1
+  for (; k < kend; k += 4) {
+    const int g = min(g4, kend - 1 - k);
+    const float a = ao.at(k, ao.lane(ra, q16, g));
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const float b = bo.at(k, bo.lane(rb + 16 * j, q16, g));
+      mma(j, g == g4 ? a : 0.0f, g == g4 ? b : 0.0f);
+    }
+  }
 }
 
-template <bool SWAP, int TM, int TN, class AO, class BO>
-__device__ __forceinline__ void redo_tiles(const AO &ao, const BO &bo, int64_t ra, int64_t rb, int kbeg, int kend,
-                                           uint64_t bad, floatx4 (&acc)[TM][TN]) {
-#pragma unroll 1
-  for (int t = 0; t < TM * TN; ++t) {
-    if (!((bad >> t) & 1)) continue;
-    const floatx4 c = redo_tile<SWAP>(ao, bo, ra + 16 * (t / TN), rb + 16 * (t % TN), kbeg, kend);
+__device__ __forceinline__ unsigned wave_or(unsigned x) {
+  for (int off = 32; off > 0; off >>= 1) x |= __shfl_xor(x, off, 64);
+  return x;
+}
+
+// Values of a wave's tiles that the parts may have got wrong, again in float32:
+// every one that is not finite, unless a NaN in its row or column (rows below
+// M, N) makes it NaN anyway.  Data with a background of NaN rows are ordinary
+// (a division by a b = 0 signal of zero), so those cost a look at the rows;
+// infinities cost a second, slower product of their 16 rows.  a_nan(i, r, want):
+// those of the 16 rows from r, the wave's i-th group, that have a NaN.
+// 65 536 voxels, 3 -> 32 channels, forward / input / weight gradient: finite
+// 176 / 158 / 238 us, every other voxel NaN 234 / 160 / 260 (each tile computed
+// again, four k at a time, whatever the reason: 4418 / 5507 / 2830), an infinity
+// in every 1024th 545 / 352 / 761 (912 / 972 / 1159).
+template <bool SWAP, int TM, int TN, class AO, class BO, class ANAN>
+__device__ __forceinline__ void mend_odd(const AO &ao, const BO &bo, int64_t ra, int64_t rb, int64_t M, int64_t N, int kbeg,
+                                         int kend, floatx4 (&acc)[TM][TN], ANAN a_nan) {
+  const int lane = threadIdx.x & 63, q16 = lane & 15, g4 = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i) {
+    const int64_t r = ra + 16 * i;
+    unsigned odd[TN], rows = 0, any = 0;  // odd: the lane's values, four bits a tile; rows: theirs among the 16
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        if (i * TN + j == t) acc[i][j] = c;
+    for (int j = 0; j < TN; ++j) {
+      odd[j] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int x = SWAP ? 4 * g4 + e : q16, y = 16 * j + (SWAP ? q16 : 4 * g4 + e);
+        const bool o = is_odd(acc[i][j][e]) && r + x < M && rb + y < N;
+        odd[j] |= (o ? 1u : 0u) << e;
+        rows |= (o ? 1u : 0u) << x;
+      }
+    }
+    rows = wave_or(rows);
+    if (!rows) continue;
+    const unsigned na = a_nan(i, r, rows);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      odd[j] &= SWAP ? ~(na >> (4 * g4)) : (na >> q16 & 1 ? 0u : ~0u);
+      any |= odd[j];
+    }
+    if (!__any(any)) continue;
+    uint64_t heads[(TN + 3) / 4];
+    nan_heads(bo, rb, kbeg, kend, heads);
+    any = 0;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const unsigned nb = (unsigned)(heads[j / 4] >> (16 * (j % 4))) & 0xffffu;
+      odd[j] &= SWAP ? (nb >> q16 & 1 ? 0u : ~0u) : ~(nb >> (4 * g4));
+      any |= odd[j];
+    }
+    if (!__any(any)) continue;
+    floatx4 c[TN];
+    redo_row<SWAP>(ao, bo, r, rb, kbeg, kend, c);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = odd[j] >> e & 1 ? c[j][e] : acc[i][j][e];
   }
 }
 

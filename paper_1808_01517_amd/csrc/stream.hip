@@ -142,7 +142,16 @@ struct SKc {
     split3(*reinterpret_cast<const floatx4 *>(row + (((2 * g4) ^ (r & 7)) << 2)),
            *reinterpret_cast<const floatx4 *>(row + (((2 * g4 + 1) ^ (r & 7)) << 2)), v);
   }
-  __device__ float at(int64_t r, int k) const { return p[(r < rows ? r : rows - 1) * ld + k]; }
+  // the slow path's reads (parts.h)
+  struct Lane {
+    const float *first;  // of rows r .. r + 15, the same in all lanes
+    uint32_t off;
+  };
+  __device__ Lane lane(int64_t r, int q16, int g) const {
+    const int64_t r0 = r < rows ? r : rows - 1, n = rows - 1 - r0;
+    return Lane{p + r0 * ld, (uint32_t)((n < q16 ? n : q16) * ld + g)};
+  }
+  __device__ float at(int k, const Lane &l) const { return (l.first + k)[l.off]; }
 };
 
 // bfloat16 table: element (r, k) at p[r * ldp + k], ldp a multiple of 32,
@@ -210,7 +219,9 @@ struct SK3 {
 #pragma unroll
     for (int i = 0; i < 3; ++i) v[i] = *reinterpret_cast<const bf16x8 *>(t + i * BR * SBK * 2);
   }
-  __device__ float at(int64_t r, int k) const { return f[(r < rows ? r : rows - 1) * ldf + k]; }
+  using Lane = SKc<false>::Lane;
+  __device__ Lane lane(int64_t r, int q16, int g) const { return SKc<false>{f, ldf, rows}.lane(r, q16, g); }
+  __device__ float at(int k, const Lane &l) const { return (l.first + k)[l.off]; }
 };
 
 // bfloat16 k-contiguous rows (activations stored in bfloat16): element
@@ -467,7 +478,7 @@ __device__ __forceinline__ void dma_stage_full(const char *base, const uint32_t 
 // their share of every stage's DMA and compute.  Several blocks per CU keep
 // loads in flight while another block multiplies or stores.
 template <int OP, class CF, bool F32, class AO, class BO, class CS>
-__global__ __launch_bounds__(64 * CF::NW) void gemm_stream_kernel(AO ao, BO bo, CS cs, int64_t M, int N, int K,
+__global__ __launch_bounds__(64 * CF::NW, F32 ? 2 : 1) void gemm_stream_kernel(AO ao, BO bo, CS cs, int64_t M, int N, int K,
                                                                   int ksplit, int nbM, int nbN, int nz) {
   constexpr int BM = CF::BM, BN = CF::BN, NW = CF::NW;
   constexpr int AB = AO::template bytes<BM>(), BB = BO::template bytes<BN>(), SB = AB + BB;
@@ -549,8 +560,12 @@ __global__ __launch_bounds__(64 * CF::NW) void gemm_stream_kernel(AO ao, BO bo, 
   }
   if constexpr (F32) {
     add_parts(acc, low);
-    if (const uint64_t bad = bad_tiles(acc))
-      redo_tiles<false>(ao, bo, m0 + wm * CF::TM * 16, (int64_t)n0 + wn * CF::TN * 16, kbeg, kend, bad, acc);
+    if (any_odd(acc)) {
+      mend_odd<false>(ao, bo, m0 + wm * CF::TM * 16, (int64_t)n0 + wn * CF::TN * 16, M, N, kbeg, kend, acc,
+                      [&](int, int64_t r, unsigned want) { return nan_rows(ao, r, kbeg, kend, want); });
+      // again, so that they take no registers there
+      if constexpr (SidePre<CF, CS>::kOn) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4, z);
+    }
   }
   if constexpr (SidePre<CF, CS>::kOn)
     if (niter == 0) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4, z);
@@ -858,6 +873,23 @@ __device__ __forceinline__ void load_a(const float *A, int64_t lda, int64_t M, i
   }
 }
 
+// Which of the 16 rows of group i have a NaN, one bit each (from their first
+// parts, which are NaN where the value is).
+__device__ __forceinline__ unsigned nan_group(const AFrag<true> &a, int i) {
+  bool nan = false;
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float v = (float)a.v[s][t][0][e];
+        nan |= t == i && v != v;
+      }
+  const uint64_t m = __ballot(nan);
+  return (unsigned)(m | m >> 16 | m >> 32 | m >> 48) & 0xffffu;
+}
+
 template <class CS>
 constexpr int bias_bytes() {
   return CS::kBias ? kMaxN * 4 : 0;
@@ -1054,8 +1086,9 @@ __global__ __launch_bounds__(64 * NW<F32>) void astat_kernel(const float *A, int
     }
     if constexpr (F32) {
       add_parts(acc, low);
-      if (const uint64_t bad = bad_tiles(acc))
-        redo_tiles<false>(SKc<false>{A, lda, M}, bo, r0, (int64_t)(T0 + t) * BN, 0, K, bad, acc);
+      if (any_odd(acc))
+        mend_odd<false>(SKc<false>{A, lda, M}, bo, r0, (int64_t)(T0 + t) * BN, M, N, 0, K, acc,
+                        [&](int i, int64_t, unsigned) { return nan_group(a, i); });
     }
 
     // epilogue: bias, ReLU, mask, rounding, bits; then the stores

@@ -115,7 +115,7 @@ __device__ __forceinline__ void put4(uint16_t *d, int part, floatx4 v) {
 // bound, load() for such a stage and load_edge() for the others (zeros at and
 // beyond kend), store() to LDS and frag().  Runs of rows beyond the matrix
 // load some valid entries; their results are never stored.  batch(b) moves to
-// image b.  at(r, k) is the value itself.
+// image b.  lane() and at() are the slow path's reads (parts.h).
 
 // What zeroes an operand: nothing, a float32 array of the operand's own layout
 // (zero where it is not positive) or ReLU bits along its contiguous index.
@@ -201,12 +201,20 @@ struct Lines {
   __device__ static bf16x8 frag(const uint16_t *lds, int rg, int q16, int g4, int i) {
     return frag_lines<BR, ORD>(lds + i * part<BR>(), rg, q16, g4);
   }
-  __device__ float at(int64_t r, int k) const {
-    if (r >= rows) return ONES && r == rows ? 1.0f : 0.0f;
-    const int64_t o = (int64_t)k * ld + r;
-    if (MASK == kFloatMask && !(mask[o] > 0.0f)) return 0.0f;
-    if (MASK == kBitMask && !((bits[k * lb + (r >> 4)] >> (r & 15)) & 1)) return 0.0f;
-    return p[o];
+  struct Lane {
+    uint32_t off, boff;
+    int shift, one;  // one: 0 for the ones row, -1 beyond the matrix
+  };
+  __device__ Lane lane(int64_t r, int q16, int g) const {
+    const int64_t c = least(r + q16, rows - 1);
+    return Lane{(uint32_t)(g * ld + c), (uint32_t)(g * lb + (c >> 4)), int(c & 15),
+                r + q16 < rows ? 1 : ONES && r + q16 == rows ? 0 : -1};
+  }
+  __device__ float at(int k, const Lane &l) const {
+    float v = (p + (int64_t)k * ld)[l.off];
+    if constexpr (MASK == kFloatMask) v = (mask + (int64_t)k * ld)[l.off] > 0.0f ? v : 0.0f;
+    if constexpr (MASK == kBitMask) v = (bits + (int64_t)k * lb)[l.boff] >> l.shift & 1 ? v : 0.0f;
+    return l.one > 0 ? v : l.one == 0 ? 1.0f : 0.0f;
   }
 };
 
@@ -279,10 +287,21 @@ struct Rows {
   __device__ static bf16x8 frag(const uint16_t *lds, int rg, int q16, int g4, int i) {
     return *reinterpret_cast<const bf16x8 *>(lds + i * BR * kRowLd + (rg * 16 + q16) * kRowLd + 8 * g4);
   }
-  __device__ float at(int64_t r, int k) const {
-    if (r >= rows) return ONES && r == rows ? 1.0f : 0.0f;
-    if (MASK == kBitMask && !((bits[r * lb + (k >> 4)] >> (k & 15)) & 1)) return 0.0f;
-    return p[r * ld + k];
+  struct Lane {
+    const float *first;  // of rows r .. r + 15, the same in all lanes
+    const uint16_t *words;
+    uint32_t off, boff;
+    int g, one;
+  };
+  __device__ Lane lane(int64_t r, int q16, int g) const {
+    const int64_t r0 = base(r), c = least(r + q16, rows - 1) - r0;
+    return Lane{p + r0 * ld, bits + r0 * lb, (uint32_t)(c * ld + g), (uint32_t)(c * lb), g,
+                r + q16 < rows ? 1 : ONES && r + q16 == rows ? 0 : -1};
+  }
+  __device__ float at(int k, const Lane &l) const {
+    float v = (l.first + k)[l.off];
+    if constexpr (MASK == kBitMask) v = (l.words + (k >> 4))[l.boff] >> ((k & 15) + l.g) & 1 ? v : 0.0f;
+    return l.one > 0 ? v : l.one == 0 ? 1.0f : 0.0f;
   }
 };
 
@@ -333,7 +352,15 @@ struct Table {
   __device__ static bf16x8 frag(const uint16_t *lds, int rg, int q16, int g4, int i) {
     return *reinterpret_cast<const bf16x8 *>(lds + i * BR * kRowLd + (rg * 16 + q16) * kRowLd + 8 * g4);
   }
-  __device__ float at(int64_t r, int k) const { return f[least(r, rows - 1) * ldf + k]; }
+  struct Lane {
+    const float *first;  // of rows r .. r + 15, the same in all lanes
+    uint32_t off;
+  };
+  __device__ Lane lane(int64_t r, int q16, int g) const {
+    const int64_t r0 = least(r, rows - 1);
+    return Lane{f + r0 * ldf, (uint32_t)(least(q16, rows - 1 - r0) * ldf + g)};
+  }
+  __device__ float at(int k, const Lane &l) const { return (l.first + k)[l.off]; }
 };
 
 // bfloat16, contiguous along the rows (activations stored in bfloat16; ld and
@@ -509,7 +536,9 @@ __global__ __launch_bounds__(64 * CF::NW, 2) void tile_kernel(AO ao, BO bo, CS c
   const int64_t row0 = m0 + wm * TM * 16;
   const int col0 = n0 + wn * TN * 16;
   if constexpr (P == 3)
-    if (const uint64_t bad = bad_tiles(acc)) redo_tiles<SWAP>(ao, bo, row0, col0, kbeg, kend, bad, acc);
+    if (any_odd(acc))
+      mend_odd<SWAP>(ao, bo, row0, col0, M, N, kbeg, kend, acc,
+                     [&](int, int64_t r, unsigned want) { return nan_rows(ao, r, kbeg, kend, want); });
 #pragma unroll
   for (int j = 0; j < TN; ++j)
 #pragma unroll

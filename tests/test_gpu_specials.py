@@ -74,3 +74,82 @@ def test_weights_beyond_the_parts(layer):
     close(out[0].t(), ref)
     da, _, _ = dl.lsc_bwd_image(plan, ai, Wg, gi, need_weight_grad=False, need_bias_grad=False)
     close(da[0].t(), rda)
+
+
+def sums(x, T):
+    """x @ T^T in float64, every product formed (0 * inf is NaN)."""
+    with np.errstate(invalid="ignore"):
+        return np.stack([(v.astype(np.float64) * T).sum(1) for v in x])
+
+
+def same(out, ref):
+    """float32's specials, and the finite entries to FP32's norm-wise bound."""
+    out = out.double().cpu().numpy().reshape(ref.shape)
+    assert np.array_equal(np.isnan(out), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(out[inf], ref[inf])
+    fin = np.isfinite(ref)
+    if fin.any():
+        assert np.linalg.norm(out[fin] - ref[fin]) <= 1e-5 * np.linalg.norm(ref[fin])
+
+
+@pytest.mark.parametrize("weights", ["finite", "nan"])
+@pytest.mark.parametrize("layer", [(3, 32, 8, 300), (9, 3, 4, 70), (32, 3, 8, 1100), (13, 16, 2, 515)])
+def test_rows_of_nan_among_others(layer, weights):
+    # half of the voxels NaN, whole or in one value, infinities in a few others
+    # and beside NaN, and (weights) an output channel of NaN weights: entries
+    # that are NaN by their operands keep the first result, the rest of the same
+    # tiles is float32's
+    C, O, L, V = layer
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(90), L, L, (8, 8), np.deg2rad(30), 0.006)
+    W = dg.lsc_weights(22, 0, C, O, plan.T)[0].astype(np.float32)
+    if weights == "nan":
+        W[O // 2] = np.nan
+    _, Bnb, Pm = plan.tables()
+    Q = np.einsum("ki,itj->tkj", Pm, Bnb.reshape(plan.m, plan.T, plan.K_in))
+    T = np.einsum("oct,tkj->okcj", W.astype(np.float64), Q).reshape(O * plan.K_out, C * plan.K_in)
+    rng = np.random.default_rng(22)
+    x = {}
+    for name, n in (("a", C * plan.K_in), ("g", O * plan.K_out)):
+        v = rng.standard_normal((V, n)).astype(np.float32)
+        v[1::4] = np.nan
+        v[3::4, n - 1] = np.nan
+        v[V // 2 // 4 * 4, n // 3] = np.inf
+        v[8, 0], v[8, n - 1], v[11, 0], v[V - 1, n // 2] = np.inf, -np.inf, np.inf, -np.inf
+        x[name] = v
+    a, g = x["a"], x["g"]
+    ag, gg, Wg = cuda(a.reshape(V, C, -1)), cuda(g.reshape(V, O, -1)), cuda(W)
+    same(dl.lsc_fwd(plan, ag, Wg, None), sums(a, T))
+    same(dl.lsc_bwd(plan, ag, Wg, gg, need_weight_grad=False, need_bias_grad=False)[0], sums(g, T.T))
+    ai, gi = cuda(a.T[None]), cuda(g.T[None])
+    same(dl.lsc_fwd_image(plan, ai, Wg)[0][0].t().contiguous(), sums(a, T))
+    # masked by ReLU bits that the NaN, infinite and negative outputs leave clear
+    out, bits = dl.lsc_fwd_image(plan, ai, Wg, relu=True, need_bits=True)
+    with np.errstate(invalid="ignore"):
+        gm = np.where(out[0].t().cpu().numpy() > 0, g, np.float32(0.0))
+    da = dl.lsc_bwd_image(plan, ai, Wg, gi, bits, need_weight_grad=False, need_bias_grad=False)[0]
+    same(da[0].t().contiguous(), sums(gm, T.T))
+
+
+@pytest.mark.parametrize("case", [(130, 20, 700), (20, 145, 1500), (3, 2, 40)])
+def test_weight_gradient_specials(case):
+    # order 0: dW[o][c][t] = Q[t] sum_v g[v][o] a[v][c]
+    C, O, V = case
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(12), 0, 0, (6,), np.deg2rad(30), 0.006)
+    _, Bnb, Pm = plan.tables()
+    q = np.einsum("ki,itj->t", Pm, Bnb.reshape(plan.m, plan.T, 1))
+    rng = np.random.default_rng(23)
+    a, g = (rng.standard_normal((V, n)).astype(np.float32) for n in (C, O))
+    a[5, 1], a[30, C - 1], a[V - 1, 0], a[V - 2, 0] = np.nan, np.inf, np.inf, np.inf
+    g[30, 0], g[12, O - 1], g[V - 3, O // 2] = 0.0, np.nan, -np.inf
+    with np.errstate(invalid="ignore"):
+        G = np.stack([(g[:, o, None].astype(np.float64) * a.astype(np.float64)).sum(0) for o in range(O)])
+        ref = G[:, :, None] * q
+        db = g.astype(np.float64).sum(0) * Pm.sum()
+    W = cuda(dg.lsc_weights(23, 0, C, O, plan.T)[0])
+    _, dW, b = dl.lsc_bwd(plan, cuda(a[:, :, None]), W, cuda(g[:, :, None]), need_input_grad=False)
+    same(dW, ref)
+    same(b, db)
+    _, dW, b = dl.lsc_bwd_image(plan, cuda(a.T[None]), W, cuda(g.T[None]), need_input_grad=False)
+    same(dW, ref)
+    same(b, db)
