@@ -2,7 +2,8 @@
 //
 // x = x0 + x1 + x2 with each part the bfloat16 rounding (RNE) of what the
 // parts before it leave, so |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x| and the three
-// hold all 24 bits.  A product takes the six part products above 2^-26 of it
+// hold all 24 bits, down to |x| = 2^-109 (below, x2's lie under bfloat16's
+// smallest number, 2^-133).  A product takes the six part products above 2^-26 of it
 // (kPartA, kPartB); the three left out are below float32's own rounding of
 // the product.  x0 y0 goes to one accumulator and the other five, at most
 // 2^-8 of it, to a second, added at the end: the long sum then has one
@@ -14,11 +15,13 @@
 // Six 16x16x32 bfloat16 instructions take 96 matrix-core cycles per 32 k
 // where eight 16x16x4 float32 ones take 256.
 //
-// Infinities, NaN and values that round to an infinite x0 end as NaN here;
-// kernels look for results that are not finite (any_odd) and compute those
+// Infinities, NaN and values that round to an infinite x0 end as NaN here, and
+// an operand below 2^-109 is off by up to 2^-134.  Kernels look for results
+// that are not finite, or not zero and below 2^-80 (any_odd), and compute those
 // again with the float32 instructions from the values themselves
 // (activations, and the table's beside its parts), so that float32's rules
-// hold.
+// hold.  (A result above 2^-80 is off by less than float32's rounding unless
+// the sum of the factors beside such operands exceeds 2^30.)
 #pragma once
 
 #include "gemm_common.h"
@@ -122,19 +125,29 @@ __device__ __forceinline__ void add_parts(floatx4 (&hi)[TM][TN], const floatx4 (
     for (int j = 0; j < TN; ++j) hi[i][j] += lo[i][j];
 }
 
-// Whether a wave's tiles hold a value that is not finite.
+// Whether a wave's tiles hold a value that is not finite, or not zero and
+// below 2^-80.  Doubled, a value's bits are its magnitude's, and one less than
+// them leaves zero above all others.
+constexpr unsigned kTiny = (127u - 80u) << 24;
 template <int TM, int TN>
 __device__ __forceinline__ bool any_odd(const floatx4 (&acc)[TM][TN]) {
   float z = 0.0f;
+  unsigned least = ~0u;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) z = fmaf(acc[i][j][e], 0.0f, z);
-  return __any(z != z);
+      for (int e = 0; e < 4; ++e) {
+        z = fmaf(acc[i][j][e], 0.0f, z);
+        least = min(least, (__builtin_bit_cast(unsigned, acc[i][j][e]) << 1) - 1u);
+      }
+  return __any(z != z || least < kTiny - 1u);
 }
-__device__ __forceinline__ bool is_odd(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7f800000u) == 0x7f800000u; }
+__device__ __forceinline__ bool not_finite(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7f800000u) == 0x7f800000u; }
+__device__ __forceinline__ bool is_odd(float v) {
+  return not_finite(v) || (__builtin_bit_cast(unsigned, v) << 1) - 1u < kTiny - 1u;
+}
 
 // The slow path reads its operands from global memory, 16 rows of four k at a
 // time: op.at(k, l) is the value of lane (q16, g4) of rows r .. r + 15 at
@@ -240,7 +253,7 @@ __device__ __forceinline__ unsigned wave_or(unsigned x) {
 }
 
 // Values of a wave's tiles that the parts may have got wrong, again in float32:
-// every one that is not finite, unless a NaN in its row or column (rows below
+// every one below 2^-80, and every one that is not finite, unless a NaN in its row or column (rows below
 // M, N) makes it NaN anyway.  Data with a background of NaN rows are ordinary
 // (a division by a b = 0 signal of zero), so those cost a look at the rows;
 // infinities cost a second, slower product of their 16 rows.  a_nan(i, r, want):
@@ -256,7 +269,7 @@ __device__ __forceinline__ void mend_odd(const AO &ao, const BO &bo, int64_t ra,
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int64_t r = ra + 16 * i;
-    unsigned odd[TN], rows = 0, any = 0;  // odd: the lane's values, four bits a tile; rows: theirs among the 16
+    unsigned odd[TN], rows = 0, any = 0;  // odd: the lane's values, four bits a tile; rows: the 16 with one not finite
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       odd[j] = 0;
@@ -265,12 +278,14 @@ __device__ __forceinline__ void mend_odd(const AO &ao, const BO &bo, int64_t ra,
         const int x = SWAP ? 4 * g4 + e : q16, y = 16 * j + (SWAP ? q16 : 4 * g4 + e);
         const bool o = is_odd(acc[i][j][e]) && r + x < M && rb + y < N;
         odd[j] |= (o ? 1u : 0u) << e;
-        rows |= (o ? 1u : 0u) << x;
+        any |= o ? 1u : 0u;
+        rows |= (o && not_finite(acc[i][j][e]) ? 1u : 0u) << x;
       }
     }
+    if (!__any(any)) continue;
     rows = wave_or(rows);
-    if (!rows) continue;
-    const unsigned na = a_nan(i, r, rows);
+    const unsigned na = rows ? a_nan(i, r, rows) : 0u;
+    any = 0;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       odd[j] &= SWAP ? ~(na >> (4 * g4)) : (na >> q16 & 1 ? 0u : ~0u);

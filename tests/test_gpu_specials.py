@@ -153,3 +153,72 @@ def test_weight_gradient_specials(case):
     _, dW, b = dl.lsc_bwd_image(plan, cuda(a.T[None]), W, cuda(g.T[None]), need_input_grad=False)
     same(dW, ref)
     same(b, db)
+
+
+@pytest.mark.parametrize("scale", [-90, -112, -120, -124])
+@pytest.mark.parametrize("layer", [(3, 32, 8, 130), (9, 3, 4, 70), (32, 3, 8, 300)])
+def test_values_below_the_parts(layer, scale):
+    # operands whose third part lies under bfloat16's smallest number: the
+    # bound is float32's, sqrt(K) / 2 roundings of 2^-24 of products that add up
+    # at random (K up to 1440: 1.1e-6), and below 2^-121 the operand's spacing,
+    # 2^-149, against its scale
+    C, O, L, V = layer
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(90), L, L, (8, 8), np.deg2rad(30), 0.006)
+    W = dg.lsc_weights(24, 0, C, O, plan.T)[0].astype(np.float32)
+    _, Bnb, Pm = plan.tables()
+    Q = np.einsum("ki,itj->tkj", Pm, Bnb.reshape(plan.m, plan.T, plan.K_in))
+    rng = np.random.default_rng(24)
+    s = 2.0 ** scale
+    a, g = (rng.standard_normal((V, n)).astype(np.float32) for n in (C * plan.K_in, O * plan.K_out))
+    at, gt = ((x.astype(np.float64) * s).astype(np.float32) for x in (a, g))
+    a[::3], at[::3] = 0.0, 0.0  # zeros stay zeros
+    tol = 1.1e-6 + 2.0 ** (-149 - scale)
+
+    def close(out, ref):
+        out = out.double().cpu().numpy().reshape(ref.shape) / s
+        ref = ref / s
+        assert np.linalg.norm(out - ref) <= tol * np.linalg.norm(ref)
+
+    def grads(x, y):
+        G = (y.astype(np.float64).T @ x.astype(np.float64)).reshape(O, plan.K_out, C, plan.K_in)
+        return np.einsum("okcj,tkj->oct", G, Q)
+
+    T = np.einsum("oct,tkj->okcj", W.astype(np.float64), Q).reshape(O * plan.K_out, C * plan.K_in)
+    ac, gc, Wc = cuda(a.reshape(V, C, -1)), cuda(g.reshape(V, O, -1)), cuda(W)
+    atc, gtc = cuda(at.reshape(V, C, -1)), cuda(gt.reshape(V, O, -1))
+    close(dl.lsc_fwd(plan, atc, Wc, None), at.astype(np.float64) @ T.T)
+    da, dW, _ = dl.lsc_bwd(plan, ac, Wc, gtc)
+    close(da, gt.astype(np.float64) @ T)
+    close(dW, grads(a, gt))
+    close(dl.lsc_bwd(plan, atc, Wc, gc)[1], grads(at, g))
+    out = dl.lsc_fwd_image(plan, cuda(at.T[None]), Wc)[0]
+    close(out[0].t().contiguous(), at.astype(np.float64) @ T.T)
+    da, dW, _ = dl.lsc_bwd_image(plan, cuda(a.T[None]), Wc, cuda(gt.T[None]))
+    close(da[0].t().contiguous(), gt.astype(np.float64) @ T)
+    close(dW, grads(a, gt))
+
+
+@pytest.mark.parametrize("scale", [-90, -108, -118])
+@pytest.mark.parametrize("layer", [(3, 32, 8, 130), (9, 3, 4, 70), (32, 3, 8, 300)])
+def test_weights_below_the_parts(layer, scale):
+    # the same of the weights: float32's roundings as above, and those of the
+    # folded entries, sums of T products that each round to the float32 grid,
+    # 2^-149 at the finest, against their root mean square
+    C, O, L, V = layer
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(90), L, L, (8, 8), np.deg2rad(30), 0.006)
+    s = 2.0 ** scale
+    W = (dg.lsc_weights(25, 0, C, O, plan.T)[0].astype(np.float64) * s).astype(np.float32)
+    _, Bnb, Pm = plan.tables()
+    Q = np.einsum("ki,itj->tkj", Pm, Bnb.reshape(plan.m, plan.T, plan.K_in))
+    T = np.einsum("oct,tkj->okcj", W.astype(np.float64) / s, Q).reshape(O * plan.K_out, C * plan.K_in)
+    tol = 1.1e-6 + np.sqrt(plan.T) * 2.0 ** (-149 - scale) / np.sqrt(np.mean(T ** 2))
+    rng = np.random.default_rng(25)
+    a, g = (rng.standard_normal((V, n)).astype(np.float32) for n in (C * plan.K_in, O * plan.K_out))
+    a[::3] = 0.0
+    ac, gc, Wc = cuda(a.reshape(V, C, -1)), cuda(g.reshape(V, O, -1)), cuda(W)
+    da = dl.lsc_bwd(plan, ac, Wc, gc, need_weight_grad=False, need_bias_grad=False)[0]
+    im = dl.lsc_fwd_image(plan, cuda(a.T[None]), Wc)[0][0].t().contiguous()
+    for out, ref in ((dl.lsc_fwd(plan, ac, Wc, None), a.astype(np.float64) @ T.T), (da, g.astype(np.float64) @ T),
+                     (im, a.astype(np.float64) @ T.T)):
+        out = out.double().cpu().numpy().reshape(ref.shape) / s
+        assert np.linalg.norm(out - ref) <= tol * np.linalg.norm(ref)
