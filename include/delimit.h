@@ -220,7 +220,9 @@ void dlm_lsc_plan_destroy(dlm_lsc_plan *plan);
  * output channels.  DLM_LSC_RESAMPLE: for `V_chunk` voxels per pass; a call
  * given fewer bytes than needed for its V processes the voxels in several
  * passes, the minimum being one 64-voxel pass (less -> DLM_EWORKSPACE).
- * DLM_LSC_FOLDED: independent of V_chunk. */
+ * DLM_LSC_FOLDED: independent of V_chunk.  A workspace may start at any
+ * multiple of 4 bytes; the folded form is fastest from a multiple of 16, and
+ * bfloat16 activations, ReLU bits and images need one (DLM_EINVAL otherwise). */
 dlm_status dlm_lsc_workspace_bytes(const dlm_lsc_plan *plan, int C, int O, int64_t V_chunk,
                                    dlm_lsc_form form, dlm_precision prec, size_t *bytes);
 
@@ -298,7 +300,7 @@ int dlm_sh_image_supported(const dlm_sh_plan *plan, int64_t B, int64_t P);
 dlm_status dlm_sh_image(const dlm_sh_plan *plan, dlm_sh_op op, const float *in, float *out, int64_t B,
                         int64_t P, dlm_precision prec, void *stream);
 /* The folded LSC layer and its adjoint on images; workspace as for the folded
- * form.  relu_bits: NULL, or (needs fuse_relu) a device array of uint16
+ * form, 16-byte aligned (DLM_EINVAL otherwise).  relu_bits: NULL, or (needs fuse_relu) a device array of uint16
  * [B][O*K_out][(P+15)/16] whose bit v % 16 of word [..][v / 16] the forward
  * sets to 1 iff the output there is > 0; the backward masks da_out by it (the
  * gradient of a layer whose forward fused a ReLU). */

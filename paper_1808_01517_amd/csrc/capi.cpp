@@ -1236,6 +1236,13 @@ dlm_status image_check(int64_t B, int64_t P) {
                 (long long)P);
   return DLM_OK;
 }
+
+dlm_status image_ws_check(const dlm_lsc_plan *p, int C, int O, const void *ws, size_t ws_bytes) {
+  if (ws_bytes < fold_ws_need(p, C, O))
+    return fail(DLM_EWORKSPACE, "workspace of %zu bytes is below the %zu-byte minimum", ws_bytes, fold_ws_need(p, C, O));
+  if (!aligned16p(ws)) return fail(DLM_EINVAL, "images need a 16-byte aligned workspace");
+  return DLM_OK;
+}
 }  // namespace
 
 int dlm_sh_image_supported(const dlm_sh_plan *p, int64_t B, int64_t P) {
@@ -1292,8 +1299,7 @@ dlm_status dlm_lsc_fwd_image(const dlm_lsc_plan *p, const float *a_in, int C, co
   if ((s = image_check(B, P)) != DLM_OK) return s;
   if (relu_bits && !fuse_relu) return fail(DLM_EINVAL, "ReLU bits need fuse_relu");
   if (!a_in || !W || !a_out || !ws) return fail(DLM_EINVAL, "null device pointer");
-  if (ws_bytes < fold_ws_need(p, C, O))
-    return fail(DLM_EWORKSPACE, "workspace of %zu bytes is below the %zu-byte minimum", ws_bytes, fold_ws_need(p, C, O));
+  if ((s = image_ws_check(p, C, O, ws, ws_bytes)) != DLM_OK) return s;
   FoldWs w = fold_ws_carve(p, C, O, ws);
   if ((s = fold_weights(p, C, O, W, bias, w, false, false, prec, stream)) != DLM_OK) return s;
   ImageGemm x;
@@ -1325,8 +1331,7 @@ dlm_status dlm_lsc_bwd_image(const dlm_lsc_plan *p, const float *a_in, int C, co
   if ((s = image_check(B, P)) != DLM_OK) return s;
   if (dbias && !dW) return fail(DLM_EINVAL, "dbias without dW is not supported");
   if (!a_in || !W || !da_out || !ws) return fail(DLM_EINVAL, "null device pointer");
-  if (ws_bytes < fold_ws_need(p, C, O))
-    return fail(DLM_EWORKSPACE, "workspace of %zu bytes is below the %zu-byte minimum", ws_bytes, fold_ws_need(p, C, O));
+  if ((s = image_ws_check(p, C, O, ws, ws_bytes)) != DLM_OK) return s;
   FoldWs w = fold_ws_carve(p, C, O, ws);
   const int M = O * p->K_out, CK = C * p->K_in;
   const double V = double(B) * double(P), bits = relu_bits ? M / 8.0 : 0.0;

@@ -56,3 +56,30 @@ def test_folded_calls_at_any_dword(layer, offset, prec):
             check("da", da, da_ref * (a > 0) if relu_in else da_ref, prec)
             check("dW", dW, dW_ref, prec, kind="sum")
             check("db", db, db_ref, prec, kind="sum")
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_images_and_bits_refuse_before_any_launch(prec):
+    C, O, P = 2, 16, 40
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(30), 2, 2, (6,), np.deg2rad(30), 0.006)
+    L, code = dl.lib(), dl.precision_code(prec)
+    gen = torch.Generator(device=DEV).manual_seed(13)
+    a, g = (torch.randn(1, n * plan.K_in, P, device=DEV, generator=gen) for n in (C, O))
+    W = torch.randn(O, C, plan.T, device=DEV, generator=gen)
+    out, da, dW = torch.zeros_like(g), torch.zeros_like(a), torch.zeros_like(W)
+    bits = torch.zeros((P, O * plan.K_out // 16), dtype=torch.int16, device=DEV)
+    ws = workspace_at(plan, C, O, prec, 4)
+    ws.buf.zero_()
+    st = torch.cuda.current_stream().cuda_stream
+    calls = [
+        L.dlm_lsc_fwd_image(plan.handle, a.data_ptr(), C, W.data_ptr(), None, O, out.data_ptr(), 1, P, 0, None, ws.ptr(),
+                            ws.nbytes, code, st),
+        L.dlm_lsc_bwd_image(plan.handle, a.data_ptr(), C, W.data_ptr(), O, None, g.data_ptr(), da.data_ptr(),
+                            dW.data_ptr(), None, 1, P, ws.ptr(), ws.nbytes, code, st),
+        L.dlm_lsc_fwd_io(plan.handle, a.data_ptr(), C, W.data_ptr(), None, O, out.data_ptr(), P, 1, 0, bits.data_ptr(),
+                         dl.form_code("folded"), ws.ptr(), ws.nbytes, code, st),
+    ]
+    torch.cuda.synchronize()
+    assert calls == [dl._lib.DLM_EINVAL] * 3
+    for t in (out, da, dW, bits, ws.buf):
+        assert not t.any()
