@@ -303,7 +303,8 @@ dlm_status dlm_sh_image(const dlm_sh_plan *plan, dlm_sh_op op, const float *in, 
  * form, 16-byte aligned (DLM_EINVAL otherwise).  relu_bits: NULL, or (needs fuse_relu) a device array of uint16
  * [B][O*K_out][(P+15)/16] whose bit v % 16 of word [..][v / 16] the forward
  * sets to 1 iff the output there is > 0; the backward masks da_out by it (the
- * gradient of a layer whose forward fused a ReLU). */
+ * gradient of a layer whose forward fused a ReLU) and may be given no a_in
+ * where it makes no dW. */
 dlm_status dlm_lsc_fwd_image(const dlm_lsc_plan *plan, const float *a_in, int C, const float *W,
                              const float *bias, int O, float *a_out, int64_t B, int64_t P, int fuse_relu,
                              uint16_t *relu_bits, void *ws, size_t ws_bytes, dlm_precision prec, void *stream);

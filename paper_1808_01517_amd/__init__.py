@@ -460,22 +460,34 @@ def lsc_fwd_image(plan: LSCPlan, a: torch.Tensor, W: torch.Tensor, bias=None, re
     return out, bits
 
 
-def lsc_bwd_image(plan: LSCPlan, a: torch.Tensor, W: torch.Tensor, g: torch.Tensor, bits=None, need_input_grad=True,
+def lsc_bwd_image(plan: LSCPlan, a, W: torch.Tensor, g: torch.Tensor, bits=None, need_input_grad=True,
                   need_weight_grad=True, need_bias_grad=True, precision="fp32"):
     """(da_in or None, dW [O][C][T] or None, dbias [O] or None) of lsc_fwd_image
-    for the output gradient g, masked by the forward's ReLU bits."""
-    a, g = _f32_dev(a, "a_in"), _f32_dev(g, "da_out")
+    for the output gradient g, masked by the forward's ReLU bits.  The input a
+    may be None where neither dW nor dbias is wanted."""
+    g = _f32_dev(g, "da_out")
     W = _f32_dev(W, "W").reshape(W.shape[0], W.shape[1], -1)
     O, Cin, _ = W.shape
-    prec = precision_code(precision)
-    B, P = a.shape[0], a.shape[2:].numel()
-    ws = _default_ws(plan, Cin, O, B * P, prec, a.device, "folded")
-    da = torch.empty_like(a) if need_input_grad else None
     need_dW = need_weight_grad or need_bias_grad
-    dW = torch.empty((O, Cin, plan.T), dtype=torch.float32, device=a.device) if need_dW else None
-    db = torch.empty((O,), dtype=torch.float32, device=a.device) if need_bias_grad else None
+    if a is not None:
+        a = _f32_dev(a, "a_in")
+    elif need_dW:
+        raise ValueError("a_in is needed for dW and dbias")
+    prec = precision_code(precision)
+    B, P, dev = g.shape[0], g.shape[2:].numel(), g.device
+    if g.dim() < 3 or g.shape[1] != O * plan.K_out or W.shape[2] != plan.T or \
+            (a is not None and tuple(a.shape) != (B, Cin * plan.K_in, *g.shape[2:])):
+        raise ValueError(f"shapes: a_in {None if a is None else tuple(a.shape)}, da_out {tuple(g.shape)}, "
+                         f"W {tuple(W.shape)}, plan K_in={plan.K_in} K_out={plan.K_out} T={plan.T}")
+    if bits is not None and (bits.dtype != torch.int16 or not bits.is_cuda or not bits.is_contiguous() or
+                             tuple(bits.shape) != (B, g.shape[1], (P + 15) // 16)):
+        raise ValueError(f"bits must be a contiguous int16 device tensor of shape {(B, g.shape[1], (P + 15) // 16)}")
+    ws = _default_ws(plan, Cin, O, B * P, prec, dev, "folded")
+    da = torch.empty((B, Cin * plan.K_in, *g.shape[2:]), dtype=torch.float32, device=dev) if need_input_grad else None
+    dW = torch.empty((O, Cin, plan.T), dtype=torch.float32, device=dev) if need_dW else None
+    db = torch.empty((O,), dtype=torch.float32, device=dev) if need_bias_grad else None
     check(lib().dlm_lsc_bwd_image(plan.handle, _ptr(a), Cin, _ptr(W), O, _ptr(bits), _ptr(g), _ptr(da), _ptr(dW),
-                                  _ptr(db), B, P, ws.ptr(), ws.nbytes, prec, _stream(a)))
+                                  _ptr(db), B, P, ws.ptr(), ws.nbytes, prec, _stream(g)))
     return da, (dW if need_weight_grad else None), db
 
 

@@ -1330,7 +1330,7 @@ dlm_status dlm_lsc_bwd_image(const dlm_lsc_plan *p, const float *a_in, int C, co
   if (s != DLM_OK) return s;
   if ((s = image_check(B, P)) != DLM_OK) return s;
   if (dbias && !dW) return fail(DLM_EINVAL, "dbias without dW is not supported");
-  if (!a_in || !W || !da_out || !ws) return fail(DLM_EINVAL, "null device pointer");
+  if ((!a_in && dW) || !W || !da_out || !ws) return fail(DLM_EINVAL, "null device pointer");
   if ((s = image_ws_check(p, C, O, ws, ws_bytes)) != DLM_OK) return s;
   FoldWs w = fold_ws_carve(p, C, O, ws);
   const int M = O * p->K_out, CK = C * p->K_in;

@@ -74,8 +74,9 @@ class _LSCImageFn(torch.autograd.Function):
             ctx.plan, ctx.precision = plan, precision
             ctx.has_bias = b is not None
             # a copy, as the voxel-major form keeps one: the caller may change
-            # its input (and the output) before the backward
-            ctx.save_for_backward(a.clone() if ctx.needs_input_grad[1] or ctx.needs_input_grad[2] else a, W, bits)
+            # its input (and the output) before the backward; only the weight
+            # and bias gradients read it
+            ctx.save_for_backward(a.clone() if ctx.needs_input_grad[1] or ctx.needs_input_grad[2] else None, W, bits)
         return out
 
     @staticmethod
