@@ -101,6 +101,11 @@ struct Runs {
 // and read one word per MFMA.  Both use the same k order inside a 16-wide
 // slice: MFMA j of 4 takes k = 4*(lane/16) + j, which is a permutation of
 // the reduction index applied identically to A and B.
+// Outputs whose sums are taken in pieces: those of every 128 k are added up on
+// their own, so that a long sum's roundings are those of a short one.
+template <class CS>
+constexpr bool kSumPieces = false;
+
 template <int OP, class CF, class AL, class BL, class CS>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(AL al, BL bl, CS cs, int64_t M, int N, int K, int ksplit,
                                                        int nbM, int nbN, int nz) {
@@ -167,11 +172,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(AL al, BL bl, CS cs, int6
       }
     }
   };
-  floatx4 acc[CF::TM][CF::TN];
+  constexpr bool kPieces = kSumPieces<CS>;
+  floatx4 acc[CF::TM][CF::TN], sum[kPieces ? CF::TM : 1][CF::TN];
 #pragma unroll
   for (int i = 0; i < CF::TM; ++i)
 #pragma unroll
-    for (int j = 0; j < CF::TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < CF::TN; ++j) {
+      acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (kPieces) sum[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
 
   const int niter = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
   if (niter > 0) {
@@ -179,7 +188,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(AL al, BL bl, CS cs, int6
     stash(0);
     __syncthreads();
   }
-  for (int it = 0; it < niter; ++it) {
+  auto step = [&](int it) {
     const int cur = it & 1;
     if (it + 1 < niter) load(kbeg + (it + 1) * BK);
     const float *Ac = As[cur];
@@ -208,6 +217,26 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(AL al, BL bl, CS cs, int6
           acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[jn][j], a[i][j], acc[i][jn], 0, 0, 0);
     if (it + 1 < niter) stash(cur ^ 1);
     __syncthreads();
+  };
+  if constexpr (kPieces) {
+    for (int it = 0; it < niter;) {
+      const int end = min(it + 128 / BK, niter);
+#pragma unroll 1
+      for (; it < end; ++it) step(it);
+#pragma unroll
+      for (int i = 0; i < CF::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < CF::TN; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < CF::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < CF::TN; ++j) acc[i][j] = sum[i][j];
+  } else {
+    for (int it = 0; it < niter; ++it) step(it);
   }
   // The MFMAs take the B fragment as their first operand, so each 16 x 16
   // accumulator is the transposed tile: lane l holds row m = l % 16 and the
@@ -817,6 +846,12 @@ struct CRowBias {
     st4(y + r * m + n, v);
   }
 };
+
+// T K entries are summed here (765 at order 8, 17 taps) where the paper's order
+// sums C T (544 of 32 channels): in one piece its error against 64 bits was
+// 3.9e-7 where that order has 3.4e-7.
+template <>
+constexpr bool kSumPieces<CRowBias> = true;
 
 // Element (n, k) of a row-contiguous table at B[k ld + n].
 struct BTableT {

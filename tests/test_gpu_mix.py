@@ -57,3 +57,21 @@ def test_mixed_order_matches_oracle(case, relu_in):
                                 need_input_grad=False, need_bias_grad=False)
         assert da is None and db is None
         check("dW alone", dW, dW_ref, "fp32", kind="sum")
+
+
+@pytest.mark.parametrize("case", [(32, 3), (16, 16), (9, 1)])
+def test_mixed_order_is_as_close_as_the_papers(case):
+    # With u = 2^-24 / sqrt(3) the rounding of one sum, a running sum of n equal
+    # terms, four to a rounding, is off by u sqrt(n / 8).  T K = 765 of them in
+    # pieces of 128: 1.5e-7 (in one piece 3.4e-7); with the sum over the channels
+    # and the refit's 90 2.0e-7 (3.6e-7).  The bound is between; the paper's order,
+    # with sums over 45, C T and 90 entries, measured 2.2e-7 to 3.4e-7.
+    C, O = case
+    g = dg.fibonacci_hemisphere(90)
+    plan = dl.LSCPlan(g, 8, 8, (8, 8), np.deg2rad(30), 0.006)
+    oplan = olsc.LSCPlan(g, 8, 8, (8, 8), np.deg2rad(30), 0.006)
+    W, b = (x.astype(np.float32).astype(np.float64) for x in dg.lsc_weights(9, 0, C, O, plan.T))
+    a = np.random.default_rng(9).standard_normal((300, C, plan.K_in)).astype(np.float32).astype(np.float64)
+    ref = olsc.lsc_forward(oplan, a, W, b, False)[0]
+    out = dl.lsc_fwd(plan, cuda(a), cuda(W), cuda(b), form="resample").double().cpu().numpy()
+    assert np.linalg.norm(out - ref) <= 2.8e-7 * np.linalg.norm(ref)
