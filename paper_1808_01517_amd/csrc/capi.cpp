@@ -944,8 +944,9 @@ bool lsc_mix_first(const dlm_lsc_plan *p, int C, int O, dlm_precision prec) {
 // Largest chunk (multiple of kMinChunk unless V is smaller) whose workspace fits.
 int64_t lsc_chunk(const dlm_lsc_plan *p, int C, int O, int64_t V, size_t ws_bytes) {
   int64_t hi = std::max<int64_t>(V, 1);
-  // keep (chunk * m) within int range for the reduction index
-  hi = std::min<int64_t>(hi, (int64_t(1) << 30) / std::max<int64_t>(p->m, 1));
+  // keep (chunk * m) within int range for the reduction index, and (chunk * O)
+  // for the rows (voxel, output channel)
+  hi = std::min<int64_t>(hi, (int64_t(1) << 30) / std::max<int64_t>(p->m, O));
   if (lsc_ws_need(p, C, O, hi) <= ws_bytes) return hi;
   int64_t lo = std::min<int64_t>(V, kMinChunk);
   if (lsc_ws_need(p, C, O, lo) > ws_bytes) return 0;

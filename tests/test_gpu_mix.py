@@ -75,3 +75,20 @@ def test_mixed_order_is_as_close_as_the_papers(case):
     ref = olsc.lsc_forward(oplan, a, W, b, False)[0]
     out = dl.lsc_fwd(plan, cuda(a), cuda(W), cuda(b), form="resample").double().cpu().numpy()
     assert np.linalg.norm(out - ref) <= 2.8e-7 * np.linalg.norm(ref)
+
+
+def test_rows_beyond_32_bits():
+    # 2^31 rows (voxel, output channel) in one workspace: the call takes them in passes
+    C, O = 128, 256
+    V = 2 ** 31 // O + 5
+    g = dg.fibonacci_hemisphere(3)
+    plan = dl.LSCPlan(g, 0, 0, (2,), np.deg2rad(30), 0.006)
+    W, b = (x.astype(np.float32).astype(np.float64) for x in dg.lsc_weights(10, 0, C, O, plan.T))
+    gen = torch.Generator(device=DEV).manual_seed(10)
+    a = torch.randn(V, C, 1, device=DEV, generator=gen)
+    ws = dl.Workspace(dl.lsc_workspace_bytes(plan, C, O, V, "fp32", "resample"), DEV)
+    out = dl.lsc_fwd(plan, a, cuda(W), cuda(b), form="resample", workspace=ws)
+    rows = [0, 1, V // 2, 2 ** 30 // O - 1, 2 ** 30 // O, V - 2, V - 1]
+    oplan = olsc.LSCPlan(g, 0, 0, (2,), np.deg2rad(30), 0.006)
+    ref = olsc.lsc_forward(oplan, a[rows].double().cpu().numpy(), W, b, False)[0]
+    check("out", out[rows], ref, "fp32")
