@@ -37,18 +37,27 @@ _PRECISIONS = {DLM_FP32: DLM_FP32, "fp32": DLM_FP32, "f32": DLM_FP32, torch.floa
                DLM_BF16: DLM_BF16, "bf16": DLM_BF16, torch.bfloat16: DLM_BF16}
 
 
+def _code(table: dict, x, what: str) -> int:
+    """The code of a value that is no key itself but may equal one (a
+    zero-dimensional tensor, an array of one number)."""
+    for key, code in table.items():
+        if key == x:
+            return code
+    raise ValueError(f"unknown {what} {x!r}")
+
+
 def form_code(f) -> int:
     try:
         return _FORMS[f]
     except (KeyError, TypeError):
-        raise ValueError(f"unknown LSC form {f!r}") from None
+        return _code(_FORMS, f, "LSC form")
 
 
 def precision_code(p) -> int:
     try:
         return _PRECISIONS[p]
     except (KeyError, TypeError):
-        raise ValueError(f"unknown precision {p!r}") from None
+        return _code(_PRECISIONS, p, "precision")
 
 
 # The raw handle of a device's current stream (a Stream object for it costs
