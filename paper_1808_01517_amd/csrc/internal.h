@@ -49,7 +49,6 @@ enum KernelOp : int {
   kOpContractFwd,
   kOpContractBwdData,
   kOpContractBwdWeight,
-  kOpFoldMake,
   kOpFoldFwd,
   kOpFoldBwdData,
   kOpFoldGrad,
@@ -102,7 +101,7 @@ inline bool stream_table_only(const TableGemm &g) {
   return g.Ah || g.Ch || g.out_mask_h || g.relu_bits_out || g.relu_bits_in;
 }
 int launch_stream_table(const TableGemm &g, dlm_precision prec, void *stream);
-// Weight gradient of the folded form over voxel slices of ksplit voxels:
+// Weight gradient of the folded form over `splits` slices of the voxels:
 // partial[s][m][n] = sum_v g[v][m] a[v][n], with a ones column at n = CK (the
 // bias).  g / a as float32, or (BF16 only) as bfloat16 gh / ah (M, CK
 // multiples of 8, 16-byte aligned); the other pointer of each pair is null.

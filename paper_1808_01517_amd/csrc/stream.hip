@@ -89,15 +89,14 @@ __device__ __forceinline__ bf16x8 to_bf16x8(floatx4 lo, floatx4 hi) {
 // (q16, g4): row rg*16 + q16, k = 8*g4 .. 8*g4 + 7.
 
 // k-contiguous float32: element (r, k) at p[r * ld + k], valid for r < rows,
-// k < kend.  LDS: [BR][32] floats, 4-float chunk c of row r stored at chunk
-// c ^ (r & 7).  VEC (16-byte lanes) needs 16-byte aligned rows and kend % 4
+// k < K.  LDS: [BR][32] floats, 4-float chunk c of row r stored at chunk
+// c ^ (r & 7).  VEC (16-byte lanes) needs 16-byte aligned rows and K % 4
 // == 0, so a chunk lies wholly inside or wholly beyond the range.
 template <bool VEC>
 struct SKc {
   const float *p;
   int64_t ld, rows;
   static constexpr int kUnit = VEC ? 16 : 4;
-  static constexpr bool kOnes = false;
   template <int BR>
   static constexpr int bytes() { return BR * SBK * 4; }
   template <int BR>
@@ -126,7 +125,6 @@ struct SKc {
     if constexpr (VEC) return ((s & 7) ^ ((s >> 3) & 7)) << 2;
     else return ((((s >> 2) & 7) ^ ((s >> 5) & 7)) << 2) | (s & 3);
   }
-  __device__ void bind(int64_t) {}
   template <int BR>
   __device__ bf16x8 frag(const char *lds, int rg, int q16, int g4) const {
     const int r = rg * 16 + q16;
@@ -161,7 +159,6 @@ struct SKh {
   const uint16_t *p;
   int64_t ldp, rows;
   static constexpr int kUnit = 16;
-  static constexpr bool kOnes = false;
   template <int BR>
   static constexpr int bytes() { return BR * SBK * 2; }
   template <int BR>
@@ -178,7 +175,6 @@ struct SKh {
   // the table is zero-padded to a whole stage: no copy lies beyond the range
   template <int BR>
   __device__ static int k_of(int) { return 0; }
-  __device__ void bind(int64_t) {}
   template <int BR>
   __device__ bf16x8 frag(const char *lds, int rg, int q16, int g4) const {
     const int r = rg * 16 + q16;
@@ -194,7 +190,6 @@ struct SK3 {
   const float *f;  // the values, rows of ldf
   int64_t ldf;
   static constexpr int kUnit = 16;
-  static constexpr bool kOnes = false;
   template <int BR>
   static constexpr int bytes() { return 3 * BR * SBK * 2; }
   template <int BR>
@@ -211,7 +206,6 @@ struct SK3 {
   }
   template <int BR>
   __device__ static int k_of(int) { return 0; }
-  __device__ void bind(int64_t) {}
   template <int BR>
   __device__ void frag3(const char *lds, int rg, int q16, int g4, bf16x8 (&v)[3]) const {
     const int r = rg * 16 + q16;
@@ -225,8 +219,8 @@ struct SK3 {
 };
 
 // bfloat16 k-contiguous rows (activations stored in bfloat16): element
-// (r, k) at p[r * ldp + k], valid for r < rows, k < kend; ldp a multiple of 8
-// with 16-byte aligned rows and kend a multiple of 8, so a 16-byte chunk
+// (r, k) at p[r * ldp + k], valid for r < rows, k < K; ldp a multiple of 8
+// with 16-byte aligned rows and K a multiple of 8, so a 16-byte chunk
 // (8 k) lies wholly inside or wholly beyond the range.  LDS as SKh.
 struct SKb : SKh {
   template <int BR>
@@ -293,7 +287,7 @@ struct SidePre {
 
 template <class CF, class CS>
 __device__ __forceinline__ void load_side(const CS &cs, SidePre<CF, CS> &sp, int64_t M, int N, int64_t m0, int n0,
-                                          int wm, int wn, int q16, int g4, int z) {
+                                          int wm, int wn, int q16, int g4) {
 #pragma unroll
   for (int j = 0; j < CF::TN; ++j) {
     const int n = n0 + (wn * CF::TN + j) * 16 + 4 * g4;
@@ -305,7 +299,7 @@ __device__ __forceinline__ void load_side(const CS &cs, SidePre<CF, CS> &sp, int
 #pragma unroll
     for (int j = 0; j < CF::TN; ++j) {
       const int n = n0 + (wn * CF::TN + j) * 16 + 4 * g4;
-      sp.em[i][j] = r < M && n + 3 < N ? cs.elside(r, n, z) : floatx4{0.f, 0.f, 0.f, 0.f};
+      sp.em[i][j] = r < M && n + 3 < N ? cs.elside(r, n, 0) : floatx4{0.f, 0.f, 0.f, 0.f};
     }
   }
 }
@@ -314,7 +308,7 @@ __device__ __forceinline__ void load_side(const CS &cs, SidePre<CF, CS> &sp, int
 // + q16 and columns n0 + (wn*TN+j)*16 + 4 g4 .. + 3 of tile (i, j).
 template <class CF, class CS>
 __device__ __forceinline__ void store_tiles(const CS &cs, const floatx4 (&acc)[CF::TM][CF::TN], int64_t M, int N,
-                                            int64_t m0, int n0, int wm, int wn, int q16, int g4, int z,
+                                            int64_t m0, int n0, int wm, int wn, int q16, int g4,
                                             const SidePre<CF, CS> &sp) {
   if constexpr (SidePre<CF, CS>::kOn) {
 #pragma unroll
@@ -325,10 +319,10 @@ __device__ __forceinline__ void store_tiles(const CS &cs, const floatx4 (&acc)[C
       for (int j = 0; j < CF::TN; ++j) {
         const int n = n0 + (wn * CF::TN + j) * 16 + 4 * g4;
         if (n + 3 < N) {
-          cs.store4s(r, n, z, acc[i][j], sp.cb[j], sp.em[i][j]);
+          cs.store4s(r, n, 0, acc[i][j], sp.cb[j], sp.em[i][j]);
         } else {
           for (int q = 0; q < 4; ++q)
-            if (n + q < N) cs(r, n + q, z, acc[i][j][q]);
+            if (n + q < N) cs(r, n + q, 0, acc[i][j][q]);
         }
       }
     }
@@ -351,7 +345,7 @@ __device__ __forceinline__ void store_tiles(const CS &cs, const floatx4 (&acc)[C
 #pragma unroll
         for (int j = 0; j < CF::TN; ++j) {
           const int n = n0 + (wn * CF::TN + j) * 16 + 4 * g4;
-          em[ii][j] = i0 + ii < CF::TM && r < M && n + 3 < N ? cs.elside(r, n, z) : floatx4{0.f, 0.f, 0.f, 0.f};
+          em[ii][j] = i0 + ii < CF::TM && r < M && n + 3 < N ? cs.elside(r, n, 0) : floatx4{0.f, 0.f, 0.f, 0.f};
         }
       }
       // Let the side loads land before the first store.  Without this the
@@ -368,10 +362,10 @@ __device__ __forceinline__ void store_tiles(const CS &cs, const floatx4 (&acc)[C
         auto one = [&](int j) {
           const int n = n0 + (wn * CF::TN + j) * 16 + 4 * g4;
           if (n + 3 < N) {
-            cs.store4s(r, n, z, acc[i][j], cb[j], em[ii][j]);
+            cs.store4s(r, n, 0, acc[i][j], cb[j], em[ii][j]);
           } else {
             for (int q = 0; q < 4; ++q)
-              if (n + q < N) cs(r, n + q, z, acc[i][j][q]);
+              if (n + q < N) cs(r, n + q, 0, acc[i][j][q]);
           }
         };
         if constexpr (CS::kPair) {
@@ -404,17 +398,17 @@ __device__ __forceinline__ void store_tiles(const CS &cs, const floatx4 (&acc)[C
       for (int j = 0; j < CF::TN; ++j) {
         const int n = n0 + (wn * CF::TN + j) * 16 + 4 * g4;
         if (n + 3 < N) {
-          cs.store4(r, n, z, acc[i][j]);
+          cs.store4(r, n, 0, acc[i][j]);
         } else {
           for (int q = 0; q < 4; ++q)
-            if (n + q < N) cs(r, n + q, z, acc[i][j][q]);
+            if (n + q < N) cs(r, n + q, 0, acc[i][j][q]);
         }
       }
     }
   }
 }
 
-// The stage where the range ends (krem = kend - k0 < SBK reduction entries
+// The stage where the range ends (krem = K - k0 < SBK reduction entries
 // left): lanes whose entries lie beyond it copy zeros instead.
 template <int BR, class OPND, int STEP, int NW>
 __device__ __forceinline__ void dma_stage_tail(const char *base, const uint32_t (&off)[NW], char *dst, int first,
@@ -474,12 +468,12 @@ __device__ __forceinline__ void dma_stage_full(const char *base, const uint32_t 
   }
 }
 
-// One output tile (and one split-K slice) per block; all four waves issue
+// One output tile per block; all its waves issue
 // their share of every stage's DMA and compute.  Several blocks per CU keep
 // loads in flight while another block multiplies or stores.
 template <int OP, class CF, bool F32, class AO, class BO, class CS>
-__global__ __launch_bounds__(64 * CF::NW, F32 ? 2 : 1) void gemm_stream_kernel(AO ao, BO bo, CS cs, int64_t M, int N, int K,
-                                                                  int ksplit, int nbM, int nbN, int nz) {
+__global__ __launch_bounds__(64 * CF::NW, F32 ? 2 : 1) void gemm_stream_kernel(AO ao, BO bo, CS cs, int64_t M,
+                                                                              int N, int K, int nbM, int nbN) {
   constexpr int BM = CF::BM, BN = CF::BN, NW = CF::NW;
   constexpr int AB = AO::template bytes<BM>(), BB = BO::template bytes<BN>(), SB = AB + BB;
   constexpr int NIA = (AO::template slots<BM>() + 63) / 64, NIB = (BO::template slots<BN>() + 63) / 64;
@@ -495,34 +489,24 @@ __global__ __launch_bounds__(64 * CF::NW, F32 ? 2 : 1) void gemm_stream_kernel(A
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % CF::WM, wn = wave / CF::WM;
   const int q16 = lane & 15, g4 = lane >> 4;
-  const TileMap tm(blockIdx.x, nbM, nbN, nz, ksplit > 0);
+  const TileMap tm(blockIdx.x, nbM, nbN, 1, false);
   const int64_t m0 = (int64_t)tm.mt * BM;
   const int n0 = tm.nt * BN;
-  const int z = tm.z;
-  int kbeg = 0, kend = K;
-  if (ksplit > 0) {
-    kbeg = z * ksplit;
-    kend = min(K, kbeg + ksplit);
-  }
-  const int niter = kend > kbeg ? (kend - kbeg + SBK - 1) / SBK : 0;
+  const int niter = (K + SBK - 1) / SBK;
 
-  AO aw = ao;
-  BO bw = bo;
-  aw.bind(m0);
-  bw.bind(n0);
   constexpr int NWA = dma_per_wave<BM, AO>(NW), NWB = dma_per_wave<BN, BO>(NW);
   uint32_t offa[NWA], offb[NWB];
   dma_offsets<BM>(ao, offa, wave, NW, lane, m0);
   dma_offsets<BN>(bo, offb, wave, NW, lane, n0);
   auto issue = [&](int it) {
     char *sa = lds + (it % NS) * SB;
-    const int k0 = kbeg + it * SBK;
-    if (k0 + SBK <= kend) {
+    const int k0 = it * SBK;
+    if (k0 + SBK <= K) {
       dma_stage_full<BM, AO, NW>(ao.base(m0, k0), offa, sa, wave, lane);
       dma_stage_full<BN, BO, NW>(bo.base(n0, k0), offb, sa + AB, wave, lane);
     } else {  // the range ends inside this stage: zeros beyond it
-      dma_stage_tail<BM, AO, NW>(ao.base(m0, k0), offa, sa, wave, lane, kend - k0);
-      dma_stage_tail<BN, BO, NW>(bo.base(n0, k0), offb, sa + AB, wave, lane, kend - k0);
+      dma_stage_tail<BM, AO, NW>(ao.base(m0, k0), offa, sa, wave, lane, K - k0);
+      dma_stage_tail<BN, BO, NW>(bo.base(n0, k0), offb, sa + AB, wave, lane, K - k0);
     }
   };
 
@@ -554,32 +538,32 @@ __global__ __launch_bounds__(64 * CF::NW, F32 ? 2 : 1) void gemm_stream_kernel(A
   for (int it = 0; it < niter; ++it) {
     wait_issue(it);
     if constexpr (SidePre<CF, CS>::kOn)
-      if (it == side_it) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4, z);
+      if (it == side_it) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4);
     const char *sa = lds + (it % NS) * SB;
-    mma_stage<CF, F32>(aw, bw, sa, sa + AB, wm, wn, q16, g4, acc, low);
+    mma_stage<CF, F32>(ao, bo, sa, sa + AB, wm, wn, q16, g4, acc, low);
   }
   if constexpr (F32) {
     add_parts(acc, low);
     if (any_odd(acc)) {
-      mend_odd<false>(ao, bo, m0 + wm * CF::TM * 16, (int64_t)n0 + wn * CF::TN * 16, M, N, kbeg, kend, acc,
-                      [&](int, int64_t r, unsigned want) { return nan_rows(ao, r, kbeg, kend, want); });
+      mend_odd<false>(ao, bo, m0 + wm * CF::TM * 16, (int64_t)n0 + wn * CF::TN * 16, M, N, 0, K, acc,
+                      [&](int, int64_t r, unsigned want) { return nan_rows(ao, r, 0, K, want); });
       // again, so that they take no registers there
-      if constexpr (SidePre<CF, CS>::kOn) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4, z);
+      if constexpr (SidePre<CF, CS>::kOn) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4);
     }
   }
   if constexpr (SidePre<CF, CS>::kOn)
-    if (niter == 0) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4, z);
-  store_tiles<CF>(cs, acc, M, N, m0, n0, wm, wn, q16, g4, z, sp);
+    if (niter == 0) load_side<CF>(cs, sp, M, N, m0, n0, wm, wn, q16, g4);
+  store_tiles<CF>(cs, acc, M, N, m0, n0, wm, wn, q16, g4, sp);
 }
 
 template <int OP, class CF, bool F32, class AO, class BO, class CS>
-int run_stream(AO ao, BO bo, CS cs, int64_t M, int N, int K, int Z, int ksplit, hipStream_t st) {
-  if (M <= 0 || N <= 0 || Z <= 0) return 0;
+int run_stream(AO ao, BO bo, CS cs, int64_t M, int N, int K, hipStream_t st) {
+  if (M <= 0 || N <= 0) return 0;
   const int64_t nbM = (M + CF::BM - 1) / CF::BM;
   const int nbN = (N + CF::BN - 1) / CF::BN;
-  if (nbM * nbN * Z > 0x7fffffff) return -4;
-  hipLaunchKernelGGL((gemm_stream_kernel<OP, CF, F32, AO, BO, CS>), dim3((unsigned)(nbM * nbN * Z)),
-                     dim3(64 * CF::NW), 0, st, ao, bo, cs, M, N, K, ksplit, (int)nbM, nbN, Z);
+  if (nbM * nbN > 0x7fffffff) return -4;
+  hipLaunchKernelGGL((gemm_stream_kernel<OP, CF, F32, AO, BO, CS>), dim3((unsigned)(nbM * nbN)), dim3(64 * CF::NW), 0,
+                     st, ao, bo, cs, M, N, K, (int)nbM, nbN);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -794,8 +778,8 @@ struct CRowSideH {
 // Per element the epilogue is the tiled core's (bias, ReLU, mask, RNE
 // rounding, bits of the stored value) with the ReLU chosen at compile time;
 // the accumulation order is also the tiled core's (k-slices in order; FP32:
-// within a slice, k groups of 16, then the four MFMAs of a group), so with
-// one accumulator set the results are bitwise the same.
+// within a slice the six part products of parts.h in their order), so the
+// results are bitwise the same.
 namespace astat {
 
 #ifndef DLM_ASTAT_TM
@@ -1293,7 +1277,7 @@ int stream_table_c(AO ao, BO bo, CS cs, const TableGemm &t, hipStream_t st) {
   if constexpr (astat::takes<CS>())
     if (astat::ok<F32>(t)) return astat::run<F32>(t, bo, cs, st);
   if constexpr (F32) {
-    auto go = [&](auto cfg) { return run_stream<OP, decltype(cfg), F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st); };
+    auto go = [&](auto cfg) { return run_stream<OP, decltype(cfg), F32>(ao, bo, cs, t.M, t.N, t.K, st); };
     switch (f32_tile(t.M, t.N)) {
       case 0: return go(SCfg<256, 144, 8, 1, 2>{});
       case 1: return go(SCfg<256, 96, 8, 1, 2>{});
@@ -1302,13 +1286,13 @@ int stream_table_c(AO ao, BO bo, CS cs, const TableGemm &t, hipStream_t st) {
       default: return go(SCfg<64, 48, 4, 1, 4>{});
     }
   } else {
-    if (t.N <= 96) return run_stream<OP, SCfgSmall, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+    if (t.N <= 96) return run_stream<OP, SCfgSmall, F32>(ao, bo, cs, t.M, t.N, t.K, st);
     if constexpr (!CS::kMask)
       if (t.N > 144 && t.K > 256 && (t.M + 255) / 256 * ((t.N + 95) / 96) >= 512)
-        return run_stream<OP, SCfgWide, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+        return run_stream<OP, SCfgWide, F32>(ao, bo, cs, t.M, t.N, t.K, st);
     if ((t.M + 127) / 128 * ((t.N + 143) / 144) < 128)
-      return run_stream<OP, SCfgFew, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
-    return run_stream<OP, SCfgNarrow, F32>(ao, bo, cs, t.M, t.N, t.K, 1, 0, st);
+      return run_stream<OP, SCfgFew, F32>(ao, bo, cs, t.M, t.N, t.K, st);
+    return run_stream<OP, SCfgNarrow, F32>(ao, bo, cs, t.M, t.N, t.K, st);
   }
 }
 
