@@ -34,6 +34,10 @@ sys.path.insert(0, ROOT)
 METRIC = "voxels/s fwd+bwd Signal2SH+LSC+SH2Signal, 3×90 dirs, L=8; % roofline"
 HBM_PEAK_GBS = 8000.0
 MFMA_PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0}
+# the FP32 products of the folded layer run on the bfloat16 matrix cores, six
+# part products each
+PART_PRODUCTS = 6
+PART_TAGS = ("lsc_folded_fwd", "lsc_folded_bwd_data", "lsc_folded_grad")
 
 
 def parse():
@@ -122,14 +126,25 @@ def measured_traffic(tag, prec):
     return None
 
 
+def in_parts(tag, prec):
+    return prec == "fp32" and tag in PART_TAGS
+
+
+def mfma_peak(tag, prec):
+    """TFLOP/s of the matrix unit that runs a kernel, in the kernel's own products."""
+    return MFMA_PEAK_TFLOPS["bf16"] / PART_PRODUCTS if in_parts(tag, prec) else MFMA_PEAK_TFLOPS[prec]
+
+
 def roofline(tag, ms, launches, nbytes, flops, prec):
     t = ms / 1e3
+    peak = mfma_peak(tag, prec)
     hbm_time = nbytes / (HBM_PEAK_GBS * 1e9)
-    mfma_time = flops / (MFMA_PEAK_TFLOPS[prec] * 1e12)
+    mfma_time = flops / (peak * 1e12)
     if mfma_time > hbm_time:
         ach = flops / t / 1e12
-        return {"kernel": tag, "bound": "mfma", "achieved": round(ach, 2), "peak": MFMA_PEAK_TFLOPS[prec],
-                "unit": "TFLOP/s", "frac": round(ach / MFMA_PEAK_TFLOPS[prec], 4), "traffic": None,
+        return {"kernel": tag, "bound": "mfma", "achieved": round(ach, 2), "peak": round(peak, 1),
+                "peak_of": "bf16 MFMA, six part products" if in_parts(tag, prec) else f"{prec} MFMA",
+                "unit": "TFLOP/s", "frac": round(ach / peak, 4), "traffic": None,
                 "launches": launches, "avg_launch_ms": round(ms / launches, 4),
                 "alg_flops_per_launch": flops / launches, "alg_bytes_per_launch": nbytes / launches}
     ach = nbytes / t / 1e9
@@ -476,7 +491,6 @@ def time_c2(step, loss, prec, form, args, V, full_size):
     torch.cuda.synchronize()
     dl.timing_enable(False)
     rep = dl.timing_report()
-    peak = MFMA_PEAK_TFLOPS[prec]
     kern = {}
     for t, v in sorted(rep.items(), key=lambda kv: -kv[1][0]):
         sec = v[0] / 1e3
@@ -484,14 +498,14 @@ def time_c2(step, loss, prec, form, args, V, full_size):
                    "GB/s": round(v[2] / sec / 1e9, 1) if sec > 0 else None,
                    "TFLOP/s": round(v[3] / sec / 1e12, 2) if sec > 0 else None,
                    "hbm_frac": round(v[2] / sec / 1e9 / HBM_PEAK_GBS, 3) if sec > 0 else None,
-                   "mfma_frac": round(v[3] / sec / 1e12 / peak, 3) if sec > 0 else None}
+                   "mfma_frac": round(v[3] / sec / 1e12 / mfma_peak(t, prec), 3) if sec > 0 else None}
     top = max(rep.items(), key=lambda kv: kv[1][0])
     out["roofline"] = roofline(top[0], *top[1], prec)
     if form == "folded" and full_size:
         # counters were taken on this workload in the folded form only
         out["roofline"]["traffic"] = measured_traffic(top[0], prec)
         out["roofline"]["traffic_source"] = os.path.relpath(TRAFFIC_FILE, ROOT)
-    roof_s = sum(max(v[2] / (HBM_PEAK_GBS * 1e9), v[3] / (peak * 1e12)) for v in rep.values())
+    roof_s = sum(max(v[2] / (HBM_PEAK_GBS * 1e9), v[3] / (mfma_peak(t, prec) * 1e12)) for t, v in rep.items())
     out["step_roofline_frac"] = round(roof_s / args.steps / (ms_step / 1e3), 4)
     out["kernels"] = kern
     return out
@@ -501,9 +515,14 @@ def with_measured_peak(roof, peaks, prec):
     """The roofline's achieved rate also against the peak measured on this GPU."""
     if not roof or not peaks:
         return roof
-    key = "hbm_copy_GBs" if roof["bound"] == "hbm" else f"{prec}_mfma_TFLOPs"
-    roof["measured_peak"] = peaks[key]
-    roof["frac_of_measured_peak"] = round(roof["achieved"] / peaks[key], 4)
+    if roof["bound"] == "hbm":
+        peak = peaks["hbm_copy_GBs"]
+    elif in_parts(roof["kernel"], prec):
+        peak = round(peaks["bf16_mfma_TFLOPs"] / PART_PRODUCTS, 1)
+    else:
+        peak = peaks[f"{prec}_mfma_TFLOPs"]
+    roof["measured_peak"] = peak
+    roof["frac_of_measured_peak"] = round(roof["achieved"] / peak, 4)
     return roof
 
 
