@@ -130,3 +130,27 @@ def test_long_sums_do_not_drift(case):
     _, dW, _ = dl.lsc_bwd(plan, a, cuda(W), g, need_input_grad=False)
     err = np.linalg.norm(dW.double().cpu().numpy().reshape(ref.shape) - ref) / np.linalg.norm(ref)
     assert err <= 3.4e-7, err
+
+
+@pytest.mark.parametrize("positive", [False, True])
+@pytest.mark.parametrize("case", [(256, 3, 200), (256, 64, 300), (64, 256, 300)])
+def test_longest_reductions(case, positive):
+    # 256 channels of order 8, 11 520 entries: the float32 instruction's running
+    # sum, four entries to a rounding of 2^-24 / sqrt(3), is off by sqrt(K / 8) of
+    # them, 1.3e-6 (measured 1.9e-6); the part products are held to it, also
+    # where every product is positive and the matrix unit's cuts add up
+    C, O, V = case
+    plan = _plan(8, 8, m=90, ks=(8, 8))
+    W = dg.lsc_weights(11, 0, C, O, plan.T)[0].astype(np.float32).astype(np.float64)
+    rng = np.random.default_rng(11)
+    a = rng.standard_normal((V, C * plan.K_in)).astype(np.float32)
+    g = rng.standard_normal((V, O * plan.K_out)).astype(np.float32)
+    if positive:
+        W, a, g = np.abs(W), np.abs(a), np.abs(g)
+    T, _ = _folded(plan, W)
+    T = torch.from_numpy(T).to(DEV)
+    ag, gg, Wg = cuda(a.reshape(V, C, -1)), cuda(g.reshape(V, O, -1)), cuda(W)
+    out = dl.lsc_fwd(plan, ag, Wg, None).reshape(V, -1).double()
+    da = dl.lsc_bwd(plan, ag, Wg, gg, need_weight_grad=False, need_bias_grad=False)[0].reshape(V, -1).double()
+    for got, ref in ((out, ag.reshape(V, -1).double() @ T.t()), (da, gg.reshape(V, -1).double() @ T)):
+        assert float((got - ref).norm() / ref.norm()) <= 1.3e-6
