@@ -42,10 +42,15 @@ typedef enum {
   DLM_EWORKSPACE = 5   /* workspace smaller than the minimum                 */
 } dlm_status;
 
-/* Arithmetic form.  DLM_FP32: float32 inputs and products, float32
- * accumulation.  DLM_BF16: matrix-core inputs rounded to bfloat16 (round to
- * nearest even) with float32 accumulation; tables are formed in float64 and
- * rounded once.  Storage at the ABI is float32 in both forms. */
+/* Arithmetic form.  DLM_FP32: float32 inputs, products to float32's accuracy,
+ * float32 accumulation; infinities, NaN and small numbers come out as float32
+ * has them.  (The folded layer forms its products on the bfloat16 matrix
+ * cores, from three bfloat16 parts of either factor; results that the parts
+ * may have got wrong, not finite or below 2^-80, are formed again in float32.
+ * What that leaves: a factor below 2^-134 beside others is zero, and one below
+ * 2^-109 is off by up to 2^-134.)  DLM_BF16: matrix-core inputs rounded to
+ * bfloat16 (round to nearest even) with float32 accumulation; tables are formed
+ * in float64 and rounded once.  Storage at the ABI is float32 in both forms. */
 typedef enum { DLM_FP32 = 0, DLM_BF16 = 1 } dlm_precision;
 
 const char *dlm_status_str(dlm_status s);
@@ -191,7 +196,10 @@ typedef struct dlm_lsc_plan dlm_lsc_plan;
  * map (up to float rounding order):
  *  DLM_LSC_RESAMPLE -- the paper's order (Sec. 2.3, Fig. 4): resample the
  *    neighbourhood matrices X into the workspace, row-dot them with the
- *    cyclic kernel, refit.  Workspace grows with the voxels per pass.
+ *    cyclic kernel, refit.  Workspace grows with the voxels per pass.  In
+ *    DLM_FP32, where that takes fewer multiplications (O not much above C, K_in
+ *    <= m, C m >= O K_in), the channels are mixed with the kernel before the
+ *    resampling, with which they commute, and X is never formed.
  *  DLM_LSC_FOLDED -- by linearity of resample, row dot and refit, the layer
  *    is a_out[o] = sum_c T_oc a_in[c] + bias[o] P_m 1 with
  *    T_oc = sum_t W[o][c][t] (P_m B_t), B_t the resampling rows of tap t;
@@ -226,7 +234,8 @@ void dlm_lsc_plan_destroy(dlm_lsc_plan *plan);
 dlm_status dlm_lsc_workspace_bytes(const dlm_lsc_plan *plan, int C, int O, int64_t V_chunk,
                                    dlm_lsc_form form, dlm_precision prec, size_t *bytes);
 
-/* LSC forward in the paper's order (Sec. 2.3, Fig. 4):
+/* LSC forward in the paper's order (Sec. 2.3, Fig. 4; DLM_LSC_RESAMPLE says
+ * when another is taken):
  *   X[v][c][i*T+t] = sum_j B_nb[i*T+t][j] a_in[v][c][j]   (neighbourhood resampling)
  *   y[v][o][i]     = bias[o] + sum_c sum_t W[o][c][t] X[v][c][i*T+t]
  *                    (kernel row dot, a cross-correlation; channels = b-values)
@@ -258,8 +267,9 @@ typedef enum { DLM_RELU_OUT = 1, DLM_RELU_IN = 2 } dlm_relu_flags;
  *   dbias device [O]            = sum_{v,i} dy[v][o][i]                (overwritten)
  * relu_flags: a combination of dlm_relu_flags (other bits: DLM_EINVAL).
  * Resample form: the neighbourhood matrices X are recomputed from a_in, not
- * stored.  Folded form: dW comes from dT_oc = sum_v da_out[v][o] a_in[v][c]^T
- * contracted with each tap's (P_m B_t). */
+ * stored (with the channels mixed first, the resampled dy takes their place).
+ * Folded form: dW comes from dT_oc = sum_v da_out[v][o] a_in[v][c]^T contracted
+ * with each tap's (P_m B_t). */
 dlm_status dlm_lsc_bwd(const dlm_lsc_plan *plan, const float *a_in, int C, const float *W, int O,
                        const float *a_out, const float *da_out, float *da_in, float *dW, float *dbias,
                        int64_t V, int relu_flags, dlm_lsc_form form, void *ws, size_t ws_bytes,
@@ -300,9 +310,9 @@ int dlm_sh_image_supported(const dlm_sh_plan *plan, int64_t B, int64_t P);
 dlm_status dlm_sh_image(const dlm_sh_plan *plan, dlm_sh_op op, const float *in, float *out, int64_t B,
                         int64_t P, dlm_precision prec, void *stream);
 /* The folded LSC layer and its adjoint on images; workspace as for the folded
- * form, 16-byte aligned (DLM_EINVAL otherwise).  relu_bits: NULL, or (needs fuse_relu) a device array of uint16
- * [B][O*K_out][(P+15)/16] whose bit v % 16 of word [..][v / 16] the forward
- * sets to 1 iff the output there is > 0; the backward masks da_out by it (the
+ * form, 16-byte aligned (DLM_EINVAL otherwise).  relu_bits: NULL, or (needs
+ * fuse_relu) a device array of uint16 [B][O*K_out][(P+15)/16] whose bit v % 16
+ * of word [..][v / 16] the forward sets to 1 iff the output there is > 0; the backward masks da_out by it (the
  * gradient of a layer whose forward fused a ReLU) and may be given no a_in
  * where it makes no dW. */
 dlm_status dlm_lsc_fwd_image(const dlm_lsc_plan *plan, const float *a_in, int C, const float *W,

@@ -681,12 +681,16 @@ struct CImage {
   }
 };
 
-// Tiles, measured on 121360 voxels (BF16) and 32768 (FP32), 135 -> 1440 and
-// 1440 -> 135 channels, us: BF16 128 x 96 with eight waves 391 and 297 (128 x
-// 144 with four 527 and 342, 256 x 144 498 and 290, 64 x 48 462 and 327): its
-// small accumulators leave room for the most waves.  FP32 256 x 144 with
-// eight waves 179 and 201 (128 x 144 228 and 179, 128 x 48 242 and 178): the
-// part products want the larger tile once it fills the chip.
+// Tiles.  Measured on 121360 voxels (BF16) and 32768 (FP32), 135 -> 1440 and
+// 1440 -> 135 channels, us, when the rule below was laid: BF16 128 x 96 with
+// eight waves 391 and 297 (128 x 144 with four 527 and 342, 256 x 144 498 and
+// 290, 64 x 48 462 and 327): its small accumulators leave room for the most
+// waves.  FP32 256 x 144 with eight waves 179 and 201 (128 x 144 228 and 179,
+// 128 x 48 242 and 178): the part products want the larger tile once it fills
+// the chip.  Since then the table's runs of the other tiles have left scratch
+// memory; with the fold, 256 x 144 now takes 159 and 156 in FP32, 128 x 144 147
+// and 122, 128 x 48 171 and 111, 64 x 48 185 and 129; BF16 128 x 96 385 and 216,
+// 256 x 144 366 and 191, 128 x 144 349 and 204.
 template <int OP, int P, class AO>
 int image_table(AO ao, const ImageGemm &x, hipStream_t st) {
   const Table<P> tab{x.table, x.ldb, x.N, x.values, x.K};
