@@ -484,15 +484,17 @@ def lsc_bwd_image(plan: LSCPlan, a, W: torch.Tensor, g: torch.Tensor, bits=None,
         raise ValueError("a_in is needed for dW and dbias")
     prec = precision_code(precision)
     B, P, dev = g.shape[0], g.shape[2:].numel(), g.device
-    if g.dim() < 3 or g.shape[1] != O * plan.K_out or W.shape[2] != plan.T or \
-            (a is not None and tuple(a.shape) != (B, Cin * plan.K_in, *g.shape[2:])):
-        raise ValueError(f"shapes: a_in {None if a is None else tuple(a.shape)}, da_out {tuple(g.shape)}, "
+    in_shape = (B, Cin * plan.K_in, *g.shape[2:]) if a is None else tuple(a.shape)
+    if tuple(g.shape[1:2]) != (O * plan.K_out,) or W.shape[2] != plan.T or \
+            in_shape[:2] != (B, Cin * plan.K_in) or torch.Size(in_shape[2:]).numel() != P:
+        raise ValueError(f"shapes: a_in {None if a is None else in_shape}, da_out {tuple(g.shape)}, "
                          f"W {tuple(W.shape)}, plan K_in={plan.K_in} K_out={plan.K_out} T={plan.T}")
-    if bits is not None and (bits.dtype != torch.int16 or not bits.is_cuda or not bits.is_contiguous() or
-                             tuple(bits.shape) != (B, g.shape[1], (P + 15) // 16)):
-        raise ValueError(f"bits must be a contiguous int16 device tensor of shape {(B, g.shape[1], (P + 15) // 16)}")
+    words = B * g.shape[1] * ((P + 15) // 16)
+    if bits is not None and (bits.element_size() != 2 or not bits.is_cuda or not bits.is_contiguous() or
+                             bits.numel() != words):
+        raise ValueError(f"bits must be a contiguous device tensor of {words} 16-bit words")
     ws = _default_ws(plan, Cin, O, B * P, prec, dev, "folded")
-    da = torch.empty((B, Cin * plan.K_in, *g.shape[2:]), dtype=torch.float32, device=dev) if need_input_grad else None
+    da = torch.empty(in_shape, dtype=torch.float32, device=dev) if need_input_grad else None
     dW = torch.empty((O, Cin, plan.T), dtype=torch.float32, device=dev) if need_dW else None
     db = torch.empty((O,), dtype=torch.float32, device=dev) if need_bias_grad else None
     check(lib().dlm_lsc_bwd_image(plan.handle, _ptr(a), Cin, _ptr(W), O, _ptr(bits), _ptr(g), _ptr(da), _ptr(dW),

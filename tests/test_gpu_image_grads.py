@@ -57,3 +57,20 @@ def test_no_input_without_weight_gradients():
             dl.lsc_bwd_image(plan, a, W, bad)
     with pytest.raises(ValueError):
         dl.lsc_bwd_image(plan, a, W, g, torch.zeros(1, 3, 3, dtype=torch.int16, device=DEV))
+
+
+def test_voxel_axes_of_the_backward():
+    # any number of voxel axes, none for one voxel; the gradient and the input
+    # need not have the same ones
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(30), 2, 2, (6,), np.deg2rad(30), 0.006)
+    gen = torch.Generator(device=DEV).manual_seed(16)
+    W = torch.randn(3, 2, plan.T, device=DEV, generator=gen)
+    for axes, other in (((1,), ()), ((30,), (2, 3, 5)), ((2, 3, 5), (6, 5))):
+        a, g = (torch.randn(2, n * plan.K_in, *axes, device=DEV, generator=gen) for n in (2, 3))
+        _, bits = dl.lsc_fwd_image(plan, a, W, relu=True, need_bits=True)
+        want = dl.lsc_bwd_image(plan, a, W, g, bits)
+        flat = bits.view(torch.uint16).flatten()
+        for a2, g2, b2 in ((a.view(2, -1, *other), g, bits), (a, g.view(2, -1, *other), flat)):
+            got = dl.lsc_bwd_image(plan, a2, W, g2, b2)
+            assert got[0].shape == a2.shape and torch.equal(got[0].flatten(), want[0].flatten())
+            assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
