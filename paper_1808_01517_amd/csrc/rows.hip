@@ -341,14 +341,31 @@ bool shell_rows_ok(const ShellRows &x) {
 // units a wave outlast the copies and need later blocks to hide behind them
 // (three shells of 90, order 12, 30 000 voxels: 29.0 against 30.6 us; 200 000
 // voxels 191 -> 153).
+// Rows save reading lines twice that two shells share, which costs little
+// while a call's data stays in the last-level cache (half of its 256 MB: a step
+// has another call's data beside it; at 130 MB rows still take 1.03 to 1.1 times
+// as long in the cases below, at 144 MB 0.82 to 1.01).  There the per-shell waves win wherever every wave of a row
+// block has products to do and either the rows start on 16 bytes, so that
+// shells' slices are read in whole pieces all the same (two shells of 90, order
+// 10, 80 000 voxels, 100 MB, BF16 SH2Signal 25 against 31 us, 300 000 voxels 97
+// -> 95; four of 45, order 8, 20 000 voxels 9.7 against 11.8), or the FP32
+// reduction is long (three shells of 90, order 8, 40 000 voxels Signal2SH 22.4
+// against 25.2 us; two of 90, order 12, 25.2 against 28.4), or FP32 reads short
+// slices and writes whole pieces (three shells of 60, order 2, 70 000 voxels
+// 17.2 against 18.5).
 bool shell_rows_pay(const ShellRows &x, dlm_precision prec) {
-  constexpr int64_t kMany = 65536;
+  constexpr int64_t kMany = 65536, kCached = 128 << 20;
   const bool f32 = prec != DLM_BF16;
   for (int s = 1; s < x.S; ++s)
     if (x.sh[s].nred != x.sh[0].nred || x.sh[s].ncol != x.sh[0].ncol) return true;
-  if (x.sh[0].nred % 4 == 0 || x.sh[0].ncol % 4 == 0)
-    return x.S > 2 && x.V >= kMany && !(f32 && x.sh[0].nred % 4 == 0);
+  const int nred = x.sh[0].nred, ncol = x.sh[0].ncol;
+  const int64_t bytes = int64_t(4) * x.V * (x.n_in + x.n_out);
+  const bool busy = x.units >= rows::kWaves && bytes < kCached;
+  if (busy && x.n_in % 4 == 0 && x.n_out % 4 == 0 && bytes >= kCached / 16) return false;
+  if (nred % 4 == 0 || ncol % 4 == 0)
+    return x.S > 2 && x.V >= kMany && !(f32 && (nred % 4 == 0 || (nred <= 64 && bytes < kCached)));
   if (f32 && x.V < kMany && x.units > 2 * rows::kWaves && x.max_red > 64) return false;
+  if (f32 && busy && nred > 64 && bytes >= kCached / 4) return false;
   return x.S > 1 || !f32;
 }
 

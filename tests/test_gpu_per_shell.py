@@ -68,3 +68,28 @@ def test_against_oracle_and_other_forms(kind, V, prec):
                 check("c, other form", b, refs[0], prec)
             else:
                 assert torch.equal(a, b), (switch, i)
+
+
+# either side of the lines between whole rows and per-shell waves: call bytes
+# from 8 to 128 MiB with 16-byte rows (two shells of 90, order 10, 1 248 bytes a
+# voxel), from 32 MiB with long FP32 reductions (three of 90, order 8, 1 620
+# bytes), below 128 MiB with short FP32 slices (three of 60, order 2, 792 bytes)
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("dirs,order,sizes", [((90, 90), 10, (6_721, 6_722, 107_546, 107_547)),
+                                              ((90, 90, 90), 8, (20_712, 20_713, 82_850, 82_851)),
+                                              ((60, 60, 60), 2, (65_535, 65_536, 169_466, 169_467))])
+def test_lines_between_rows_and_shells(dirs, order, sizes, prec):
+    tab = [dg.perturb_directions(dg.fibonacci_hemisphere(n), 2.0, dg.rng_for(12, 0, s)) for s, n in enumerate(dirs)]
+    bvecs = np.concatenate(tab)
+    bvals = np.concatenate([np.full(d.shape[0], 1000.0 * (s + 1)) for s, d in enumerate(tab)])
+    oplan, plan = osh.SHPlan(bvecs, bvals, order, 0.006), dl.SHPlan(bvecs, bvals, order, 0.006)
+    rng = np.random.default_rng(98)
+    V = max(sizes)
+    c = rng.standard_normal((V, plan.n_shells, plan.K)).astype(np.float32).astype(np.float64)
+    x = osh.sh2signal(oplan, rng.standard_normal(c.shape)).astype(np.float32).astype(np.float64)
+    xg, cg = cuda(x), cuda(c)
+    refs = (osh.signal2sh(oplan, x), osh.sh2signal_adjoint(oplan, x), osh.sh2signal(oplan, c),
+            osh.signal2sh_adjoint(oplan, c))
+    for n in sizes:
+        for name, o, r in zip(("c", "dc", "x", "dx"), run(plan, xg[:n], cg[:n], prec), refs):
+            check(f"{name}, V={n}", o, r[:n], prec)
