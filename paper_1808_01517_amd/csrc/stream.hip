@@ -1250,21 +1250,32 @@ using SCfgFew = SCfg<64, 48, 4, 1, 8>;
 // 256 x 144: against the float32 matrix instructions 8192 x 2880 x 1440 591 ->
 // 383 us (177 TFLOP/s, 1.06 PFLOP/s of part products), K = 1440 onto 135 at 1M
 // voxels 3.30 -> 2.18 ms, the K = 135 kernel above 3.82 -> 2.55 ms.
+// Rows that are not whole 16-byte pieces are copied element by element, four
+// times the instructions, and a block alone on its compute unit has nothing to
+// hide them behind: up to 1280 inputs, where the stages do, those take one of
+// the tiles with two blocks, whose stages then took the times in the last
+// column (120000 voxels, 45 onto 480: 64 x 144 107 us, 128 x 48 111, 256 x 144
+// 185, 256 x 96 151; onto 1440 with a mask to load 406, 462, 587 and 848; 315
+// onto 1440 787, 911, 962, 853; 1485 onto 1440 3.50, 3.59, 3.45, 3.10 ms).
 struct F32Tile {
   int bm, bn, slots;  // slots: blocks of a chip of 256 compute units
-  double half, full;
+  double half, full, pieces;
 };
-inline int f32_tile(int64_t M, int N) {
-  static constexpr F32Tile kTiles[] = {
-      {256, 144, 256, 2.3, 3.0}, {256, 96, 256, 1.8, 2.1}, {64, 144, 512, 1.1, 1.85}, {128, 48, 512, 0.93, 1.29},
-      {64, 48, 512, 0.66, 0.80}};
-  int best = 0;
+inline int f32_tile(int64_t M, int N, int K, bool whole) {
+  static constexpr F32Tile kTiles[] = {{256, 144, 256, 2.3, 3.0, 3.0},
+                                       {256, 96, 256, 1.8, 2.1, 2.1},
+                                       {64, 144, 512, 1.1, 1.85, 1.65},
+                                       {128, 48, 512, 0.93, 1.29, 1.33},
+                                       {64, 48, 512, 0.66, 0.80, 0.80}};
+  const bool two = !whole && K < 1280;
+  int best = -1;
   double least = 0.0;
-  for (int i = 0; i < 5; ++i) {
+  for (int i = two ? 2 : 0; i < 5; ++i) {
     const F32Tile &c = kTiles[i];
     const int64_t blocks = (M + c.bm - 1) / c.bm * ((N + c.bn - 1) / c.bn), rest = blocks % c.slots;
-    const double cost = double(blocks / c.slots) * c.full + (rest == 0 ? 0.0 : rest <= c.slots / 2 ? c.half : c.full);
-    if (i == 0 || cost < least) {
+    const double full = two ? c.pieces : c.full;
+    const double cost = double(blocks / c.slots) * full + (rest == 0 ? 0.0 : rest <= c.slots / 2 ? c.half : full);
+    if (best < 0 || cost < least) {
       best = i;
       least = cost;
     }
@@ -1278,7 +1289,7 @@ int stream_table_c(AO ao, BO bo, CS cs, const TableGemm &t, hipStream_t st) {
     if (astat::ok<F32>(t)) return astat::run<F32>(t, bo, cs, st);
   if constexpr (F32) {
     auto go = [&](auto cfg) { return run_stream<OP, decltype(cfg), F32>(ao, bo, cs, t.M, t.N, t.K, st); };
-    switch (f32_tile(t.M, t.N)) {
+    switch (f32_tile(t.M, t.N, t.K, AO::kUnit == 16)) {
       case 0: return go(SCfg<256, 144, 8, 1, 2>{});
       case 1: return go(SCfg<256, 96, 8, 1, 2>{});
       case 2: return go(SCfg<64, 144, 4, 1, 2>{});

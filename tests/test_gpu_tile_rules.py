@@ -1,0 +1,51 @@
+"""Which tile a folded product takes, at the lines of the rules: FP32 rows that
+are not whole 16-byte pieces (odd channel counts at even orders, 45 entries a
+channel), around a tile's rows and its batch, up to and above the reduction from
+which they are treated like the others.
+"""
+import numpy as np
+import pytest
+import torch
+
+import datagen as dg
+import paper_1808_01517_amd as dl
+
+from parity_util import check
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _products(C, O, voxels, prec, store):
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(90), 8, 8, (8, 8), np.deg2rad(30), 0.006)
+    W, b = dg.lsc_weights(8, 0, C, O, plan.T)
+    W, b = (torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to(DEV) for x in (W, b))
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    a = torch.randn(voxels, C, plan.K_in, device=DEV, generator=gen)
+    g = torch.randn(voxels, O, plan.K_out, device=DEV, generator=gen)
+    if store == "half":
+        a, g = a.bfloat16(), g.bfloat16()
+    _, Bnb, Pm = (torch.from_numpy(np.asarray(t)).double() for t in plan.tables())
+    Q = torch.einsum("ki,itj->tkj", Pm, Bnb.reshape(plan.m, plan.T, plan.K_in))
+    T = torch.einsum("oct,tkj->okcj", W.double().cpu(), Q).reshape(O * plan.K_out, C * plan.K_in).to(DEV)
+    bias = (b.double()[:, None] * Pm.sum(1).to(DEV)).reshape(-1)
+    flat = a.reshape(voxels, -1)
+
+    out = dl.lsc_fwd(plan, a, W, b, relu=True, precision=prec, out_dtype=a.dtype)
+    check("out", out.float().reshape(voxels, -1), (flat.double() @ T.t() + bias).clamp(min=0.0), prec)
+    ref = g.reshape(voxels, -1).double() @ T
+    for relu_in in (False, True):
+        da, _, _ = dl.lsc_bwd(plan, a, W, g, need_weight_grad=False, need_bias_grad=False, relu_in=relu_in,
+                              precision=prec)
+        check("da", da.float().reshape(voxels, -1), ref * (flat > 0) if relu_in else ref, prec)
+
+
+# 45 onto 360 and back (64 x 48, 128 x 48 and 64 x 144 by batch), 1215 and 1305
+# onto 180
+@pytest.mark.parametrize("case,voxels",
+                         [((1, 8), v) for v in (1, 63, 65, 4097, 8191, 16385, 40001)] +
+                         [((27, 4), v) for v in (65, 8191, 16385)] + [((29, 4), v) for v in (65, 8191, 16385)])
+def test_rows_of_pieces(case, voxels):
+    _products(*case, voxels, "fp32", "fp32")
+    _products(*case[::-1], voxels, "fp32", "fp32")
