@@ -1230,11 +1230,14 @@ using SCfgSmall = SCfg<128, 48, 4, 1, 3>;   // N <= 96
 // BF16, long reductions onto wide outputs without a mask to load: 64 x 96 per
 // wave reads 10 KB of LDS for 24 matrix instructions where 32 x 144 reads 11 KB
 // for 18 (8192 x 2880 x 2880 187 -> 175 us; with the mask, whose loads then do
-// not fit in registers ahead of the epilogue, 203 -> 228 us)
+// not fit in registers ahead of the epilogue, 203 -> 228 us).  From bfloat16
+// rows only: of float32 ones a ring of three fills 115 KB, one block to a
+// compute unit (the same product 213 -> 260 us, 120000 x 720 x 720 314 -> 460)
 using SCfgWide = SCfg<256, 96, 4, 1, 3>;
 // BF16, too few rows for a block per compute unit: small tiles, and a ring deep
 // enough that a block waits for memory once and not at every stage (8192 x 135
-// x 2880, 64 blocks: 47 -> 27 us; with a ring of four 36 us)
+// x 2880, 64 blocks: 47 -> 27 us; with a ring of four 36 us).  2000 rows, 2880
+// onto 960, 112 blocks: 63 -> 79 us; 1440 onto 720, 80 blocks, 2000 rows gain
 using SCfgFew = SCfg<64, 48, 4, 1, 8>;
 // FP32: the tile that takes the fewest stage times for the batch at hand.  A
 // stage (32 k) of one block took, in us, with up to half of the chip's blocks
@@ -1298,10 +1301,10 @@ int stream_table_c(AO ao, BO bo, CS cs, const TableGemm &t, hipStream_t st) {
     }
   } else {
     if (t.N <= 96) return run_stream<OP, SCfgSmall, F32>(ao, bo, cs, t.M, t.N, t.K, st);
-    if constexpr (!CS::kMask)
+    if constexpr (!CS::kMask && std::is_same_v<AO, SKb>)
       if (t.N > 144 && t.K > 256 && (t.M + 255) / 256 * ((t.N + 95) / 96) >= 512)
         return run_stream<OP, SCfgWide, F32>(ao, bo, cs, t.M, t.N, t.K, st);
-    if ((t.M + 127) / 128 * ((t.N + 143) / 144) < 128)
+    if ((t.M + 127) / 128 * ((t.N + 143) / 144) <= 96)
       return run_stream<OP, SCfgFew, F32>(ao, bo, cs, t.M, t.N, t.K, st);
     return run_stream<OP, SCfgNarrow, F32>(ao, bo, cs, t.M, t.N, t.K, st);
   }

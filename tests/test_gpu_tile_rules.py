@@ -49,3 +49,13 @@ def _products(C, O, voxels, prec, store):
 def test_rows_of_pieces(case, voxels):
     _products(*case, voxels, "fp32", "fp32")
     _products(*case[::-1], voxels, "fp32", "fp32")
+
+
+# BF16: onto 2880 columns the small tiles take up to 96 tiles of 128 x 144 (512
+# rows), and the wide ones from 512 on, of bfloat16 rows only; onto 360 (three
+# column tiles) the small ones take up to 4 096 rows
+@pytest.mark.parametrize("store", ["fp32", "half"])
+@pytest.mark.parametrize("case,voxels", [((8, 64), v) for v in (511, 512, 513, 4353, 4609)] +
+                         [((64, 8), v) for v in (4095, 4096, 4097)])
+def test_bf16_lines(case, voxels, store):
+    _products(*case, voxels, "bf16", store)
