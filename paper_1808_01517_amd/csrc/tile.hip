@@ -736,13 +736,16 @@ int image_grad(const ImageGrad &x, int ks, hipStream_t st) {
 
 // Voxel slices: blocks for three rounds of the chip (two blocks per compute
 // unit) while a slice keeps 512 voxels; wide layers, whose partial matrices
-// are large (33 MB for 2880 x 2881), one round.
+// are large (33 MB for 2880 x 2881), one round.  Batches that leave compute
+// units without a block at that take slices down to 128 voxels (both gradients
+// of 8 -> 16 channels, order 6, 2000 voxels, masked, FP32: 108 us with three
+// slices, 58 so; float32 instructions on small tiles 81).
 static int grad_slices(int64_t V, int M, int N1, int most, int target_divisor) {
   using tile::GradCfg;
   const int big = std::max(M, N1), small = std::min(M, N1);
   const int tiles = (big + GradCfg::BM - 1) / GradCfg::BM * ((small + GradCfg::BN - 1) / GradCfg::BN);
   int s = (int)std::min<int64_t>(most, std::max(1, (tiles <= 128 ? 1536 : 512) / (tiles * target_divisor)));
-  s = (int)std::min<int64_t>(s, std::max<int64_t>(1, V / 512));
+  s = (int)std::min<int64_t>(s, std::max({int64_t(1), V / 512, std::min<int64_t>(V / 128, 256 / tiles)}));
   while (s > 1 && (V + tile::split_len(V, s) - 1) / tile::split_len(V, s) != s) --s;
   return s;
 }

@@ -1,7 +1,8 @@
 """Which tile a folded product takes, at the lines of the rules: FP32 rows that
 are not whole 16-byte pieces (odd channel counts at even orders, 45 entries a
 channel), around a tile's rows and its batch, up to and above the reduction from
-which they are treated like the others.
+which they are treated like the others; the BF16 tiles for few rows and for wide
+outputs; the voxel slices of the weight gradients.
 """
 import numpy as np
 import pytest
@@ -59,3 +60,25 @@ def test_rows_of_pieces(case, voxels):
                          [((64, 8), v) for v in (4095, 4096, 4097)])
 def test_bf16_lines(case, voxels, store):
     _products(*case, voxels, "bf16", store)
+
+
+# slices of 128 voxels up to a block for every compute unit, of 512 beyond: two
+# column tiles of 144 by one to three row tiles here
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("case,voxels", [((4, 5), v) for v in (1, 127, 128, 255, 256, 257, 2000, 8191, 70001)])
+def test_gradient_slices(case, voxels, masked, prec):
+    C, O = case
+    plan = dl.LSCPlan(dg.fibonacci_hemisphere(90), 8, 8, (8, 8), np.deg2rad(30), 0.006)
+    W = torch.from_numpy(np.ascontiguousarray(dg.lsc_weights(9, 0, C, O, plan.T)[0], dtype=np.float32)).to(DEV)
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    a = torch.randn(voxels, C, plan.K_in, device=DEV, generator=gen)
+    g, y = (torch.randn(voxels, O, plan.K_out, device=DEV, generator=gen) for _ in range(2))
+    _, Bnb, Pm = (torch.from_numpy(np.asarray(t)).double().to(DEV) for t in plan.tables())
+    Q = torch.einsum("ki,itj->tkj", Pm, Bnb.reshape(plan.m, plan.T, plan.K_in))
+    gm = (g * (y > 0) if masked else g).double()
+    dT = (gm.reshape(voxels, -1).t() @ a.reshape(voxels, -1).double()).reshape(O, plan.K_out, C, plan.K_in)
+    kw = {"a_out": y, "relu": True} if masked else {}
+    _, dW, db = dl.lsc_bwd(plan, a, W, g, need_input_grad=False, precision=prec, **kw)
+    check("dW", dW, torch.einsum("okcj,tkj->oct", dT, Q), prec, kind="sum")
+    check("db", db, (gm.sum(0) * Pm.sum(1)).sum(1), prec, kind="sum")
