@@ -198,8 +198,9 @@ typedef struct dlm_lsc_plan dlm_lsc_plan;
  *    neighbourhood matrices X into the workspace, row-dot them with the
  *    cyclic kernel, refit.  Workspace grows with the voxels per pass.  In
  *    DLM_FP32, where that takes fewer multiplications (O not much above C, K_in
- *    <= m, C m >= O K_in), the channels are mixed with the kernel before the
- *    resampling, with which they commute, and X is never formed.
+ *    <= m, C m >= O K_in) and, in the forward, a pass has voxels enough, the
+ *    channels are mixed with the kernel before the resampling, with which they
+ *    commute, and X is never formed.
  *  DLM_LSC_FOLDED -- by linearity of resample, row dot and refit, the layer
  *    is a_out[o] = sum_c T_oc a_in[c] + bias[o] P_m 1 with
  *    T_oc = sum_t W[o][c][t] (P_m B_t), B_t the resampling rows of tap t;

@@ -941,6 +941,16 @@ bool lsc_mix_first(const dlm_lsc_plan *p, int C, int O, dlm_precision prec) {
   return prec == DLM_FP32 && K <= m && C * m >= O * K && K * CTO + O * m * T * K < C * K * m * T + m * CTO;
 }
 
+// Whether a pass of V voxels in the forward, which in the other order sums T K
+// entries in a row, has the traffic it saves to show for them: 8 T (C m - O K)
+// bytes a voxel at about 3 TB/s against 35 ns an entry.  Order 8, us in the
+// paper's order and the other: 1 -> 1 channel, 256 voxels 21 and 49, 2 000 27 and
+// 47, 8 192 56 and 62; 8 -> 1, 256 voxels 32 and 49, 2 000 76 and 47; 32 -> 3, 256
+// voxels 78 and 51.  The adjoints gain at any size.
+bool lsc_mix_fwd_pays(const dlm_lsc_plan *p, int C, int O, int64_t V) {
+  return double(V) * (C * double(p->m) - double(O) * p->K_in) >= 13000.0 * p->K_in;
+}
+
 // Largest chunk (multiple of kMinChunk unless V is smaller) whose workspace fits.
 int64_t lsc_chunk(const dlm_lsc_plan *p, int C, int O, int64_t V, size_t ws_bytes) {
   int64_t hi = std::max<int64_t>(V, 1);
@@ -1437,7 +1447,7 @@ dlm_status dlm_lsc_fwd(const dlm_lsc_plan *p, const float *a_in, int C, const fl
   const int T = p->T, m = int(p->m);
   const int64_t P = p->m * T;
   const double CTO = double(C) * T * O;
-  const bool mix = lsc_mix_first(p, C, O, prec);
+  const bool mix = lsc_mix_first(p, C, O, prec) && lsc_mix_fwd_pays(p, C, O, std::min(V, Vc));
   const int K = p->K_in;
   {
     TimedScope ts("lsc_prepare_weights", stream, CTO * 12.0, 0.0);

@@ -92,3 +92,25 @@ def test_rows_beyond_32_bits():
     oplan = olsc.LSCPlan(g, 0, 0, (2,), np.deg2rad(30), 0.006)
     ref = olsc.lsc_forward(oplan, a[rows].double().cpu().numpy(), W, b, False)[0]
     check("out", out[rows], ref, "fp32")
+
+
+# the forward's line, in voxels a pass: 13 000 K <= V (C m - O K), just below, at
+# and above it, and a last pass of any size
+@pytest.mark.parametrize("case,line", [((32, 3, 8, 8, (8, 8), 90), 214), ((16, 16, 4, 4, (6, 6), 60), 271),
+                                       ((9, 1, 4, 2, (6,), 30), 765), ((5, 4, 2, 4, (3, 4, 5), 45), 389)])
+def test_mixed_forward_from_its_line_on(case, line):
+    C, O, L_in, L_out, ks, m = case
+    g = dg.fibonacci_hemisphere(m)
+    oplan = olsc.LSCPlan(g, L_in, L_out, ks, np.deg2rad(30), 0.006)
+    plan = dl.LSCPlan(g, L_in, L_out, ks, np.deg2rad(30), 0.006)
+    assert (line - 1) * (C * m - O * plan.K_in) < 13000 * plan.K_in <= line * (C * m - O * plan.K_in)
+    W, b = (x.astype(np.float32).astype(np.float64) for x in dg.lsc_weights(11, 0, C, O, plan.T))
+    V = 2 * line + 65
+    a = np.random.default_rng(11).standard_normal((V, C, plan.K_in)).astype(np.float32).astype(np.float64)
+    ref = olsc.lsc_forward(oplan, a, W, b, True)[0]
+    ag, Wg, bg = cuda(a), cuda(W), cuda(b)
+    for n in (line - 1, line, line + 1, V):
+        check("out", dl.lsc_fwd(plan, ag[:n], Wg, bg, relu=True, form="resample"), ref[:n], "fp32")
+    for per in (line - 1, line, line + 63):
+        ws = dl.Workspace(dl.lsc_workspace_bytes(plan, C, O, per, "fp32", "resample"), DEV)
+        check("passes", dl.lsc_fwd(plan, ag, Wg, bg, relu=True, form="resample", workspace=ws), ref, "fp32")
