@@ -476,20 +476,21 @@ def lsc_bwd_image(plan: LSCPlan, a, W: torch.Tensor, g: torch.Tensor, bits=None,
     may be None where neither dW nor dbias is wanted."""
     g = _f32_dev(g, "da_out")
     W = _f32_dev(W, "W").reshape(W.shape[0], W.shape[1], -1)
-    O, Cin, _ = W.shape
+    O, Cin, T = W.shape
     need_dW = need_weight_grad or need_bias_grad
     if a is not None:
         a = _f32_dev(a, "a_in")
     elif need_dW:
         raise ValueError("a_in is needed for dW and dbias")
     prec = precision_code(precision)
-    B, P, dev = g.shape[0], g.shape[2:].numel(), g.device
-    in_shape = (B, Cin * plan.K_in, *g.shape[2:]) if a is None else tuple(a.shape)
-    if tuple(g.shape[1:2]) != (O * plan.K_out,) or W.shape[2] != plan.T or \
-            in_shape[:2] != (B, Cin * plan.K_in) or torch.Size(in_shape[2:]).numel() != P:
-        raise ValueError(f"shapes: a_in {None if a is None else in_shape}, da_out {tuple(g.shape)}, "
+    gs, dev = g.shape, g.device
+    B, P = gs[0], gs[2:].numel()
+    in_shape = (B, Cin * plan.K_in, *gs[2:]) if a is None else a.shape
+    if len(gs) < 2 or gs[1] != O * plan.K_out or T != plan.T or len(in_shape) < 2 or in_shape[0] != B or \
+            in_shape[1] != Cin * plan.K_in or (a is not None and a.shape[2:].numel() != P):
+        raise ValueError(f"shapes: a_in {None if a is None else tuple(in_shape)}, da_out {tuple(gs)}, "
                          f"W {tuple(W.shape)}, plan K_in={plan.K_in} K_out={plan.K_out} T={plan.T}")
-    words = B * g.shape[1] * ((P + 15) // 16)
+    words = B * gs[1] * ((P + 15) // 16)
     if bits is not None and (bits.element_size() != 2 or not bits.is_cuda or not bits.is_contiguous() or
                              bits.numel() != words):
         raise ValueError(f"bits must be a contiguous device tensor of {words} 16-bit words")
